@@ -12,8 +12,7 @@
 // k-slice selected by (l div 32), the same slice for Q and K, so no transpose or LDS staging is
 // needed.  A tile's 32 x 32 results sit 16 per lane: column = l mod 32, row = 8*(v/4) + 4*(l/32) + v%4.
 //
-// One workgroup per unit at a time, of as many waves as the prompt has blocks of 32 queries (at most four);
-// wave w owns query blocks w, w + waves, ...
+// One workgroup per unit at a time.
 // Prompts of up to 128 tokens (one block per wave; the case the decode path's prompts fall in): the workgroup
 // fetches the unit's Q and K once, fully coalesced, and hands the matrix cores their fragments through LDS; the
 // tiles are taken as K Q^T so that a query's softmax statistics stay inside a lane pair and only the column
@@ -21,12 +20,11 @@
 // while working on the current one.  This form is bound by HBM: at n = 64, d = 128 a unit does 1 MFLOP on 32 KB,
 // and what used to hold it back was the softmax bookkeeping on the vector ALUs (about 1100 instructions per
 // wave with the queries along the registers, about 400 now), not the matrix cores or the memory.
-// Longer prompts make, per query block, two sweeps over the key blocks up to the diagonal, operands read
-// straight from memory in fragment layout: the first keeps a running max and sum per lane and result register
-// and merges them over the 32 lanes of a row once at its end, the second recomputes the tile, normalises and
-// adds the tile's column sums into a wave-private LDS array.  In both forms the waves' arrays are added in a
-// fixed order at the end (bit-reproducible, no atomics).
+// Longer prompts take two sweeps over the tiles on or below the diagonal -- the rows' maxima and sums, then the
+// column sums -- in which one operand stays in registers and the other streams through LDS
+// (prefill_scores_long_kernel).  Nothing is added across waves but in a fixed order (bit-reproducible, no atomics).
 #include <cmath>
+#include <type_traits>
 
 #include "ssd_device.h"
 
@@ -59,26 +57,6 @@ template <> struct Mma<float> {
     }
 };
 
-// max / sum over the 32 lanes that share (lane div 32): DPP inside a 16-lane row, one swap across rows
-static __device__ __forceinline__ float half_max(float v) {
-    v = fmaxf(v, dpp_f<0xB1>(v));
-    v = fmaxf(v, dpp_f<0x4E>(v));
-    v = fmaxf(v, dpp_f<0x141>(v));
-    v = fmaxf(v, dpp_f<0x140>(v));
-    float a, b;
-    rows_pair(v, a, b);
-    return fmaxf(a, b);
-}
-static __device__ __forceinline__ float half_sum(float v) {
-    v += dpp_f<0xB1>(v);
-    v += dpp_f<0x4E>(v);
-    v += dpp_f<0x141>(v);
-    v += dpp_f<0x140>(v);
-    float a, b;
-    rows_pair(v, a, b);
-    return a + b;
-}
-
 struct PrefillArgs {
     const char *Q;
     const char *K;
@@ -88,53 +66,6 @@ struct PrefillArgs {
     int row_bytes;
     float qscale;        // softmax scale * log2(e)
 };
-
-// Fragments of one block of 32 rows (queries or keys): row = first + (lane mod 32), clamped to the last row.
-template <typename T, int D>
-static __device__ __forceinline__ void load_block(const char *base, int first, int n, int row_bytes, int l32, int half,
-                                                  typename Mma<T>::Frag (&f)[D / Mma<T>::KSTEP]) {
-    int row = first + l32;
-    if (row > n - 1) row = n - 1;                          // rows past the end repeat the last one; masked later
-#pragma unroll
-    for (int ks = 0; ks < D / Mma<T>::KSTEP; ++ks) f[ks] = Mma<T>::load(base + (size_t)row * row_bytes, ks, half);
-}
-
-// One 32 x 32 tile of scaled logits, masked where key > query (causal) or either lies beyond n.
-template <typename T, int D>
-static __device__ __forceinline__ void logits_tile(const typename Mma<T>::Frag (&qa)[D / Mma<T>::KSTEP],
-                                                   const typename Mma<T>::Frag (&kf)[D / Mma<T>::KSTEP], int qb, int kb, int n,
-                                                   int l32, int half, float qscale, float (&z)[16]) {
-    f32x16_t c = {0.f};
-#pragma unroll
-    for (int ks = 0; ks < D / Mma<T>::KSTEP; ++ks) c = Mma<T>::mma(qa[ks], kf[ks], c);
-    const int key = kb * 32 + l32;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int row = qb * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
-        z[v] = (key < n && key <= row && row < n) ? c[v] * qscale : NEG_BIG;
-    }
-}
-
-// Row maxima and sums held per lane -> per query row (over the 32 lanes that share it); l becomes 1 / sum.
-static __device__ __forceinline__ void merge_rows(float (&m)[16], float (&l)[16]) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const float m_row = half_max(m[v]);
-        const float l_row = half_sum(l[v] * fast_exp2(m[v] - m_row));
-        m[v] = m_row;
-        l[v] = l_row > 0.f ? __builtin_amdgcn_rcpf(l_row) : 0.f;
-    }
-}
-
-// Sum over the tile's 32 queries of the normalised probabilities of key (lane mod 32); valid in lanes 0..31.
-static __device__ __forceinline__ float column_sum(const float (&z)[16], const float (&m)[16], const float (&inv_l)[16]) {
-    float cs = 0.f;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) cs += z[v] > NEG_BIG * 0.5f ? fast_exp2(z[v] - m[v]) * inv_l[v] : 0.f;
-    float lo, hi;
-    halves_pair(cs, lo, hi);                               // the other 16 rows of the tile live in the other half
-    return lo + hi;
-}
 
 static __device__ __forceinline__ void write_scores(const PrefillArgs &a, const float *colsum, int waves, int unit) {
     __syncthreads();
@@ -146,55 +77,7 @@ static __device__ __forceinline__ void write_scores(const PrefillArgs &a, const 
     }
 }
 
-// Any prompt length: wave w owns query blocks w, w + waves, ...; key tiles are fetched in both sweeps.
-template <typename T, int D>
-__global__ __launch_bounds__(256) void prefill_scores_kernel(PrefillArgs a) {
-    typedef typename Mma<T>::Frag Frag;
-    constexpr int NK = D / Mma<T>::KSTEP;
-    extern __shared__ float colsum[];                      // [waves][n]
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int waves = blockDim.x >> 6;
-    const int lane = threadIdx.x & 63;
-    const int half = lane >> 5;
-    const int l32 = lane & 31;
-    const int n = a.n;
-    const size_t unit_off = (size_t)blockIdx.x * (size_t)n * (size_t)a.row_bytes;
-    const char *Qu = a.Q + unit_off;
-    const char *Ku = a.K + unit_off;
-    float *mine = colsum + (size_t)w * n;
-    for (int j = lane; j < n; j += 64) mine[j] = 0.f;      // only this wave touches `mine` until the final sum
-
-    const int n_blocks = (n + 31) / 32;
-    for (int qb = w; qb < n_blocks; qb += waves) {
-        Frag qa[NK], kf[NK];
-        load_block<T, D>(Qu, qb * 32, n, a.row_bytes, l32, half, qa);
-        float m[16], l[16], z[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) { m[v] = NEG_BIG; l[v] = 0.f; }
-        for (int kb = 0; kb <= qb; ++kb) {                 // sweep 1: per-lane running max and sum
-            load_block<T, D>(Ku, kb * 32, n, a.row_bytes, l32, half, kf);
-            logits_tile<T, D>(qa, kf, qb, kb, n, l32, half, a.qscale, z);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float m_new = fmaxf(m[v], z[v]);
-                const float p = z[v] > NEG_BIG * 0.5f ? fast_exp2(z[v] - m_new) : 0.f;
-                l[v] = l[v] * fast_exp2(m[v] - m_new) + p;
-                m[v] = m_new;
-            }
-        }
-        merge_rows(m, l);
-        for (int kb = 0; kb <= qb; ++kb) {                 // sweep 2: normalised column sums
-            load_block<T, D>(Ku, kb * 32, n, a.row_bytes, l32, half, kf);
-            logits_tile<T, D>(qa, kf, qb, kb, n, l32, half, a.qscale, z);
-            const float cs = column_sum(z, m, l);
-            const int key = kb * 32 + l32;
-            if (half == 0 && key < n) mine[key] += cs;
-        }
-    }
-    write_scores(a, colsum, waves, (int)blockIdx.x);
-}
-
-// Fragment of an operand block that was staged in LDS (rows of `stride` bytes): what Mma<T>::load takes from memory.
+// Fragment of an operand block that was staged in LDS: what Mma<T>::load takes from memory.
 template <typename T> static __device__ __forceinline__ typename Mma<T>::Frag lds_frag(const unsigned char *row, int ks, int half);
 template <> __device__ __forceinline__ uint4 lds_frag<bf16_t>(const unsigned char *row, int ks, int half) {
     return *reinterpret_cast<const uint4 *>(row + (ks * Mma<bf16_t>::KSTEP + 8 * half) * 2);
@@ -392,6 +275,232 @@ __global__ __launch_bounds__(64 * KT) void prefill_scores_short_kernel(PrefillAr
     }
 }
 
+// ---- prompts of more than 128 tokens ----------------------------------------------------------------------------
+//
+// Two sweeps over the 32 x 32 tiles on or below the diagonal, the same loop with the operands' roles exchanged:
+//   sweep 1, K Q^T: queries stay, keys stream.  A lane pair (l, l + 32) owns one query, the tile's keys lie along
+//            its registers: running maximum and sum of a query never leave the lane until one exchange at the end.
+//   sweep 2, Q K^T: keys stay, queries stream.  A lane pair owns one key, the tile's queries lie along its
+//            registers: the key's column sum never leaves the lane until one exchange at the end; the queries'
+//            maxima and 1 / sums come from LDS as broadcasts.
+// The operand that stays sits in registers (NS tiles per wave, fragment layout); the one that streams passes through
+// LDS, STAGE rows at a time, fetched once per workgroup with coalesced loads a stage ahead and read by every wave, so a
+// wave reads a streamed fragment once for its NS tiles.  A workgroup holds WAVES * NS tiles at a time and its waves
+// pair tile w with tile WAVES * NS - 1 - w, so all of them meet the diagonal after the same amount of work.
+// What bounds it: the vector ALUs' share.  Per tile and lane sweep 1 takes 16 exponentials (8 cycles each), 8 three-way
+// maxima, 16 multiply-adds and 16 adds, sweep 2 16 exponentials and 32 multiply-adds: 300 cycles of a SIMD each,
+// beside 256 of its matrix core (d = 128, bf16).  Keeping a whole row's exponentials instead of taking them twice
+// would need 192 KB of registers per 32 queries at 1500 tokens.  Measured at 256 units of 1500 tokens (bf16, d = 128):
+// 839 -> 195 us (counters: vector ALUs 44 % busy, matrix cores 31 %; the rest is the waves of a SIMD waiting for each
+// other at the stages' barriers).  One wave per query block with all operands read from memory in fragment layout,
+// which is what the 839 us were, touched 32 rows per load.  Tried on this form, no faster: 16 waves of one tile, 12 of
+// two, stages of 128 rows, three stages with the next fragments read ahead, held tiles brought in through LDS, and
+// one logarithm of the sum per query in place of maximum and 1 / sum (which doubles the error against 64 bits).
+static __device__ __forceinline__ void arrived(uint4 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
+static __device__ __forceinline__ void arrived(float &v) { asm volatile("" : "+v"(v)); }
+
+template <typename T> struct LongShape;
+template <> struct LongShape<bf16_t> { static constexpr int NS = 2, STAGE = 64; };
+template <> struct LongShape<float> { static constexpr int NS = 1, STAGE = 32; };      // (fp32 fragments take twice the registers and LDS)
+
+template <typename T, int D, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void prefill_scores_long_kernel(PrefillArgs a) {
+    typedef typename Mma<T>::Frag Frag;
+    constexpr int NK = D / Mma<T>::KSTEP;
+    constexpr int NS = LongShape<T>::NS, STAGE = LongShape<T>::STAGE;
+    constexpr int ROW = D * (int)sizeof(T);
+    constexpr int STRIDE = ROW + 16;                       // conflict-free both ways, as in the short kernel
+    constexpr int FPR = ROW / 16;
+    constexpr int THREADS = 64 * WAVES;
+    constexpr int NF = STAGE * FPR / THREADS;              // 16-byte fragments per thread and stage
+    static_assert(NF * THREADS == STAGE * FPR, "a stage divides evenly over the workgroup");
+    constexpr int HELD = WAVES * NS;                       // tiles the workgroup holds at a time
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int half = lane >> 5;
+    const int l32 = lane & 31;
+    const int n = a.n;
+    const int n_tiles = (n + 31) / 32;
+    float *row_max = reinterpret_cast<float *>(lds_raw + 2 * STAGE * STRIDE);        // [n_tiles * 32]
+    float *row_inv = row_max + n_tiles * 32;                                         // 1 / sum; 0 for queries beyond n
+    const size_t unit_off = (size_t)blockIdx.x * (size_t)n * (size_t)ROW;
+
+    auto sweep = [&](auto second, const char *held_base, const char *stream_base) {
+        constexpr bool COLS = decltype(second)::value;     // sweep 2
+        for (int first = 0; first < n_tiles; first += HELD) {
+            int tile[NS];
+            Frag keep[NS][NK];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                tile[s] = first + (s == 0 ? w : HELD - 1 - w);
+                int row = tile[s] * 32 + l32;
+                row = row < n ? row : n - 1;               // rows past the end repeat the last one
+#pragma unroll
+                for (int ks = 0; ks < NK; ++ks) keep[s][ks] = Mma<T>::load(held_base + (size_t)row * ROW, ks, half);
+            }
+            // wait for them here: left pending across the loop below, every use of them would wait for the newest
+            // request as well, which is the stage ahead
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int ks = 0; ks < NK; ++ks) arrived(keep[s][ks]);
+            // sweep 1: of the lane's query, running maximum (log2 domain) and sum; sweep 2: of the lane's key, the
+            // column sum as a compensated pair (one term per tile)
+            float st0[NS], st1[NS];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) { st0[s] = COLS ? 0.f : NEG_BIG; st1[s] = 0.f; }
+
+            const int from = COLS ? first * 32 : 0;                                   // streamed rows [from, to)
+            const int to = COLS ? n : (first + HELD) * 32 < n ? (first + HELD) * 32 : n;
+            u32x4_nt_t ahead[NF];
+            auto fetch = [&](int row0) {
+#pragma unroll
+                for (int i = 0; i < NF; ++i) {
+                    const int f = (int)threadIdx.x + i * THREADS;
+                    int r = row0 + f / FPR;
+                    r = r < n ? r : n - 1;
+                    ahead[i] = *reinterpret_cast<const u32x4_nt_t *>(stream_base + (size_t)r * ROW + (f % FPR) * 16);
+                }
+            };
+            auto stash = [&](int buf) {
+#pragma unroll
+                for (int i = 0; i < NF; ++i) {
+                    const int f = (int)threadIdx.x + i * THREADS;
+                    *reinterpret_cast<u32x4_nt_t *>(lds_raw + buf * (STAGE * STRIDE) + (f / FPR) * STRIDE + (f % FPR) * 16) = ahead[i];
+                }
+            };
+            auto fragments = [&](int buf, int sub, Frag (&fr)[NK]) {
+                const unsigned char *frow = lds_raw + buf * (STAGE * STRIDE) + (sub * 32 + l32) * STRIDE;
+#pragma unroll
+                for (int ks = 0; ks < NK; ++ks) fr[ks] = lds_frag<T>(frow, ks, half);
+            };
+            auto product = [&](const Frag (&fr)[NK], int s) {
+                f32x16_t c = {0.f};
+#pragma unroll
+                for (int ks = 0; ks < NK; ++ks) c = Mma<T>::mma(fr[ks], keep[s][ks], c);
+                return c;
+            };
+            // rm, ri: maxima and 1 / sums of the tile's queries, register by register (sweep 2)
+            // A logit that is not a number counts as masked; the tests for it look at one value per lane and tile.
+            auto absorb = [&](f32x16_t &c, int s, const float (&rm)[16], const float (&ri)[16]) {
+                float p0 = 0.f, p1 = 0.f;
+                auto drop_nan = [&]() {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) c[v] = c[v] == c[v] ? c[v] : -INFINITY;
+                };
+                if constexpr (!COLS) {
+                    auto tile_max = [&]() {
+                        float mx = c[0];
+#pragma unroll
+                        for (int v = 1; v < 16; ++v) mx = __builtin_elementwise_maximum(mx, c[v]);       // NaN if one of them is
+                        return mx;
+                    };
+                    float mx = tile_max();
+                    if (__any(mx != mx)) { drop_nan(); mx = tile_max(); }
+                    const float m_new = fmaxf(st0[s], mx * a.qscale);                 // qscale > 0; finite also where all keys are masked
+#pragma unroll
+                    for (int v = 0; v < 16; v += 2) {
+                        p0 += fast_exp2(fmaf(c[v], a.qscale, -m_new));
+                        p1 += fast_exp2(fmaf(c[v + 1], a.qscale, -m_new));
+                    }
+                    st1[s] = fmaf(st1[s], fast_exp2(st0[s] - m_new), p0 + p1);
+                    st0[s] = m_new;
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 16; v += 2) {
+                        p0 = fmaf(fast_exp2(fmaf(c[v], a.qscale, -rm[v])), ri[v], p0);
+                        p1 = fmaf(fast_exp2(fmaf(c[v + 1], a.qscale, -rm[v + 1])), ri[v + 1], p1);
+                    }
+                    if (__any(p0 + p1 != p0 + p1)) {
+                        drop_nan();
+                        p0 = p1 = 0.f;
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) p0 = fmaf(fast_exp2(fmaf(c[v], a.qscale, -rm[v])), ri[v], p0);
+                    }
+                    // st0 + st1 += p0 + p1 without losing what st0 cannot hold (terms are not negative, so sums over
+                    // thousands of queries would otherwise drift by a rounding per tile)
+                    const float add = (p0 + p1) + st1[s];
+                    const float sum = st0[s] + add;
+                    st1[s] = add - (sum - st0[s]);
+                    st0[s] = sum;
+                }
+            };
+            auto streamed = [&](int buf, int sub, int t) {          // one streamed tile against the tiles this wave holds
+                bool on[NS], any = false;                  // on or below the diagonal (wave-uniform)
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    on[s] = t < n_tiles && tile[s] < n_tiles && (COLS ? t >= tile[s] : t <= tile[s]);
+                    any = any || on[s];
+                }
+                if (!any) return;
+                Frag fr[NK];
+                fragments(buf, sub, fr);
+                float rm[16], ri[16];
+                if constexpr (COLS) {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const float4 x = *reinterpret_cast<const float4 *>(row_max + t * 32 + 8 * g + 4 * half);
+                        const float4 y = *reinterpret_cast<const float4 *>(row_inv + t * 32 + 8 * g + 4 * half);
+                        ri[4 * g] = y.x; ri[4 * g + 1] = y.y; ri[4 * g + 2] = y.z; ri[4 * g + 3] = y.w;
+                        rm[4 * g] = x.x; rm[4 * g + 1] = x.y; rm[4 * g + 2] = x.z; rm[4 * g + 3] = x.w;
+                    }
+                }
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    if (!on[s]) continue;
+                    f32x16_t c = product(fr, s);
+                    // register v of the tile is streamed row 8*(v/4) + 4*half + v%4; the diagonal tile is masked where key > query
+                    if (t == tile[s]) {
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            const int r = (v >> 2) * 8 + half * 4 + (v & 3);
+                            c[v] = (COLS ? l32 <= r : r <= l32) ? c[v] : -INFINITY;
+                        }
+                    }
+                    absorb(c, s, rm, ri);
+                }
+            };
+            fetch(from);
+            __syncthreads();                               // everybody is done with the buffers (and, sweep 2, the statistics are written)
+            stash(0);
+            int cur = 0;
+            for (int row0 = from; row0 < to; row0 += STAGE, cur ^= 1) {
+                __syncthreads();                           // this stage is in LDS, the other buffer is free
+                const bool more = row0 + STAGE < to;
+                if (more) fetch(row0 + STAGE);
+                for (int sub = 0; sub < STAGE / 32; ++sub) streamed(cur, sub, row0 / 32 + sub);
+                if (more) stash(cur ^ 1);
+            }
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                if (tile[s] >= n_tiles) continue;
+                const int row = tile[s] * 32 + l32;        // this lane's query or key
+                float x, y;
+                if constexpr (!COLS) {
+                    halves_pair(st0[s], x, y);
+                    const float m_row = fmaxf(x, y);
+                    halves_pair(st1[s] * fast_exp2(st0[s] - m_row), x, y);
+                    if (half == 0) {
+                        row_max[row] = m_row;
+                        row_inv[row] = row < n && x + y > 0.f ? 1.0f / (x + y) : 0.f;      // (0: every logit of the query masked)
+                    }
+                } else {
+                    halves_pair(st0[s], x, y);
+                    if (half == 0 && row < n) a.score_out[(size_t)blockIdx.x * (size_t)n + row] = x + y;
+                }
+            }
+        }
+    };
+    sweep(std::false_type{}, a.Q + unit_off, a.K + unit_off);
+    sweep(std::true_type{}, a.K + unit_off, a.Q + unit_off);
+}
+
+// LDS of the long kernel: two stages of the streamed operand and the queries' statistics.
+template <typename T> static size_t long_lds_bytes(int n, int row_bytes) {
+    return 2 * (size_t)LongShape<T>::STAGE * (size_t)(row_bytes + 16) + (size_t)((n + 31) / 32 * 32) * 2 * sizeof(float);
+}
+
 // Grid of a kernel whose workgroups walk the units with a stride of the grid size: as many workgroups as are
 // resident at once (workgroups per compute unit x compute units of the current device), trimmed so that every
 // workgroup gets the same number of units, give or take one at the very end.  0 on failure.
@@ -434,7 +543,6 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
     a.qscale = (softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)d)) * LOG2E;
     const int n_blocks = (n_src + 31) / 32;
     const int waves = n_blocks < 4 ? n_blocks : 4;
-    const size_t lds_long = (size_t)waves * (size_t)n_src * sizeof(float);
     const size_t lds_short = short_lds_bytes(waves, n_src, a.row_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const dim3 grid((unsigned)n_units), block(64u * waves);
@@ -452,11 +560,19 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
             else hipLaunchKernelGGL((prefill_scores_short_kernel<T_, D_, KT_>), g, block, lds_short, s, a);                     \
         }                                                                                                                       \
     } while (0)
+#define SSD_PREFILL_LONG(T_, D_, WAVES_)                                                                                         \
+    do {                                                                                                                        \
+        const void *fn = reinterpret_cast<const void *>(&prefill_scores_long_kernel<T_, D_, WAVES_>);                           \
+        const size_t lds = long_lds_bytes<T_>(n_src, a.row_bytes);                                                              \
+        if (lds > 65536) attr = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                  \
+        if (attr == hipSuccess) hipLaunchKernelGGL((prefill_scores_long_kernel<T_, D_, WAVES_>), grid, dim3(64 * WAVES_), lds, s, a); \
+    } while (0)
 #define SSD_PREFILL(T_, D_)                                                                                          \
     do {                                                                                                             \
         if (n_blocks <= 2) SSD_PREFILL_SHORT(T_, D_, 2);                                                             \
         else if (n_blocks <= 4) SSD_PREFILL_SHORT(T_, D_, 4);                                                        \
-        else hipLaunchKernelGGL((prefill_scores_kernel<T_, D_>), grid, block, lds_long, s, a);                       \
+        else if (n_blocks <= 8) SSD_PREFILL_LONG(T_, D_, 4);                                                         \
+        else SSD_PREFILL_LONG(T_, D_, 8);                                                                            \
     } while (0)
     if (dtype == SSD_BF16) {
         if (d == 128) SSD_PREFILL(bf16_t, 128); else SSD_PREFILL(bf16_t, 64);
@@ -464,6 +580,7 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
         if (d == 128) SSD_PREFILL(float, 128); else SSD_PREFILL(float, 64);
     }
 #undef SSD_PREFILL
+#undef SSD_PREFILL_LONG
 #undef SSD_PREFILL_SHORT
     if (attr != hipSuccess) return hip_fail(attr, "prefill score kernel attribute");
     hipError_t e = hipGetLastError();

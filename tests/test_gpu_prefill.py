@@ -62,6 +62,31 @@ def test_prefill_scores_largest_prompt_and_many_units():
     assert np.isfinite(got).all()
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("n", [131, 160, 161, 256, 287, 512, 513, 800])
+def test_prefill_scores_long_prompts_at_tile_and_workgroup_edges(dtype, d, n):
+    """Above 128 tokens: around whole tiles, around what a workgroup of 4 (up to 256 tokens) and of 8 waves holds at a
+    time.  A unit beside the last one must stay as it was.  Tolerance: fp32 sums of up to n terms, each within a few
+    roundings of 2^-24 of an argument below 2^5 (4e-6), against 64 bits."""
+    say("long prompt", dtype, d, n)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(n)
+    q = torch.randn((3, n, d), generator=g)
+    k = torch.randn((3, n, d), generator=g)
+    k[:, :: 50] *= 2.0                                            # some keys that every later query looks at
+    q = (q + 0.3 * k[:, :1]).to(tdt)
+    k = k.to(tdt)
+    out = torch.full((3, n), -5.0, device="cuda")
+    ssd.ssd_prefill_scores(q.cuda(), k.cuda(), 2, n, d, dtype, out)
+    torch.cuda.synchronize()
+    z = torch.matmul(q.double(), k.double().transpose(1, 2)) / np.sqrt(d)
+    ref = torch.softmax(z.masked_fill(torch.ones(n, n, dtype=torch.bool).triu(1), -np.inf), dim=-1).sum(dim=1)
+    got = out.cpu().double()
+    assert bool((got[2] == -5.0).all())
+    err = ((got[:2] - ref[:2]).abs() / ref[:2].clamp_min(1e-3)).max()
+    assert float(err) < 1e-5, float(err)
+
+
 def test_prefill_scores_bit_reproducible():
     g = torch.Generator().manual_seed(5)
     q = torch.randn((40, 200, 128), generator=g).to(torch.bfloat16).cuda()
