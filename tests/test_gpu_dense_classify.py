@@ -240,3 +240,26 @@ def test_copy_benchmark_copies_exactly_what_it_says():
     assert ssd.lib.ssd_bench_copy(dst.data_ptr(), src.data_ptr(), n, stream) == 0
     torch.cuda.synchronize()
     assert torch.equal(dst[:n], src) and bool((dst[n:] == 7).all())
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("P,T", [(1, 1), (1, 4), (3, 7), (5, 255), (2, 256), (17, 36), (4, 576), (2, 2050), (33, 3)])
+def test_classify_sums_every_term_once(P, T, offset):
+    """Pieces of four terms (T a multiple of 4, 16-byte aligned) and of one; rows shorter and longer than a workgroup's stride.
+    offset: the inputs start one float into an aligned allocation.  Tolerance: fp32 sums of P*T ratios below 1 over 512
+    partial sums, at most P*T/512 + 12 roundings of 2^-24 each."""
+    say("classify", P, T, offset)
+    L, H = 2, 3
+    g = torch.Generator(device="cuda").manual_seed(P * 10000 + T)
+    n = L * P * H * T
+    mem = torch.rand((2, n + 4), generator=g, device="cuda")
+    tot, far = mem[0, offset:offset + n], mem[1, offset:offset + n] * mem[0, offset:offset + n]
+    far = torch.cat((torch.zeros(offset, device="cuda"), far))[offset:]
+    tot[:: 13] = 0.0                                              # no mass: the term counts 0
+    s = torch.empty((L, H), device="cuda")
+    ty = torch.empty((L, H), dtype=torch.uint8, device="cuda")
+    ssd.ssd_classify_heads(far, tot, L, P, H, T, 0.4, s, ty)
+    f, t = far.double().view(L, P, H, T), tot.double().view(L, P, H, T)
+    ref = torch.where(t > 0, f / t.clamp_min(1e-300), torch.zeros_like(t)).sum(dim=(1, 3)) / (P * T)
+    assert float((s.double() - ref).abs().max()) <= (P * T / 512 + 12) * 2.0 ** -24
+    assert torch.equal(ty.bool(), s > 0.4)
