@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "ssd.h"
@@ -69,6 +70,13 @@ static constexpr int HMAX = 128;  // heads per layer
 struct HeadTable {
     uint16_t v[HMAX];
 };
+
+// Argument blocks carry what their launch needs and no more: one layer's entry or the whole table, and the table of
+// budgets only where they are given per head.  The runtime copies the block for every launch; with both tables always
+// in it (2.3 KB) a launch cost the host 3.9 us, with one entry 2.6.
+struct NoHeadTable {};
+template <bool HEADS> using HeadsOf = typename std::conditional<HEADS, HeadTable, NoHeadTable>::type;
+template <int LAYERS> struct LayersOf { LayerDesc layer[LAYERS]; };
 
 // ---- slot arithmetic of a spatial unit, the same on the host and in kernels ----
 // S sink slots, then a ring of RW slots (RW = W, or W + C when spatial heads use the row buffer).
@@ -152,6 +160,9 @@ int check_layers(const ssd_cache *c, int lb, int le);
 int ensure_events(ssd_cache *c);                                               // events of ssd_decode_step_split
 Geom make_geom(const ssd_cache *c, int l);                                     // geometry of layer l
 void fill_launch_meta(const ssd_cache *c, int lb, int le, LaunchMeta *out);   // le - lb <= LMAX
+template <int LAYERS> inline void fill_layers(const ssd_cache *c, int lb, int le, LayersOf<LAYERS> *out) {   // le - lb <= LAYERS
+    for (int i = 0; i < LAYERS; ++i) out->layer[i] = c->ldesc[lb + i < le ? lb + i : lb];   // entries past the run are never indexed
+}
 Segs spatial_segs(const ssd_cache *c, int l, const LayerState &st);
 Segs semantic_segs(const ssd_cache *c, int l, const LayerState &st);
 // Rows a fused append + attention streams from a spatial unit: everything retained after the append except
@@ -169,6 +180,7 @@ static inline bool per_head(const ssd_cache *c) { return !c->head_budget.empty()
 // whose heads agree is an ordinary layer with that window and budget)
 static inline bool heads_differ(const ssd_cache *c, int l) { return per_head(c) && c->heads_differ[l] != 0; }
 void fill_head_table(const ssd_cache *c, int l, HeadTable *out);
+static inline void fill_head_table(const ssd_cache *, int, NoHeadTable *) {}
 // end of the run of layers starting at lb that share layer lb's state, window and budget, at most LMAX long
 // (one layer when budgets are per head)
 int same_state_run(const ssd_cache *c, int lb, int le);

@@ -201,3 +201,48 @@ def test_cfg_mix_matches_oracle(dtype, B, V):
         assert (np.abs(got - ref) <= bound).all(), (gamma, float(np.abs(got - ref).max()))
         if gamma == 0.0:
             assert np.array_equal(got, p[0::2].float().numpy())
+
+
+@pytest.mark.parametrize("B,H", [(2, 4), (40, 16)])              # few units: a wide workgroup each; many: the narrow one
+@pytest.mark.parametrize("n", [5, 64, 70, 257, 300, 1024, 1500, 4096])
+@pytest.mark.parametrize("scores", ["spread", "few", "equal", "zero", "wide"])
+def test_dense_source_selection_is_the_sorted_one(B, H, n, scores):
+    """The kept set of the dense-source mode is what a sort by (score, lower position first) keeps, exactly, whatever the
+    scores look like to a radix descent: long-tailed, a handful of distinct values, all equal, all zero, 60 binary
+    orders of magnitude; the kept rows are the source's, bit for bit, in ascending order of position."""
+    from paper_2510_18716_amd.binding import make_config
+    if B * H > 512 and n > 1024:
+        pytest.skip("the same code at more memory")
+    M, R, W, S, d = 48, 1, 20, 1, 64
+    say("dense-source selection", B, H, n, scores)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    u = torch.rand((B, H, n), generator=g, device="cuda")
+    score = {"spread": -torch.log(u.clamp_min(1e-6)), "few": (u * 5).floor() * 0.25, "equal": torch.full_like(u, 0.7),
+             "zero": torch.zeros_like(u), "wide": torch.exp2(60 * u - 40)}[scores].contiguous()
+    K = torch.randn((B, H, n, d), generator=g, device="cuda").to(torch.bfloat16)
+    V = torch.randn((B, H, n, d), generator=g, device="cuda").to(torch.bfloat16)
+    ht = np.zeros((1, H), np.uint8)
+    ht[0, H // 2:] = ssd.SSD_SEMANTIC
+    cache = ssd.Cache(make_config(1, B, H, d, "bf16", W, S, M, R, R + 2), ht)
+    ssd.ssd_compress_kv(cache, 0, 1, K, V, score, n)
+    pos, count, kept_score = (t.cpu().numpy() for t in cache.export(0))
+    q = torch.zeros((1, B, H, d), dtype=torch.bfloat16, device="cuda")
+    out = torch.empty_like(q)
+    ssd.ssd_decode_attn(cache, 0, 1, q, out, False)               # zero query: the mean of the kept rows
+    torch.cuda.synchronize()
+    sc, Vh, got = score.cpu().numpy(), V.float().cpu().numpy(), out.float().cpu().numpy()[0]
+    n_cand = n - min(n, R)
+    for b in range(0, B, 7):
+        for h in range(H):
+            if h < H // 2:
+                want = sorted(set(range(min(S, n))) | set(range(max(S, n - W), n)))
+                assert sorted(p for p in pos[b, h] if p >= 0) == want
+            else:
+                order = np.lexsort((np.arange(n_cand), -sc[b, h, :n_cand]))[:M]
+                heavy = sorted(int(i) for i in order)
+                want = heavy + list(range(n_cand, n))
+                assert [int(p) for p in pos[b, h][:len(heavy)]] == heavy
+                assert [int(p) for p in pos[b, h][M:M + n - n_cand]] == want[len(heavy):]
+                assert np.array_equal(kept_score[b, h][:len(heavy)], sc[b, h][heavy])
+            assert count[b, h] == len(want)
+            np.testing.assert_allclose(got[b, h], Vh[b, h][want].mean(axis=0), atol=2e-2, rtol=1e-2)
