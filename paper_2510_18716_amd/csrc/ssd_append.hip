@@ -7,45 +7,61 @@
 
 namespace ssd {
 
-struct AppendArgs {
+template <int LAYERS, bool HEADS> struct AppendArgs {
     Geom g;
-    LaunchMeta lm;
     const char *k_new;
     const char *v_new;
-    int layer_off;       // index of that layer inside k_new / v_new
-    int n_units;         // layers * B * H
-    int lpr;             // 16-byte fragments per row
+    int layer_off;       // index of the launch's first layer inside k_new / v_new
+    int lpr_log2;        // 16-byte fragments per row: 8, 16 or 32
     int slot_sp;         // destination slot of spatial heads
     int slot_se;         // destination slot of semantic heads
     int pos;             // absolute position of the token
-    int heads;           // budgets per head: a spatial head's slot follows from its own window
-    HeadTable ht;
+    LayersOf<LAYERS> lm;
+    HeadsOf<HEADS> ht;   // budgets per head: a spatial head's slot follows from its own window
 };
 
-__global__ __launch_bounds__(256) void append_kernel(AppendArgs a) {
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int frag_per_unit = 2 * a.lpr;
-    const long long unit_ll = t / frag_per_unit;
-    if (unit_ll >= a.n_units) return;
-    const int unit = (int)unit_ll;
-    const int f = (int)(t % frag_per_unit);
-    const int kv = f / a.lpr;          // 0 = K, 1 = V
-    const int sub = f % a.lpr;
-    const int BH = a.g.B * a.g.H;
-    const int lrel = unit / BH;
-    const int rem = unit % BH;
-    const int b = rem / a.g.H, h = rem % a.g.H;
+// grid = (blocks over a sequence's heads and fragments, B, layers): nothing has to be divided.  A launch this small is
+// bound by its fixed cost; 512 units of 512 bytes.
+template <int LAYERS, bool HEADS>
+__global__ __launch_bounds__(256) void append_kernel(AppendArgs<LAYERS, HEADS> a) {
+    const int t = (int)(blockIdx.x * 256 + threadIdx.x);
+    const int h = t >> (a.lpr_log2 + 1);
+    if (h >= a.g.H) return;
+    const int b = blockIdx.y, lrel = LAYERS == 1 ? 0 : blockIdx.z;
+    const bool v = (t >> a.lpr_log2) & 1;
+    const size_t sub = (size_t)(t & ((1 << a.lpr_log2) - 1)) * 16u;
+    const size_t src_row = ((size_t)(a.layer_off + lrel) * a.g.B + b) * a.g.H + h;
+    const uint4 frag = *reinterpret_cast<const uint4 *>((v ? a.v_new : a.k_new) + src_row * (size_t)a.g.row_bytes + sub);
     const UnitRef u = unit_ref(a.g, a.lm.layer[lrel], b, h);
-    const size_t src_row = ((size_t)(a.layer_off + lrel) * BH + rem) * (size_t)a.g.row_bytes;
-    const char *src = (kv ? a.v_new : a.k_new) + src_row + (size_t)sub * 16u;
     int slot = u.sem ? a.slot_se : a.slot_sp;
-    if (a.heads && !u.sem) slot = ring_slot(a.g.S, a.ht.v[h] + (a.g.RW - a.g.W), a.pos);
-    char *dst = (kv ? u.V : u.K) + (size_t)slot * (size_t)a.g.row_bytes + (size_t)sub * 16u;
-    *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(src);
-    if (u.sem && f == 0) {
+    if constexpr (HEADS) {
+        if (!u.sem) slot = ring_slot(a.g.S, a.ht.v[h] + (a.g.RW - a.g.W), a.pos);
+    }
+    *reinterpret_cast<uint4 *>((v ? u.V : u.K) + (size_t)slot * (size_t)a.g.row_bytes + sub) = frag;
+    if (u.sem && sub == 0 && !v) {
         u.pos[slot] = a.pos;
         u.score[slot] = 0.f;
     }
+}
+
+template <int LAYERS, bool HEADS>
+static hipError_t launch_append(const ssd_cache *cache, int lb, int le, int layer_off, const void *k_new, const void *v_new, hipStream_t s) {
+    const ssd_config &cf = cache->cfg;
+    const LayerState &st = cache->st[lb];
+    AppendArgs<LAYERS, HEADS> a;
+    a.g = make_geom(cache, lb);
+    a.k_new = static_cast<const char *>(k_new);
+    a.v_new = static_cast<const char *>(v_new);
+    fill_layers(cache, lb, le, &a.lm);
+    a.layer_off = layer_off;
+    a.lpr_log2 = __builtin_ctz((unsigned)(a.g.row_bytes / 16));
+    a.pos = st.n;
+    a.slot_sp = spatial_slot(cache, lb, st.n);
+    a.slot_se = cache->Ml[lb] + (st.base + st.c) % cf.stage_cap;
+    fill_head_table(cache, lb, &a.ht);
+    const unsigned per_seq = (unsigned)cf.n_heads << (a.lpr_log2 + 1);
+    hipLaunchKernelGGL((append_kernel<LAYERS, HEADS>), dim3((per_seq + 255) / 256, (unsigned)cf.n_seqs, (unsigned)(le - lb)), dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace ssd
@@ -66,28 +82,12 @@ extern "C" int ssd_append_token(ssd_cache *cache, int layer_begin, int layer_end
             return fail(SSD_ERR_STAGE_OVERFLOW, "row buffer overflow: layer %d already buffers %d tokens (C=%d); call ssd_compress_kv",
                         l, cache->st[l].c, cf.stage_cap);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int BH = cf.n_seqs * cf.n_heads;
     for (int lb = layer_begin; lb < layer_end;) {
         const int le = same_state_run(cache, lb, layer_end);
-        const LayerState st = cache->st[lb];
         if (cache->launch_enabled) {
-            AppendArgs a;
-            a.g = make_geom(cache, lb);
-            a.k_new = static_cast<const char *>(k_new);
-            a.v_new = static_cast<const char *>(v_new);
-            fill_launch_meta(cache, lb, le, &a.lm);
-            a.layer_off = lb - layer_begin;
-            a.n_units = (le - lb) * BH;
-            a.lpr = a.g.row_bytes / 16;
-            a.pos = st.n;
-            a.slot_sp = spatial_slot(cache, lb, st.n);
-            a.slot_se = cache->Ml[lb] + (st.base + st.c) % cf.stage_cap;
-            a.heads = heads_differ(cache, lb) ? 1 : 0;
-            fill_head_table(cache, lb, &a.ht);
-            const long long threads = (long long)a.n_units * 2 * a.lpr;
-            const unsigned blocks = (unsigned)((threads + 255) / 256);
-            hipLaunchKernelGGL(append_kernel, dim3(blocks), dim3(256), 0, s, a);
-            hipError_t e = hipGetLastError();
+            const hipError_t e = heads_differ(cache, lb) ? launch_append<1, true>(cache, lb, le, lb - layer_begin, k_new, v_new, s)
+                                 : le - lb == 1 ? launch_append<1, false>(cache, lb, le, lb - layer_begin, k_new, v_new, s)
+                                                : launch_append<LMAX, false>(cache, lb, le, lb - layer_begin, k_new, v_new, s);
             if (e != hipSuccess) return hip_fail(e, "append launch");
         }
         for (int l = lb; l < le; ++l) {
