@@ -18,6 +18,7 @@
 // position on the way in) and SHARE (several waves share a unit: for launches of few units).  The plain
 // kernel pays for none of them.
 #include <algorithm>
+#include <type_traits>
 
 #include "ssd_select.h"
 
@@ -64,10 +65,22 @@ struct HeadOrder {
 // rank (1) and by sequence first (all 8 workgroups of a sequence together) differ by 7 %; 1, 2 and 4 are within 1 %.
 static constexpr int RANK_GROUPS = 2;
 
+// The argument block, in three sizes with one beginning: a launch over one layer (what a model issues) carries one table
+// entry, with budgets per head the head order after it, and only a launch over several layers the whole table.
+// The runtime copies the block for every launch: 2.4 KB of it (table and head order always) cost 3.9 us of host time
+// per launch against 2.6 us for a small one.
+struct StepArgsOne {
+    StepHot h;
+    LayerDesc layer;
+};
+struct StepArgsHeads {
+    StepHot h;
+    LayerDesc layer;
+    HeadOrder ho;
+};
 struct StepArgs {
     StepHot h;
     LaunchMeta lm;
-    HeadOrder ho;
 };
 
 // A wave reads its arguments with scalar loads from the kernel-argument segment.  Left to itself the
@@ -85,7 +98,8 @@ typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 static __device__ __forceinline__ void fetch_args(int lrel, StepHot &a, LayerDesc &ld) {
     static_assert(sizeof(StepHot) <= 256, "the fixed part is read as four 64-byte pieces");
     static_assert(sizeof(LayerDesc) == 56, "one table entry is read as three 16-byte pieces and one of 8 bytes");
-    static_assert(sizeof(StepArgs) >= 256 && sizeof(StepArgs) == sizeof(StepHot) + sizeof(LaunchMeta) + sizeof(HeadOrder), "layout of the argument block");
+    static_assert(sizeof(StepArgsOne) >= 256 && offsetof(StepArgsOne, layer) == sizeof(StepHot) && offsetof(StepArgs, lm) == sizeof(StepHot) &&
+                  offsetof(StepArgsHeads, layer) == sizeof(StepHot) && offsetof(StepArgsHeads, ho) == sizeof(StepArgsOne), "one beginning");
     const SSD_KERNARG char *kp = (const SSD_KERNARG char *)__builtin_amdgcn_kernarg_segment_ptr();
     struct { u32x16_t w[4]; } fixed;
     struct { u32x4_t w[3]; u32x2_t t; } entry;
@@ -129,7 +143,7 @@ static __device__ __forceinline__ void fetch_args(int lrel, StepHot &a, LayerDes
 
 // Entry `rank` of the launch's HeadOrder (two independent scalar loads from the kernel-argument segment).
 static __device__ __forceinline__ void fetch_head_order(int rank, int &head, int &budget) {
-    const SSD_KERNARG char *kp = (const SSD_KERNARG char *)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(StepHot) + sizeof(LaunchMeta);
+    const SSD_KERNARG char *kp = (const SSD_KERNARG char *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(StepArgsHeads, ho);
     const uint32_t wh = *reinterpret_cast<const SSD_KERNARG uint32_t *>(kp + offsetof(HeadOrder, head) + (size_t)(rank >> 2) * 4);
     const uint32_t wb = *reinterpret_cast<const SSD_KERNARG uint32_t *>(kp + offsetof(HeadOrder, budget) + (size_t)(rank >> 1) * 4);
     head = (int)((wh >> ((rank & 3) * 8)) & 0xffu);
@@ -196,14 +210,18 @@ static __device__ __forceinline__ uint4 rope_fragment(const uint4 &raw, const fl
 // once in LDS; wave 0 carries on alone.  For launches of few units, which would leave most of the chip's wave
 // slots empty.  The partial sums of the waves are combined in another order than one wave adds them: outputs
 // and scores of the two forms agree to rounding, not to the bit.
-template <typename T, int D, int CH, int WPB, bool FUSED, bool HEADS = false, bool ROPE = false, int SHARE = 1>
-__global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(StepArgs) {      // read through fetch_args
+// Args: the argument block the launch carries (StepArgs: several layers).
+template <typename Args, typename T, int D, int CH, int WPB, bool FUSED, bool HEADS = false, bool ROPE = false, int SHARE = 1>
+__global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {          // read through fetch_args
+    constexpr bool MANY = std::is_same<Args, StepArgs>::value;
+    static_assert(HEADS == std::is_same<Args, StepArgsHeads>::value, "budgets per head: one layer, with the head order");
     constexpr int VEC = Elem<T>::VEC;
     constexpr int LPR = D / VEC;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     StepHot a;
     LayerDesc ld;
-    fetch_args(HEADS ? 0 : blockIdx.z >> 1, a, ld);
+    const int lrel = MANY ? blockIdx.z >> 1 : 0;
+    fetch_args(lrel, a, ld);
 
     int t_m = a.m;
     const int t_c = a.c, t_base = a.base, t_R = a.R, t_lpr = a.lpr, t_new_pos = a.new_pos,
@@ -218,7 +236,6 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(StepArgs) {     
     // grid = (ceil(max heads of a type / WPB), B, 2 * layers): z selects the layer and the head type, the type
     // with more rows first, so that within a layer the long units are dispatched before the short ones and
     // all waves of a workgroup have units of one length
-    const int lrel = HEADS ? 0 : blockIdx.z >> 1;
     bool sem_unit;
     int local, h, seq, hb = 0;
     if constexpr (HEADS) {
@@ -293,6 +310,12 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(StepArgs) {     
     }
     float pre_score[2] = {0.f, 0.f};
     int pre_pos[2] = {0, 0};
+    // The row a compression after every token may promote is known beforehand: with one candidate in the row buffer that
+    // is not the new token (one_old), its oldest row.  Fetched with the scores it is in registers when the selection has
+    // decided; read only then, its round trip to memory ends the launch whenever one unit of it promotes (7B shape, two
+    // streams: 742 -> 737 us per step).
+    const bool one_old = compress && t_c - t_R == 1 && (!FUSED || t_R > 0);
+    uint4 pre_row = make_uint4(0, 0, 0, 0);               // lanes 0..LPR-1: the K row, LPR..2*LPR-1: the V row (LPR <= 32)
 
     // Runs once, right after the stream's first loads have been issued, so that nothing here delays them: the
     // running scores and positions of the first 128 rows (one or two per lane) are requested now and have
@@ -324,6 +347,8 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(StepArgs) {     
                 pre_score[k] = u.score[slot];
                 pre_pos[k] = u.pos[slot];
             }
+            const char *plane = (lane / LPR) & 1 ? u.V : u.K;             // unconditional (like the scores): a slot of the unit in any case
+            pre_row = *reinterpret_cast<const uint4 *>(plane + (size_t)(t_M + t_base) * (size_t)t_row_bytes + (size_t)sub * 16u);
         }
     };
     if (want_z)
@@ -465,6 +490,14 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(StepArgs) {     
     const bool ev_staged = e_idx >= t_m;
     const int n_move = n_old - (ev_staged ? 1 : 0);
     if (n_move <= 0) return;
+    if (one_old) {                                        // n_move == 1: it is that row, and e_idx >= 0 unless the heavy slots are not full yet
+        const int to = ev_heavy ? e_idx : t_m;
+        if (lane < 2 * LPR) *reinterpret_cast<uint4 *>((lane < LPR ? u.K : u.V) + (size_t)to * t_row_bytes + (size_t)sub * 16u) = pre_row;
+        const unsigned long long c0 = __shfl(my_key[0], t_m & 63), c1 = __shfl(my_key[1], t_m & 63);
+        const unsigned long long key = t_m < 64 ? c0 : c1;
+        if (lane == 0) { u.pos[to] = key_pos(key); u.score[to] = key_score(key); }
+        return;
+    }
     const int frag_per_tok = 2 * t_lpr;
     // k-th promoted candidate (oldest first) and k-th free heavy slot
     auto src_idx = [&](int k) { return t_m + k + ((ev_staged && k >= e_idx - t_m) ? 1 : 0); };
@@ -520,45 +553,44 @@ static void fill_head_order(const ssd_cache *c, int l, const LayerState &before,
     }
 }
 
-template <typename T, int D, int CH, int SHARE>
-static void launch_shared(const StepArgs &full, dim3 blocks, size_t lds, bool fused, bool heads, hipStream_t s) {
-    const bool rope = full.h.rope_layout != 0;
-    if (heads || rope) {                                  // four wave-loads per chunk only; the rotary step is always fused (the host sees to both)
-        if constexpr (CH == 4) {
-            if (rope && heads) hipLaunchKernelGGL((step_kernel<T, D, CH, 1, true, true, true, SHARE>), blocks, dim3(SHARE * 64), lds, s, full);
-            else if (rope) hipLaunchKernelGGL((step_kernel<T, D, CH, 1, true, false, true, SHARE>), blocks, dim3(SHARE * 64), lds, s, full);
-            else if (fused) hipLaunchKernelGGL((step_kernel<T, D, CH, 1, true, true, false, SHARE>), blocks, dim3(SHARE * 64), lds, s, full);
-            else hipLaunchKernelGGL((step_kernel<T, D, CH, 1, false, true, false, SHARE>), blocks, dim3(SHARE * 64), lds, s, full);
+// One launch of the variant (WPB units per workgroup, or one unit shared by SHARE waves) that the call asks for.  One
+// layer: the short argument block (four wave-loads per chunk, which is what the library picks; the other chunk sizes
+// exist for sweeps and take the long block).
+template <typename T, int D, int CH, int WPB, int SHARE>
+static void launch_variant(const StepArgs &full, const HeadOrder *ho, dim3 blocks, size_t lds, int layers, bool fused, hipStream_t s) {
+    const dim3 threads(WPB * SHARE * 64);
+    const bool rope = full.h.rope_layout != 0;            // always fused (checked by the entry point)
+    if constexpr (CH == 4) {
+        if (ho) {
+            const StepArgsHeads x = {full.h, full.lm.layer[0], *ho};
+            if (rope) hipLaunchKernelGGL((step_kernel<StepArgsHeads, T, D, CH, WPB, true, true, true, SHARE>), blocks, threads, lds, s, x);
+            else if (fused) hipLaunchKernelGGL((step_kernel<StepArgsHeads, T, D, CH, WPB, true, true, false, SHARE>), blocks, threads, lds, s, x);
+            else hipLaunchKernelGGL((step_kernel<StepArgsHeads, T, D, CH, WPB, false, true, false, SHARE>), blocks, threads, lds, s, x);
+            return;
         }
-        return;
-    }
-    if (fused) hipLaunchKernelGGL((step_kernel<T, D, CH, 1, true, false, false, SHARE>), blocks, dim3(SHARE * 64), lds, s, full);
-    else hipLaunchKernelGGL((step_kernel<T, D, CH, 1, false, false, false, SHARE>), blocks, dim3(SHARE * 64), lds, s, full);
-}
-
-template <typename T, int D, int CH, int WPB>
-static void launch_one(const StepArgs &full, dim3 blocks, size_t lds, bool fused, bool heads, hipStream_t s) {
-    const bool rope = full.h.rope_layout != 0;            // fused launches only (checked by the entry point)
-    if (heads || rope) {
-        // budgets per head, rotary embedding: one variant (four wave-loads per chunk) per workgroup size
-        if constexpr (CH == 4) {
-            if (rope && heads) hipLaunchKernelGGL((step_kernel<T, D, CH, WPB, true, true, true>), blocks, dim3(WPB * 64), lds, s, full);
-            else if (rope) hipLaunchKernelGGL((step_kernel<T, D, CH, WPB, true, false, true>), blocks, dim3(WPB * 64), lds, s, full);
-            else if (fused) hipLaunchKernelGGL((step_kernel<T, D, CH, WPB, true, true>), blocks, dim3(WPB * 64), lds, s, full);
-            else hipLaunchKernelGGL((step_kernel<T, D, CH, WPB, false, true>), blocks, dim3(WPB * 64), lds, s, full);
+        if (layers == 1) {
+            const StepArgsOne x = {full.h, full.lm.layer[0]};
+            if (rope) hipLaunchKernelGGL((step_kernel<StepArgsOne, T, D, CH, WPB, true, false, true, SHARE>), blocks, threads, lds, s, x);
+            else if (fused) hipLaunchKernelGGL((step_kernel<StepArgsOne, T, D, CH, WPB, true, false, false, SHARE>), blocks, threads, lds, s, x);
+            else hipLaunchKernelGGL((step_kernel<StepArgsOne, T, D, CH, WPB, false, false, false, SHARE>), blocks, threads, lds, s, x);
+            return;
         }
-        return;
+        if (rope) {
+            hipLaunchKernelGGL((step_kernel<StepArgs, T, D, CH, WPB, true, false, true, SHARE>), blocks, threads, lds, s, full);
+            return;
+        }
     }
-    if (fused) hipLaunchKernelGGL((step_kernel<T, D, CH, WPB, true>), blocks, dim3(WPB * 64), lds, s, full);
-    else hipLaunchKernelGGL((step_kernel<T, D, CH, WPB, false>), blocks, dim3(WPB * 64), lds, s, full);
+    if (fused) hipLaunchKernelGGL((step_kernel<StepArgs, T, D, CH, WPB, true, false, false, SHARE>), blocks, threads, lds, s, full);
+    else hipLaunchKernelGGL((step_kernel<StepArgs, T, D, CH, WPB, false, false, false, SHARE>), blocks, threads, lds, s, full);
 }
 
 // One launch over sequences [a.seq_off, a.seq_off + B) of the layers in `full`.  concurrent: the launch is one part of
 // a split call, so another part's launch runs beside it on another stream.
 template <typename T, int D>
-static hipError_t launch_step(StepArgs &full, const LaunchShape &shape, LaunchShape *used, int H, int max_sp_heads, int max_se_heads, int B,
-                              int layers, bool fused, bool heads, bool concurrent, int M, hipStream_t s) {
+static hipError_t launch_step(StepArgs &full, const HeadOrder *ho, const LaunchShape &shape, LaunchShape *used, int H, int max_sp_heads, int max_se_heads,
+                              int B, int layers, bool fused, bool concurrent, int M, hipStream_t s) {
     StepHot &a = full.h;
+    const bool heads = ho != nullptr;                     // budgets per head
     const int max_type_heads = max_sp_heads > max_se_heads ? max_sp_heads : max_se_heads;
     const int n_old = a.c - a.R, n_cand = a.m + n_old;
     // Launch shape by the number of units (measured on the 7B- and 1B-shaped workloads at 16 to 256 prompts).
@@ -605,10 +637,10 @@ static hipError_t launch_step(StepArgs &full, const LaunchShape &shape, LaunchSh
     const dim3 blocks = heads ? dim3((unsigned)RANK_GROUPS, (unsigned)B, (unsigned)(((H + wpb - 1) / wpb + RANK_GROUPS - 1) / RANK_GROUPS))   // rank order, see the kernel
                               : dim3((unsigned)((max_type_heads + wpb - 1) / wpb), (unsigned)B, (unsigned)(2 * layers));
     // wpb codes 12 and 14: one unit per workgroup, shared by 2 or 4 waves
-#define SSD_SHARED(CH_, SHARE_) if (ch == CH_ && wpb == 10 + SHARE_) { launch_shared<T, D, CH_, SHARE_>(full, heads ? dim3((unsigned)RANK_GROUPS, (unsigned)B, (unsigned)((H + RANK_GROUPS - 1) / RANK_GROUPS)) : dim3((unsigned)max_type_heads, (unsigned)B, (unsigned)(2 * layers)), (size_t)a.wave_lds + SHARE_ * (2 + D) * sizeof(float), fused, heads, s); return hipGetLastError(); }
+#define SSD_SHARED(CH_, SHARE_) if (ch == CH_ && wpb == 10 + SHARE_) { launch_variant<T, D, CH_, 1, SHARE_>(full, ho, heads ? dim3((unsigned)RANK_GROUPS, (unsigned)B, (unsigned)((H + RANK_GROUPS - 1) / RANK_GROUPS)) : dim3((unsigned)max_type_heads, (unsigned)B, (unsigned)(2 * layers)), (size_t)a.wave_lds + SHARE_ * (2 + D) * sizeof(float), layers, fused, s); return hipGetLastError(); }
     SSD_SHARED(2, 2) SSD_SHARED(4, 2) SSD_SHARED(2, 4) SSD_SHARED(4, 4)
 #undef SSD_SHARED
-#define SSD_CASE(CH_, WPB_) if (ch == CH_ && wpb == WPB_) { launch_one<T, D, CH_, WPB_>(full, blocks, lds, fused, heads, s); return hipGetLastError(); }
+#define SSD_CASE(CH_, WPB_) if (ch == CH_ && wpb == WPB_) { launch_variant<T, D, CH_, WPB_, 1>(full, ho, blocks, lds, layers, fused, s); return hipGetLastError(); }
     if constexpr (sizeof(T) == 2 && D == 128) {       // the shape the sweeps are run on has every variant
         SSD_CASE(1, 1) SSD_CASE(2, 1) SSD_CASE(4, 1)
         SSD_CASE(1, 2) SSD_CASE(2, 2) SSD_CASE(4, 2)
@@ -703,8 +735,9 @@ static int run_step(ssd_cache *cache, int layer_begin, int layer_end, const void
             a.lpr = a.g.row_bytes / 16;
             a.n_att = at.n; a.nc = before.nc; a.row_buffer = cf.spatial_row_buffer;
             a.rope_layout = rope.layout; a.rope_cos = rope.cos; a.rope_sin = rope.sin;
-            if (heads_differ(cache, lb)) fill_head_order(cache, lb, before, at, fused, &full.ho);
-            else full.ho = HeadOrder{};                  // never read then; keeps the argument bytes defined
+            HeadOrder order;
+            const HeadOrder *ho = nullptr;
+            if (heads_differ(cache, lb)) { fill_head_order(cache, lb, before, at, fused, &order); ho = &order; }
             int mx_sp = 0, mx_se = 0;                       // most heads of a type in a layer of the launch
             for (int l = lb; l < le; ++l) {
                 mx_sp = cache->ldesc[l].n_sp > mx_sp ? cache->ldesc[l].n_sp : mx_sp;
@@ -715,14 +748,13 @@ static int run_step(ssd_cache *cache, int layer_begin, int layer_end, const void
                 hipStream_t s = static_cast<hipStream_t>(streams[part % n_streams]);
                 a.seq_off = part * Bp;
                 const int Bn = cf.n_seqs - a.seq_off < Bp ? cf.n_seqs - a.seq_off : Bp;
-                const bool hd = heads_differ(cache, lb);
                 hipError_t e;
                 if (cf.dtype == SSD_BF16)
-                    e = cf.head_dim == 128 ? launch_step<bf16_t, 128>(full, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, fused, hd, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s)
-                                           : launch_step<bf16_t, 64>(full, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, fused, hd, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s);
+                    e = cf.head_dim == 128 ? launch_step<bf16_t, 128>(full, ho, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, fused, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s)
+                                           : launch_step<bf16_t, 64>(full, ho, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, fused, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s);
                 else
-                    e = cf.head_dim == 128 ? launch_step<float, 128>(full, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, fused, hd, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s)
-                                           : launch_step<float, 64>(full, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, fused, hd, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s);
+                    e = cf.head_dim == 128 ? launch_step<float, 128>(full, ho, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, fused, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s)
+                                           : launch_step<float, 64>(full, ho, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, fused, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s);
                 if (e != hipSuccess) return hip_fail(e, what);
                 if (do_compress && !in_kernel) {
                     const int rc = launch_compress_inplace(cache, lb, le, at, a.seq_off, Bn, s);
