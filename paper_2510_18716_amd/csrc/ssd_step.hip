@@ -560,7 +560,7 @@ template <typename T, int D, int CH, int WPB, int SHARE>
 static void launch_variant(const StepArgs &full, const HeadOrder *ho, dim3 blocks, size_t lds, int layers, bool fused, hipStream_t s) {
     const dim3 threads(WPB * SHARE * 64);
     const bool rope = full.h.rope_layout != 0;            // always fused (checked by the entry point)
-    if constexpr (CH == 4) {
+    if constexpr (CH >= 4) {
         if (ho) {
             const StepArgsHeads x = {full.h, full.lm.layer[0], *ho};
             if (rope) hipLaunchKernelGGL((step_kernel<StepArgsHeads, T, D, CH, WPB, true, true, true, SHARE>), blocks, threads, lds, s, x);
@@ -588,7 +588,7 @@ static void launch_variant(const StepArgs &full, const HeadOrder *ho, dim3 block
 // a split call, so another part's launch runs beside it on another stream.
 template <typename T, int D>
 static hipError_t launch_step(StepArgs &full, const HeadOrder *ho, const LaunchShape &shape, LaunchShape *used, int H, int max_sp_heads, int max_se_heads,
-                              int B, int layers, bool fused, bool concurrent, int M, hipStream_t s) {
+                              int B, int layers, long long call_units, bool fused, bool concurrent, int M, hipStream_t s) {
     StepHot &a = full.h;
     const bool heads = ho != nullptr;                     // budgets per head
     const int max_type_heads = max_sp_heads > max_se_heads ? max_sp_heads : max_se_heads;
@@ -604,13 +604,25 @@ static hipError_t launch_step(StepArgs &full, const HeadOrder *ho, const LaunchS
     int wpb = shape.wpb ? shape.wpb : (units <= 2048 ? 1 : 4);
     // Several waves per unit (codes 12 and 14: two and four) where one wave per unit leaves wave slots empty:
     //  * few and long units (the high-resolution shape, 2048 units of 129 to 385 rows): four, 41.0 -> 38.1 us;
+    //  * 768 units per call or fewer, every one longer than two chunks: four waves, and five wave-loads per chunk where
+    //    that takes a wave a chunk fewer (65 to 80 rows of 256 bytes: one chunk, everything a unit needs requested at
+    //    once).  With one wave per unit such a launch is three waves on each CU going through a chain of round trips.
+    //    1B shape, W = M = 64, us per launch: 256 units 6.8 -> 5.8, 512 units 7.7 -> 7.1, 768 units 8.7 -> 8.5, budgets of
+    //    32..96 per head at 512 units 9.0 -> 7.9; 1024 units lose (9.9 -> 10.8), and so do short ones (25 rows, 512
+    //    units: 5.4 -> 5.7).  By the units of the whole call, so that the parts of a split call take what it would take.
     //  * parts of a split call, two launches in flight: two waves for parts of 1025 to 2048 units (7B shape,
     //    128 sequences on two streams: 0.705 -> 0.687 ms per step), four for parts of 513 to 1024 units (64
     //    sequences: 0.415 -> 0.385 ms).  Alone on the chip such launches are faster with one wave per unit
     //    (64 sequences on one stream: 0.443 ms against 0.452 and 0.466), and smaller parts gain nothing.
     const int longest = a.se.total > a.sp.total ? a.se.total : a.sp.total;
     if (!shape.wpb && units <= 2048) {
-        if (longest >= 96 && !heads) wpb = 14;            // (budgets per head: `longest` is the largest head's, most units are shorter)
+        constexpr int RPW = 1024 / (D * (int)sizeof(T));  // rows per wave-load
+        const int shortest = max_sp_heads == 0 ? a.se.total : max_se_heads == 0 ? a.sp.total : a.se.total < a.sp.total ? a.se.total : a.sp.total;
+        const int loads = ((longest + RPW - 1) / RPW + 3) / 4;                // of one of four waves
+        if (call_units <= 768 && shortest > 8 * RPW) {
+            wpb = 14;
+            if (!shape.ch && (loads + 4) / 5 < (loads + 3) / 4) ch = 5;
+        } else if (longest >= 96 && !heads) wpb = 14;     // (budgets per head: `longest` is the largest head's, most units are shorter)
         else if (concurrent && units > 1024) wpb = 12;
         else if (concurrent && units > 512) wpb = 14;
     }
@@ -627,9 +639,11 @@ static hipError_t launch_step(StepArgs &full, const HeadOrder *ho, const LaunchS
     const int rows_long = long_sem ? a.se.total : a.sp.total, rows_short = long_sem ? a.sp.total : a.se.total;
     const int heads_long = long_sem ? max_se_heads : max_sp_heads;
     if (!shape.wpb && !heads && max_sp_heads > 0 && max_se_heads > 0 && rows_short > 0 && rows_long >= 2 * rows_short &&
-        4 * heads_long <= H)
+        4 * heads_long <= H) {
         wpb = long_sem && rows_long >= 96 && (units <= 2048 || (units <= 4096 && rows_long >= 192)) ? 14 : 12;
-    if (wpb > 10 && ch == 1) ch = 2;                      // the shared-unit launch exists with two and four loads per chunk
+        if (ch == 5) ch = 4;
+    }
+    if (wpb > 10 && ch == 1) ch = 2;                      // the shared-unit launch exists with two, four and (four waves) five loads per chunk
     a.wave_lds = (int)(((size_t)a.zcap * 4 + (a.do_compress ? select_lds_bytes(M, n_cand, n_old) + 16 : 0) + 15) / 16 * 16);
     while (wpb > 1 && wpb < 10 && (size_t)wpb * a.wave_lds > 60000) wpb >>= 1;
     const size_t lds = (size_t)wpb * a.wave_lds;
@@ -638,7 +652,7 @@ static hipError_t launch_step(StepArgs &full, const HeadOrder *ho, const LaunchS
                               : dim3((unsigned)((max_type_heads + wpb - 1) / wpb), (unsigned)B, (unsigned)(2 * layers));
     // wpb codes 12 and 14: one unit per workgroup, shared by 2 or 4 waves
 #define SSD_SHARED(CH_, SHARE_) if (ch == CH_ && wpb == 10 + SHARE_) { launch_variant<T, D, CH_, 1, SHARE_>(full, ho, heads ? dim3((unsigned)RANK_GROUPS, (unsigned)B, (unsigned)((H + RANK_GROUPS - 1) / RANK_GROUPS)) : dim3((unsigned)max_type_heads, (unsigned)B, (unsigned)(2 * layers)), (size_t)a.wave_lds + SHARE_ * (2 + D) * sizeof(float), layers, fused, s); return hipGetLastError(); }
-    SSD_SHARED(2, 2) SSD_SHARED(4, 2) SSD_SHARED(2, 4) SSD_SHARED(4, 4)
+    SSD_SHARED(2, 2) SSD_SHARED(4, 2) SSD_SHARED(2, 4) SSD_SHARED(4, 4) SSD_SHARED(5, 4)
 #undef SSD_SHARED
 #define SSD_CASE(CH_, WPB_) if (ch == CH_ && wpb == WPB_) { launch_variant<T, D, CH_, WPB_, 1>(full, ho, blocks, lds, layers, fused, s); return hipGetLastError(); }
     if constexpr (sizeof(T) == 2 && D == 128) {       // the shape the sweeps are run on has every variant
@@ -750,11 +764,11 @@ static int run_step(ssd_cache *cache, int layer_begin, int layer_end, const void
                 const int Bn = cf.n_seqs - a.seq_off < Bp ? cf.n_seqs - a.seq_off : Bp;
                 hipError_t e;
                 if (cf.dtype == SSD_BF16)
-                    e = cf.head_dim == 128 ? launch_step<bf16_t, 128>(full, ho, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, fused, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s)
-                                           : launch_step<bf16_t, 64>(full, ho, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, fused, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s);
+                    e = cf.head_dim == 128 ? launch_step<bf16_t, 128>(full, ho, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, (long long)cf.n_heads * cf.n_seqs * (le - lb), fused, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s)
+                                           : launch_step<bf16_t, 64>(full, ho, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, (long long)cf.n_heads * cf.n_seqs * (le - lb), fused, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s);
                 else
-                    e = cf.head_dim == 128 ? launch_step<float, 128>(full, ho, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, fused, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s)
-                                           : launch_step<float, 64>(full, ho, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, fused, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s);
+                    e = cf.head_dim == 128 ? launch_step<float, 128>(full, ho, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, (long long)cf.n_heads * cf.n_seqs * (le - lb), fused, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s)
+                                           : launch_step<float, 64>(full, ho, cache->shape, &cache->last_shape, cf.n_heads, mx_sp, mx_se, Bn, le - lb, (long long)cf.n_heads * cf.n_seqs * (le - lb), fused, plan.parts > 1 && n_streams > 1, cache->Ml[lb], s);
                 if (e != hipSuccess) return hip_fail(e, what);
                 if (do_compress && !in_kernel) {
                     const int rc = launch_compress_inplace(cache, lb, le, at, a.seq_off, Bn, s);

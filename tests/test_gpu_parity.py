@@ -476,6 +476,27 @@ def test_few_long_heads_beside_many_short_ones(fused):
         assert c.last_launch_shape()[:2] == (4, 14)
 
 
+@pytest.mark.parametrize("dtype,d,rows,ch,ch3", [("bf16", 128, 33, 4, 4), ("bf16", 128, 64, 4, 5), ("bf16", 128, 65, 5, 5), ("bf16", 128, 80, 5, 4),
+                                                 ("bf16", 128, 81, 4, 4), ("bf16", 128, 129, 5, 5), ("bf16", 64, 130, 5, 5),
+                                                 ("f32", 64, 66, 5, 5), ("f32", 128, 33, 5, 5)])
+def test_small_calls_give_a_unit_four_waves_and_one_chunk_if_it_fits(dtype, d, rows, ch, ch3):
+    """Calls of at most 768 units: four waves per unit, and five loads per chunk where that saves a chunk; one chunk holds 4 *
+    ch loads of 1 KB.  `rows`: what the units stream beside the new token; the three calls stream the new one as well (ch3)."""
+    base = workload.Workload("small-call-%d" % rows, L=2, prompts=2, H=6, d=d, dtype=dtype, n0=9, grid_h=4, grid_w=rows // 2, W=rows,
+                             M=rows - 1, S=1, R=1, C=3, cadence=1, seed=300 + rows, plain=True)
+    for fused in (False, True):
+        c = _full_compare(base, lpc=1, k_units=12, export_every=5, fused=fused)
+        assert c.last_launch_shape()[:2] == (ch if fused else ch3, 14), c.last_launch_shape()
+    c = _full_compare(base.replace(name=base.name + "-rope"), lpc=None, k_units=12, export_every=7, fused=True, rope=ssd.SSD_ROPE_HALF)
+    assert c.last_launch_shape()[:2] == (ch, 14)
+    hb = np.random.default_rng(rows).integers(rows - 12, rows, (2, 6))
+    hb[:, 0] = rows                                               # the longest head of each type decides
+    hb[:, 5] = rows
+    c = _full_compare(base.replace(name=base.name + "-heads", W=rows, M=rows, head_budget=hb.tolist()), lpc=1, k_units=12, export_every=7,
+                      fused=True)
+    assert c.last_launch_shape()[1] == 14
+
+
 @pytest.mark.parametrize("fused", [False, True], ids=["three-calls", "fused-step"])
 def test_selection_with_few_evictions_among_many_candidates(fused):
     """More than 128 candidates and one to a few evictions per compression: the step kernel's wave takes the smallest keys
