@@ -85,6 +85,56 @@ __global__ __launch_bounds__(WPB * 64) void dense_kernel(DenseArgs a) {
     }
 }
 
+// The same with a unit's splits dealt to the waves of one workgroup: the partials meet in LDS, so neither a workspace nor
+// a second launch is needed.  For launches with units enough to fill the chip that way; WAVES row ranges of one unit.
+template <typename T, int D, int CH, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void dense_shared_kernel(DenseArgs a) {
+    constexpr int VEC = Elem<T>::VEC;
+    constexpr int LPR = D / VEC;
+    __shared__ float part[WAVES][4 + D];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int sub = lane % LPR;
+    const int unit = blockIdx.x;
+    const typename Elem<T>::Q q = Elem<T>::load_q(*reinterpret_cast<const uint4 *>(a.q + (size_t)unit * a.row_bytes + (size_t)sub * 16u));
+    const char *Kb = a.K + (size_t)unit * (size_t)a.n_cap * (size_t)a.row_bytes;
+    const char *Vb = a.V + (size_t)unit * (size_t)a.n_cap * (size_t)a.row_bytes;
+    Segs sg = {{0, 0, 0}, {a.n, 0, 0}, a.n};
+    const int r_begin = wave * a.rows_per_split;
+    const int r_end = r_begin + a.rows_per_split < a.n ? r_begin + a.rows_per_split : a.n;
+    Softmax<VEC> sm;
+    sm.init();
+    if (r_begin < r_end)
+        stream_rows<T, D, CH, false, true, NoHook, false>(Kb, Vb, a.row_bytes, sg, r_begin, r_end, 0, 1, q, a.qscale, sm, nullptr, a.vis_start, a.far_last);
+    merge_groups<VEC, LPR, true>(sm);
+    if (lane == 0) { part[wave][0] = sm.m; part[wave][1] = sm.l; part[wave][2] = sm.far; part[wave][3] = sm.tot; }
+    if (lane < LPR) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) part[wave][4 + sub * VEC + e] = sm.acc[e];
+    }
+    __syncthreads();
+    const int e = threadIdx.x;                             // one thread per output element (D <= 64 * WAVES)
+    if (e >= D) return;
+    float m = NEG_BIG;
+#pragma unroll
+    for (int s = 0; s < WAVES; ++s) m = fmaxf(m, part[s][0]);
+    float l = 0.f, far = 0.f, tot = 0.f, acc = 0.f;
+#pragma unroll
+    for (int s = 0; s < WAVES; ++s) {
+        const float f = fast_exp2(part[s][0] - m);
+        l += part[s][1] * f; far += part[s][2] * f; tot += part[s][3] * f;
+        acc += part[s][4 + e] * f;
+    }
+    const float inv_l = l > 0.f ? 1.0f / l : 0.f;
+    const float o = acc * inv_l;
+    if (sizeof(T) == 4) reinterpret_cast<float *>(a.out)[(size_t)unit * D + e] = o;
+    else reinterpret_cast<uint16_t *>(a.out)[(size_t)unit * D + e] = (uint16_t)f32_to_bf16_bits(o);
+    if (e == 0 && a.far) {
+        a.far[(size_t)unit * a.mass_stride] = far * inv_l;
+        a.tot[(size_t)unit * a.mass_stride] = tot * inv_l;
+    }
+}
+
 // merge the split partials of one unit: one thread per output element
 template <typename T, int D>
 __global__ __launch_bounds__(D) void dense_merge_kernel(DenseArgs a) {
@@ -119,9 +169,27 @@ static int pick_splits(int units, int n) {
     return s < 1 ? 1 : s;
 }
 
+// Waves per unit of dense_shared_kernel for a shape that would take `splits` row splits (0: not this kernel).  With 256
+// units a workgroup each fills the chip; fewer are better spread over more workgroups.  About 64 rows a wave or more:
+// 1024 units of 640 rows, us: 59.3 with two launches (5 splits), 51.9 / 51.4 / 50.4 with 2 / 4 / 8 waves; 256 units of
+// 640 rows 21.2 -> 15.0 (8), 512 of 300 18.0 -> 15.3 (2), 512 of 2368 108.4 -> 93.8 (8), 4096 of 400 134.9 -> 129.1 (2).
+static int pick_shared(int units, int n, int splits) {
+    if (units < 256 || splits < 2) return 0;
+    return n >= 512 && splits >= 4 ? 8 : splits >= 3 ? 4 : 2;
+}
+
 template <typename T, int D>
-static hipError_t launch_dense(const DenseArgs &a, hipStream_t s) {
+static hipError_t launch_dense(const DenseArgs &a, int shared, hipStream_t s) {
     constexpr int WPB = 4;
+    if (shared) {
+        DenseArgs x = a;
+        x.rows_per_split = (a.n + shared - 1) / shared;
+        const dim3 grid((unsigned)a.n_units), block((unsigned)shared * 64u);
+        if (shared == 2) hipLaunchKernelGGL((dense_shared_kernel<T, D, 4, 2>), grid, block, 0, s, x);
+        else if (shared == 4) hipLaunchKernelGGL((dense_shared_kernel<T, D, 4, 4>), grid, block, 0, s, x);
+        else hipLaunchKernelGGL((dense_shared_kernel<T, D, 4, 8>), grid, block, 0, s, x);
+        return hipGetLastError();
+    }
     const long long items = (long long)a.n_units * a.splits;
     const unsigned blocks = (unsigned)((items + WPB - 1) / WPB);
     hipLaunchKernelGGL((dense_kernel<T, D, 4, WPB>), dim3(blocks), dim3(WPB * 64), 0, s, a);
@@ -219,8 +287,9 @@ static int dense_run(const void *q, const void *K, const void *V, void *out, int
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e;
-    if (dtype == SSD_BF16) e = d == 128 ? launch_dense<bf16_t, 128>(a, s) : launch_dense<bf16_t, 64>(a, s);
-    else e = d == 128 ? launch_dense<float, 128>(a, s) : launch_dense<float, 64>(a, s);
+    const int shared = splits > 0 ? 0 : pick_shared(a.n_units, n, a.splits);      // a given number of splits takes the two launches
+    if (dtype == SSD_BF16) e = d == 128 ? launch_dense<bf16_t, 128>(a, shared, s) : launch_dense<bf16_t, 64>(a, shared, s);
+    else e = d == 128 ? launch_dense<float, 128>(a, shared, s) : launch_dense<float, 64>(a, shared, s);
     if (e != hipSuccess) return hip_fail(e, "dense attention launch");
     return SSD_OK;
 }
