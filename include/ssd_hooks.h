@@ -41,8 +41,8 @@ int ssd_cache_spatial_slot(const ssd_cache *cache, int layer, int head, int posi
  * kernel, which the library otherwise picks from the launch size.  Results
  * change by rounding only: ch and the number of wavefronts per unit set the
  * order of the fp32 softmax sums (the library's own choice is ch = 4 and one
- * wavefront, two or four as the launch size says); units per workgroup and
- * new_rows change nothing.  (0, 0, 0) restores the library's choice.
+ * wavefront, two or four as the launch size says, or ch = 5 and four, which only
+ * the library takes); units per workgroup and new_rows change nothing.  (0, 0, 0) restores the library's choice.
  *   ch       : wave-wide loads of K (and of V) per chunk: 0, 1, 2, 4
  *   wpb      : units per workgroup: 0, 1, 2, 4; 12 / 14 = one unit per workgroup
  *              shared by 2 / 4 wavefronts

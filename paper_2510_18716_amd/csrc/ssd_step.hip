@@ -351,10 +351,11 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
             pre_row = *reinterpret_cast<const uint4 *>(plane + (size_t)(t_M + t_base) * (size_t)t_row_bytes + (size_t)sub * 16u);
         }
     };
+    constexpr bool PEEL = WPB == 1 && SHARE == 1;         // up to 2048 units, a wave each (see stream_rows)
     if (want_z)
-        stream_rows<T, D, CH, true, false>(u.K, u.V, a.g.row_bytes, sg, 0, sg.total, part, SHARE, q, a.qscale, sm, zbuf, 0, 0, after_first_issue);
+        stream_rows<T, D, CH, true, false, decltype(after_first_issue), true, PEEL>(u.K, u.V, a.g.row_bytes, sg, 0, sg.total, part, SHARE, q, a.qscale, sm, zbuf, 0, 0, after_first_issue);
     else
-        stream_rows<T, D, CH, false, false>(u.K, u.V, a.g.row_bytes, sg, 0, sg.total, part, SHARE, q, a.qscale, sm, nullptr, 0, 0, after_first_issue);
+        stream_rows<T, D, CH, false, false, decltype(after_first_issue), true, PEEL>(u.K, u.V, a.g.row_bytes, sg, 0, sg.total, part, SHARE, q, a.qscale, sm, nullptr, 0, 0, after_first_issue);
     if (FUSED && part == 0) {
         // The new token, from the registers it was loaded into, is folded into lane group 0's softmax as
         // one more row (index sg.total).
