@@ -263,3 +263,31 @@ def test_classify_sums_every_term_once(P, T, offset):
     ref = torch.where(t > 0, f / t.clamp_min(1e-300), torch.zeros_like(t)).sum(dim=(1, 3)) / (P * T)
     assert float((s.double() - ref).abs().max()) <= (P * T / 512 + 12) * 2.0 ** -24
     assert torch.equal(ty.bool(), s > 0.4)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("B,H,n,n_cap", [(8, 32, 256, 256), (8, 32, 383, 400), (16, 16, 385, 385), (8, 32, 511, 511), (8, 32, 513, 600),
+                                         (64, 64, 300, 300), (3, 85, 640, 640)])
+def test_dense_waves_of_one_workgroup_share_a_unit(dtype, d, B, H, n, n_cap):
+    """From 256 units on two, four or eight waves of a workgroup take a unit's row ranges, which may divide unevenly; with 255
+    units the ranges go to two launches.  Against 64 bits, with the masses."""
+    say("dense shared", dtype, d, B, H, n)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(n)
+    mk = lambda *s: torch.randn(s, generator=g, device="cuda").to(tdt)      # noqa: E731
+    q, K, V = mk(B, H, d), mk(B, H, n_cap, d), mk(B, H, n_cap, d)
+    K[:, :, n:], V[:, :, n:] = float("nan"), float("nan")         # rows beyond n are not attended
+    out = torch.empty_like(q)
+    far, tot = torch.empty((B, H), device="cuda"), torch.empty((B, H), device="cuda")
+    ws = torch.empty(ssd.ssd_dense_workspace_bytes(B, H, d, n), dtype=torch.uint8, device="cuda")
+    vis, w = 40, 32
+    ssd.ssd_dense_decode_attn(q, K, V, out, B, H, d, dtype, n_cap, n, far=far, tot=tot, vis_start=vis, w=w, workspace=ws)
+    for b in range(0, B, max(1, B // 4)):
+        z = torch.matmul(K[b, :, :n].double(), q[b].double()[:, :, None]).squeeze(-1) / np.sqrt(d)
+        a = torch.softmax(z, dim=-1)
+        ref = torch.matmul(a[:, None], V[b, :, :n].double()).squeeze(1)
+        # bf16: half an ulp of the output; fp32: sums of n terms of fp32 products (as the other dense tests)
+        tol = (2e-2, 1e-2) if dtype == "bf16" else (1e-5, 1e-5)
+        assert bool(((out[b].double() - ref).abs() <= tol[0] + tol[1] * ref.abs()).all())
+        np.testing.assert_allclose(tot[b].double().cpu().numpy(), a[:, vis:].sum(-1).cpu().numpy(), rtol=1e-5, atol=1e-6)
+        np.testing.assert_allclose(far[b].double().cpu().numpy(), a[:, vis:n - w].sum(-1).cpu().numpy(), rtol=1e-5, atol=1e-6)

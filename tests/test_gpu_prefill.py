@@ -246,3 +246,24 @@ def test_dense_source_selection_is_the_sorted_one(B, H, n, scores):
                 assert np.array_equal(kept_score[b, h][:len(heavy)], sc[b, h][heavy])
             assert count[b, h] == len(want)
             np.testing.assert_allclose(got[b, h], Vh[b, h][want].mean(axis=0), atol=2e-2, rtol=1e-2)
+
+
+def test_cfg_mix_more_prompts_than_one_grid_dimension_holds():
+    """65536 is the first prompt a workgroup reaches with its second stride; rows of 3 break every 16-byte alignment."""
+    n, V, gamma = 65537, 3, 2.5
+    p = torch.randn((2 * n, V), generator=torch.Generator().manual_seed(3)).to(torch.bfloat16).cuda()
+    out = torch.full((n + 1, V), 7.0, device="cuda")
+    ssd.ssd_cfg_mix(p, 2 * n, V, "bf16", gamma, out)
+    c, u = p.double()[0::2], p.double()[1::2]
+    ref = c + gamma * (c - u)
+    assert float((out[:n].double() - ref).abs().max()) <= 2.0 ** -22 * float(ref.abs().max())      # two roundings of fp32
+    assert bool((out[n] == 7.0).all())
+
+
+def test_binding_takes_torchs_current_stream():
+    from paper_2510_18716_amd.binding import _stream
+    side = torch.cuda.Stream()
+    assert (_stream() or 0) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert _stream() == side.cuda_stream
+    assert _stream(side) == side.cuda_stream and _stream(123) == 123
