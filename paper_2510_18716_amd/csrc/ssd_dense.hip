@@ -5,8 +5,10 @@
 //
 // Same streaming loop as the compressed kernel, over rows 0..n-1 of a [B, H, n_cap, d] cache.
 // With only B*H units per layer and n up to a few thousand rows, the rows of a unit are split
-// over several waves (split-K); each wave leaves an unnormalised partial (max, sum, masses,
-// output) in a caller-provided workspace and a second small kernel merges them.
+// over several waves (split-K), each of which ends with an unnormalised partial (max, sum, masses,
+// output).  With 256 units or more they are the waves of one workgroup and meet in LDS; with fewer,
+// which would leave compute units idle that way, they go to separate workgroups, leave the partials
+// in a caller-provided workspace, and a second small kernel merges them.
 // Roofline: HBM; algorithmic bytes per unit = n * 2 * d * e.
 #include <mutex>
 #include <type_traits>

@@ -63,7 +63,7 @@ def test_prefill_scores_largest_prompt_and_many_units():
 
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
-@pytest.mark.parametrize("n", [131, 160, 161, 256, 287, 512, 513, 800])
+@pytest.mark.parametrize("n", [131, 160, 161, 256, 287, 512, 513, 800, 4096])
 def test_prefill_scores_long_prompts_at_tile_and_workgroup_edges(dtype, d, n):
     """Above 128 tokens: around whole tiles, around what a workgroup of 4 (up to 256 tokens) and of 8 waves holds at a
     time.  A unit beside the last one must stay as it was.  Tolerance: fp32 sums of up to n terms, each within a few
@@ -85,6 +85,26 @@ def test_prefill_scores_long_prompts_at_tile_and_workgroup_edges(dtype, d, n):
     assert bool((got[2] == -5.0).all())
     err = ((got[:2] - ref[:2]).abs() / ref[:2].clamp_min(1e-3)).max()
     assert float(err) < 1e-5, float(err)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [200, 600])
+def test_prefill_scores_long_prompts_take_a_logit_that_is_no_number_as_masked(dtype, n):
+    """A key that is no number scores 0 and changes nothing else; a query that is none gives nothing to any key."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(n)
+    q, k = (torch.randn((2, n, 64), generator=g).to(tdt) for _ in range(2))
+    k[0, 37, 5] = float("nan")
+    k[0, n - 1, 5] = float("nan")
+    q[0, 150, 3] = float("nan")
+    out = torch.empty((2, n), device="cuda")
+    ssd.ssd_prefill_scores(q.cuda(), k.cuda(), 2, n, 64, dtype, out)
+    z = torch.matmul(q.double(), k.double().transpose(1, 2)) / 8.0
+    z = z.masked_fill(torch.isnan(z) | torch.ones(n, n, dtype=torch.bool).triu(1), -np.inf)
+    ref = torch.nan_to_num(torch.softmax(z, dim=-1)).sum(dim=1)
+    got = out.cpu().double()
+    assert float(((got - ref).abs() / ref.clamp_min(1e-3)).max()) < 1e-5
+    assert float(got[0, 37]) == 0.0 and float(got[0, n - 1]) == 0.0
 
 
 def test_prefill_scores_bit_reproducible():
