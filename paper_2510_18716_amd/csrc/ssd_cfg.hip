@@ -7,9 +7,11 @@
 // image vocabulary the launch itself (64 prompts of 16384: 8.4 MB, 1.6 us at the rate of a large read).  Each lane takes
 // 16-byte fragments of the two rows (coalesced) and writes fp32.  Rows of a length that breaks the 16-byte alignment are
 // read and written in the same pieces, element-aligned (the hardware takes a 16-byte access at any element boundary);
-// the last, shorter piece of a row goes element by element.
-// Measured: 256 prompts of 47911 (rows of odd length, bf16): 27.2 us one element per lane with a division each, 20.3 now (4.8
-// TB/s); 256 of 65536 27.8 -> 27.3.  64 prompts of 16384 stay at 3.6 us, the launch.
+// the last, shorter piece of a row goes element by element, all of its loads in flight together.  Rows of at most 64 pieces
+// share a workgroup.
+// Measured, against one element per lane with a division each for unaligned rows and flat pieces with a division each for
+// aligned ones: 256 prompts of 47911 (bf16) 20.0 -> 17.5 us (4.8 TB/s); 256 of 65536 22.5 -> 22.7; 64 prompts of 16384 stay at 3.5 us,
+// the launch.  Short rows: 65536 prompts of 16 3.5 us (30 with a workgroup of its own for each row), 16384 of 257 9.2 -> 7.7.
 #include <cmath>
 
 #include "ssd_device.h"
@@ -21,6 +23,7 @@ struct CfgArgs {
     float *out;
     int V;
     int n_prompts;
+    int lanes_log2;     // threads of a workgroup that share a row: 1, 2, .. 256
     float gamma;
 };
 
@@ -32,16 +35,31 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef u32x4_nt_t u32x4_any_t __attribute__((aligned(2)));
 typedef f32x4_t f32x4_any_t __attribute__((aligned(4)));
 
-// grid = (blocks over the pieces of a row, prompts): nothing has to be divided
+// Unaligned rows with little work in all: one element per lane.  Such a launch is one round trip to memory and the time to
+// get there: 2 prompts of 47911 (bf16) take 2.7 us this way, 3.0 in pieces; 16384 of 7 2.7 and 3.4.
+template <typename T>
+__global__ __launch_bounds__(256) void cfg_mix_few_kernel(CfgArgs a) {
+    const unsigned x = blockIdx.x * 256u + threadIdx.x;
+    if (x >= (unsigned)a.V * (unsigned)a.n_prompts) return;
+    const unsigned i = x / (unsigned)a.V;
+    const T *c = reinterpret_cast<const T *>(a.p) + (size_t)x + (size_t)i * a.V;           // row 2i of p, at the element's place in row i of out
+    const float xc = widen(c[0]), xu = widen(c[a.V]);
+    a.out[x] = fmaf(a.gamma, xc - xu, xc);
+}
+
+// grid = (blocks over the pieces of a row, blocks over the prompts), 256 >> lanes_log2 rows per workgroup: nothing has to be
+// divided
 template <typename T, bool ALIGNED>
 __global__ __launch_bounds__(256) void cfg_mix_kernel(CfgArgs a) {
     constexpr int VEC = Elem<T>::VEC;
     const int pieces = a.V / VEC, rest = a.V % VEC;
-    for (int i = blockIdx.y; i < a.n_prompts; i += gridDim.y) {
-        const T *c = reinterpret_cast<const T *>(a.p) + (size_t)(2 * (long long)i) * a.V;
+    const int lanes = 1 << a.lanes_log2, rows = 256 >> a.lanes_log2;
+    const int row = (int)threadIdx.x >> a.lanes_log2, first = (int)threadIdx.x & (lanes - 1);
+    for (long long i = (long long)blockIdx.y * rows + row; i < a.n_prompts; i += (long long)gridDim.y * rows) {
+        const T *c = reinterpret_cast<const T *>(a.p) + (size_t)(2 * i) * a.V;
         const T *u = c + a.V;
         float *o = a.out + (size_t)i * a.V;
-        for (int j = (int)(blockIdx.x * 256 + threadIdx.x); j <= pieces; j += (int)(gridDim.x * 256)) {
+        for (int j = (int)blockIdx.x * lanes + first; j <= pieces; j += (int)gridDim.x * lanes) {
             const int v0 = j * VEC;
             if (j < pieces) {
                 u32x4_nt_t cr, ur;
@@ -63,14 +81,40 @@ __global__ __launch_bounds__(256) void cfg_mix_kernel(CfgArgs a) {
                     if constexpr (ALIGNED) *reinterpret_cast<f32x4_t *>(o + v0 + e) = r;
                     else *reinterpret_cast<f32x4_any_t *>(o + v0 + e) = r;
                 }
-            } else {
-                for (int e = v0; e < v0 + rest; ++e) {
-                    const float x = widen(c[e]), y = widen(u[e]);
-                    o[e] = fmaf(a.gamma, x - y, x);
+            } else if constexpr (!ALIGNED) {
+                if (rest == 0) continue;
+                float x[VEC], y[VEC];
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {            // unconditional loads: past the end the last element again
+                    const int v = e < rest ? v0 + e : a.V - 1;
+                    x[e] = widen(c[v]);
+                    y[e] = widen(u[v]);
                 }
+#pragma unroll
+                for (int e = 0; e < VEC; ++e)
+                    if (e < rest) o[v0 + e] = fmaf(a.gamma, x[e] - y[e], x[e]);
             }
         }
     }
+}
+
+template <typename T>
+static hipError_t launch_mix_few(const CfgArgs &a, hipStream_t s) {
+    hipLaunchKernelGGL((cfg_mix_few_kernel<T>), dim3(((unsigned)a.V * (unsigned)a.n_prompts + 255u) / 256u), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+template <typename T, bool ALIGNED>
+static hipError_t launch_mix(CfgArgs a, hipStream_t s) {
+    const int want = a.V / Elem<T>::VEC + (ALIGNED ? 0 : 1);   // pieces of a row, the shorter last one included
+    // (rows of 65 to 128 pieces are faster with a workgroup each, half of it idle: 16384 prompts of 1024, bf16, 20.5 us against 23.1)
+    a.lanes_log2 = want > 64 ? 8 : 0;
+    while (a.lanes_log2 < 8 && 1 << a.lanes_log2 < want) ++a.lanes_log2;
+    const int rows = 256 >> a.lanes_log2, gx = want / 256 + (want % 256 ? 1 : 0);
+    const int gy = a.n_prompts / rows + (a.n_prompts % rows ? 1 : 0);
+    const dim3 grid(gx > 1024 ? 1024 : gx, gy < 65535 ? gy : 65535);                   // strides cover the rest
+    hipLaunchKernelGGL((cfg_mix_kernel<T, ALIGNED>), grid, dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace ssd
@@ -91,20 +135,13 @@ extern "C" int ssd_cfg_mix(const void *p, int n_seqs, int V, int dtype, float ga
     a.V = V;
     a.n_prompts = n_seqs / 2;
     a.gamma = gamma;
-    const int vec = dtype == SSD_F32 ? 4 : 8;
-    const bool rows_aligned = V % vec == 0;                    // p is 16-byte aligned; then so is every row of p and of out
-    const int want = V / vec + 1;                              // pieces of a row, the shorter last one included
-    const unsigned gx = (unsigned)((V % vec ? want : want - 1) + 255) / 256;
-    const dim3 grid(gx < 1 ? 1 : gx > 1024 ? 1024 : gx, (unsigned)(a.n_prompts < 65535 ? a.n_prompts : 65535));     // strides cover the rest
+    const bool rows_aligned = V % (dtype == SSD_F32 ? 4 : 8) == 0;     // p is 16-byte aligned; then so is every row of p and of out
     hipStream_t s = static_cast<hipStream_t>(stream);
-#define SSD_CFG(T_)                                                                                                  \
-    do {                                                                                                             \
-        if (rows_aligned) hipLaunchKernelGGL((cfg_mix_kernel<T_, true>), grid, dim3(256), 0, s, a);                  \
-        else hipLaunchKernelGGL((cfg_mix_kernel<T_, false>), grid, dim3(256), 0, s, a);                              \
-    } while (0)
-    if (dtype == SSD_BF16) SSD_CFG(bf16_t); else SSD_CFG(float);
-#undef SSD_CFG
-    hipError_t e = hipGetLastError();
+    hipError_t e;
+    // The line: 64 prompts of 8191 (bf16) 3.25 us by elements, 3.4 in pieces; 4096 of 1000 6.5 and 6.2 (256 of 47911 20.0 and 17.5).
+    const bool few = !rows_aligned && (long long)V * a.n_prompts <= 600000;
+    if (dtype == SSD_BF16) e = few ? launch_mix_few<bf16_t>(a, s) : rows_aligned ? launch_mix<bf16_t, true>(a, s) : launch_mix<bf16_t, false>(a, s);
+    else e = few ? launch_mix_few<float>(a, s) : rows_aligned ? launch_mix<float, true>(a, s) : launch_mix<float, false>(a, s);
     if (e != hipSuccess) return hip_fail(e, "guidance mix launch");
     return SSD_OK;
 }

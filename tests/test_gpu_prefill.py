@@ -268,16 +268,35 @@ def test_dense_source_selection_is_the_sorted_one(B, H, n, scores):
             np.testing.assert_allclose(got[b, h], Vh[b, h][want].mean(axis=0), atol=2e-2, rtol=1e-2)
 
 
-def test_cfg_mix_more_prompts_than_one_grid_dimension_holds():
-    """65536 is the first prompt a workgroup reaches with its second stride; rows of 3 break every 16-byte alignment."""
-    n, V, gamma = 65537, 3, 2.5
-    p = torch.randn((2 * n, V), generator=torch.Generator().manual_seed(3)).to(torch.bfloat16).cuda()
+def _mix_case(n, V, dtype, gamma):
+    """Against 64 bits; a row beyond the last must stay as it was.  Two roundings of fp32: of c - u, then of the result."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    p = torch.randn((2 * n, V), generator=torch.Generator(device="cuda").manual_seed(n + V), device="cuda").to(tdt)
     out = torch.full((n + 1, V), 7.0, device="cuda")
-    ssd.ssd_cfg_mix(p, 2 * n, V, "bf16", gamma, out)
+    ssd.ssd_cfg_mix(p, 2 * n, V, dtype, gamma, out)
     c, u = p.double()[0::2], p.double()[1::2]
     ref = c + gamma * (c - u)
-    assert float((out[:n].double() - ref).abs().max()) <= 2.0 ** -22 * float(ref.abs().max())      # two roundings of fp32
+    bound = 1.01 * 2.0 ** -24 * (abs(gamma) * (c - u).abs() + ref.abs())
+    assert bool(((out[:n].double() - ref).abs() <= bound).all())
     assert bool((out[n] == 7.0).all())
+
+
+@pytest.mark.parametrize("V", [3, 521])
+def test_cfg_mix_more_prompts_than_one_grid_dimension_holds(V):
+    """65536 is the first prompt a workgroup that has a row to itself (521: 66 pieces) reaches with its second stride; neither
+    length keeps 16-byte alignment."""
+    _mix_case(65537, V, "bf16", 2.5)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,V", [(1, 1), (3, 7), (85714, 7), (85715, 7), (150001, 4), (4099, 257), (9001, 67), (2333, 515), (601, 1030), (5, 8), (999, 8),
+                                 (1001, 24), (70, 512), (67, 520), (33, 264), (1, 600001), (2, 4 * 65537 * 4)])
+def test_cfg_mix_short_rows_and_little_work(dtype, n, V):
+    """Unaligned rows on both sides of 600000 elements in all (one element per lane; pieces), rows of 1 to 64 pieces that share
+    a workgroup and of 65 that do not, every remainder of a piece, a last workgroup with rows missing, rows longer than a
+    grid's first pass."""
+    say("cfg mix", dtype, n, V)
+    _mix_case(n, V, dtype, 5.0)
 
 
 def test_binding_takes_torchs_current_stream():
