@@ -265,6 +265,39 @@ def test_classify_sums_every_term_once(P, T, offset):
     assert torch.equal(ty.bool(), s > 0.4)
 
 
+@pytest.mark.parametrize("P,T", [(1, 1), (1, 3), (1, 1023), (5, 205), (1, 1024), (3, 341), (1, 4096), (8, 512), (1, 4100), (25, 164), (300, 5)])
+def test_classify_around_the_line_between_its_two_shapes(P, T):
+    """1024 pieces per head (of four terms where T is a multiple of four) and one more.  The sums do not depend on where the
+    inputs lie.  Tolerance as above."""
+    say("classify", P, T)
+    L, H = 3, 5
+    g = torch.Generator(device="cuda").manual_seed(P * 10000 + T)
+    tot = torch.rand((L, P, H, T), generator=g, device="cuda")
+    far = torch.rand((L, P, H, T), generator=g, device="cuda") * tot
+    s, ty = torch.empty((L, H), device="cuda"), torch.empty((L, H), dtype=torch.uint8, device="cuda")
+    ssd.ssd_classify_heads(far, tot, L, P, H, T, 0.4, s, ty)
+    ref = (far.double() / tot.double().clamp_min(1e-300)).sum(dim=(1, 3)) / (P * T)
+    assert float((s.double() - ref).abs().max()) <= (P * T / 256 + 16) * 2.0 ** -24
+    moved = [torch.cat((x.new_zeros(1), x.flatten()))[1:] for x in (far, tot)]
+    again = torch.empty_like(s)
+    ssd.ssd_classify_heads(moved[0], moved[1], L, P, H, T, 0.4, again, ty)
+    assert torch.equal(s, again)
+
+
+def test_classify_more_heads_than_one_launch_holds():
+    """A launch holds 2^32 threads: 8388607 workgroups of 512, 16777215 of 256."""
+    L, H = 131073, 128
+    n = L * H
+    assert n > (2 ** 32 - 1) // 256
+    say("classify", L, H)
+    tot = torch.full((n,), 2.0, device="cuda")
+    far = torch.arange(n, device="cuda").remainder_(5).float()
+    s, ty = torch.full((n + 1,), -3.0, device="cuda"), torch.full((n + 1,), 9, dtype=torch.uint8, device="cuda")
+    ssd.ssd_classify_heads(far, tot, L, 1, H, 1, 0.75, s, ty)
+    assert torch.equal(s[:n], far / 2) and float(s[n]) == -3.0
+    assert torch.equal(ty[:n].bool(), far > 1.5) and int(ty[n]) == 9
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
 @pytest.mark.parametrize("B,H,n,n_cap", [(8, 32, 256, 256), (8, 32, 383, 400), (16, 16, 385, 385), (8, 32, 511, 511), (8, 32, 513, 600),
                                          (64, 64, 300, 300), (3, 85, 640, 640)])
