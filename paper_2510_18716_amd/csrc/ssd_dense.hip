@@ -175,8 +175,24 @@ static int pick_splits(int units, int n) {
 // units a workgroup each fills the chip; fewer are better spread over more workgroups.  About 64 rows a wave or more:
 // 1024 units of 640 rows, us: 59.3 with two launches (5 splits), 51.9 / 51.4 / 50.4 with 2 / 4 / 8 waves; 256 units of
 // 640 rows 21.2 -> 15.0 (8), 512 of 300 18.0 -> 15.3 (2), 512 of 2368 108.4 -> 93.8 (8), 4096 of 400 134.9 -> 129.1 (2).
-static int pick_shared(int units, int n, int splits) {
+// Just above one and two workgroups per compute unit some units have a workgroup more than the others, and the launch lasts as
+// long as they do; smaller workgroups even that out (bf16, d = 128, us):
+//   units of rows   two launches   2 waves   4 waves   8 waves
+//   264 of 1500         41.4         53.3      40.5      46.2
+//   352 of  640         25.1         25.7      21.5      22.9
+//   384 of 1500         58.1         56.5      48.5      49.7
+//   448 of  520         25.5         23.7      22.9      21.6
+//   528 of 1500         71.9         65.0      75.8      72.3
+//   640 of 1000         58.6         52.0      55.1      53.9
+//   704 of  640         44.2         36.8      37.8      36.4
+// Up to 31 units above a multiple of 256 with long rows the two launches stay: their pieces are smaller still (fp32, d = 128, 272
+// of 1500: 73.7, 78.3 with 4 waves; 784 of 2368: 301, 310 with 2, 313 with 8).
+static int pick_shared(int units, int n, int row_bytes, int splits) {
     if (units < 256 || splits < 2) return 0;
+    if (units > 512 && units <= 640) return 2;
+    const int over = units % 256;
+    if (over > 0 && over < 32 && (long long)n * row_bytes >= 700000) return 0;      // 272 of 1000 (512 kB): 28.8 in four waves, 29.2 in two launches
+    if (units > 256 && units <= 384) return 4;
     return n >= 512 && splits >= 4 ? 8 : splits >= 3 ? 4 : 2;
 }
 
@@ -289,7 +305,7 @@ static int dense_run(const void *q, const void *K, const void *V, void *out, int
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e;
-    const int shared = splits > 0 ? 0 : pick_shared(a.n_units, n, a.splits);      // a given number of splits takes the two launches
+    const int shared = splits > 0 ? 0 : pick_shared(a.n_units, n, a.row_bytes, a.splits);      // a given number of splits takes the two launches
     if (dtype == SSD_BF16) e = d == 128 ? launch_dense<bf16_t, 128>(a, shared, s) : launch_dense<bf16_t, 64>(a, shared, s);
     else e = d == 128 ? launch_dense<float, 128>(a, shared, s) : launch_dense<float, 64>(a, shared, s);
     if (e != hipSuccess) return hip_fail(e, "dense attention launch");

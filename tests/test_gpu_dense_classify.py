@@ -300,7 +300,11 @@ def test_classify_more_heads_than_one_launch_holds():
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
 @pytest.mark.parametrize("B,H,n,n_cap", [(8, 32, 256, 256), (8, 32, 383, 400), (16, 16, 385, 385), (8, 32, 511, 511), (8, 32, 513, 600),
-                                         (64, 64, 300, 300), (3, 85, 640, 640)])
+                                         (64, 64, 300, 300), (3, 85, 640, 640),
+                                         # more than one workgroup per compute unit, and not a whole number of them
+                                         (257, 1, 257, 257), (32, 12, 700, 700), (7, 55, 700, 700), (27, 19, 515, 515), (16, 40, 1033, 1033), (641, 1, 515, 515),
+                                         # a few workgroups too many: waves of 700 kB and more go to two launches (1367 rows of 512 bytes)
+                                         (257, 1, 1367, 1367), (257, 1, 1368, 1368), (27, 29, 2735, 2735)])
 def test_dense_waves_of_one_workgroup_share_a_unit(dtype, d, B, H, n, n_cap):
     """From 256 units on two, four or eight waves of a workgroup take a unit's row ranges, which may divide unevenly; with 255
     units the ranges go to two launches.  Against 64 bits, with the masses."""
