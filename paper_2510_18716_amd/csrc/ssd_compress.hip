@@ -146,17 +146,15 @@ static __device__ __forceinline__ void copy_fragments(int n_frag, int tid, Map m
     }
 }
 
-// One workgroup per (layer, sequence, head).  Up to RANK_MAX candidates are ranked by counting (a key per thread, LDS
-// broadcasts: cheaper than the barriers of a radix descent); more go through nth_largest.
-static constexpr int RANK_MAX = 256;
-
-template <int THREADS, int LAYERS, bool HEADS>
-__global__ __launch_bounds__(THREADS) void compress_dense_kernel(DenseSrcArgs<LAYERS, HEADS> a) {
-    constexpr int KPT = 4096 / THREADS;                       // candidates per thread, at most
+// One workgroup per (layer, sequence, head), KPT candidates per thread at most.  With one candidate per thread they are ranked
+// by counting (LDS broadcasts: cheaper than the barriers of a radix descent); more go through nth_largest.
+template <int THREADS, int KPT, int LAYERS, bool HEADS>
+__global__ __launch_bounds__(THREADS, THREADS == 1024 ? 8 : 1) void compress_dense_kernel(DenseSrcArgs<LAYERS, HEADS> a) {
     constexpr int WAVES = THREADS / 64;
+    constexpr bool RANK = KPT == 1;
     extern __shared__ int kept[];                             // [M] kept positions, ascending
-    __shared__ unsigned long long keys[RANK_MAX], share[2 * WAVES];
-    __shared__ int hist[260], count[KPT * WAVES];
+    __shared__ unsigned long long keys[RANK ? THREADS : 1], share[RANK ? 1 : 2 * WAVES];
+    __shared__ int hist[RANK ? 1 : 260], count[KPT * WAVES];
     const int BH = a.g.B * a.g.H;
     const int unit = blockIdx.x;
     const int lrel = LAYERS == 1 ? 0 : unit / BH;
@@ -205,17 +203,12 @@ __global__ __launch_bounds__(THREADS) void compress_dense_kernel(DenseSrcArgs<LA
     }
     unsigned keepbits = ~0u;                              // bit k: candidate k * THREADS + tid stays
     if (n_cand > M) {
-        if (n_cand <= RANK_MAX) {
-#pragma unroll
-            for (int k = 0; k < (RANK_MAX + THREADS - 1) / THREADS; ++k)
-                if (k * THREADS + tid < n_cand) keys[k * THREADS + tid] = key[k];
+        if constexpr (RANK) {
+            keys[tid] = key[0];                           // (0 beyond the last candidate: never counted)
             __syncthreads();
-#pragma unroll
-            for (int k = 0; k < (RANK_MAX + THREADS - 1) / THREADS; ++k) {
-                int rank = 0;
-                for (int j = 0; j < n_cand; ++j) rank += keys[j] > key[k] ? 1 : 0;
-                if (rank >= M) keepbits &= ~(1u << k);
-            }
+            int rank = 0;
+            for (int j = 0; j < n_cand; ++j) rank += keys[j] > key[0] ? 1 : 0;
+            if (rank >= M) keepbits = 0u;
         } else {
             const unsigned long long least = nth_largest<THREADS, KPT>(key, n_cand, M, hist, share, tid);
 #pragma unroll
@@ -313,11 +306,19 @@ static hipError_t launch_dense_source(const ssd_cache *cache, int lb, int le, in
     a.lpr = cf.head_dim * cache->esize / 16;
     fill_head_table(cache, lb, &a.ht);
     const size_t lds = sizeof(int) * (size_t)cache->Ml[lb];
+    const int n_cand = n_src - (n_src < cf.recent ? n_src : cf.recent);
     const unsigned units = (unsigned)((le - lb) * cf.n_seqs * cf.n_heads);
-    // few units of many tokens: sixteen waves each, so that the chip has rows enough in flight (256 units of 1500 tokens:
-    // 2 % of prompt scoring and compression together); small units start faster with four
-    if (units <= 512 && n_src > 256) hipLaunchKernelGGL((compress_dense_kernel<1024, LAYERS, HEADS>), dim3(units), dim3(1024), lds, s, a);
-    else hipLaunchKernelGGL((compress_dense_kernel<256, LAYERS, HEADS>), dim3(units), dim3(256), lds, s, a);
+    // One candidate per thread as far as it goes (8 units of 64 tokens 5.9 us, with room for 16 per thread 7.4; 4096 units 46.0 and 47.6), but
+    // a prompt that just exceeds 256 and is kept whole is a copy, for which few units want sixteen waves (8 units of 257: 7.2 us, 10.4
+    // with four).  Few units of many tokens: sixteen waves each, so that the chip has rows enough in flight (256 units of 1500 tokens: 2 % of
+    // prompt scoring and compression together), all of them on a compute unit twice (64 registers; 512 units of 600 12.7 us, 16.9
+    // with 73 registers).  More units: room for no more candidates than there may be (2048 units of 1024 tokens 51.8 us with 8 per
+    // thread, 58.3 with 16).
+    const dim3 grid(units);
+    if (n_cand <= 256 && (n_src <= 256 || n_cand > cache->Ml[lb])) hipLaunchKernelGGL((compress_dense_kernel<256, 1, LAYERS, HEADS>), grid, dim3(256), lds, s, a);
+    else if (units <= 512) hipLaunchKernelGGL((compress_dense_kernel<1024, 4, LAYERS, HEADS>), grid, dim3(1024), lds, s, a);
+    else if (n_cand <= 2048) hipLaunchKernelGGL((compress_dense_kernel<256, 8, LAYERS, HEADS>), grid, dim3(256), lds, s, a);
+    else hipLaunchKernelGGL((compress_dense_kernel<256, 16, LAYERS, HEADS>), grid, dim3(256), lds, s, a);
     return hipGetLastError();
 }
 

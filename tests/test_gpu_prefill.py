@@ -223,6 +223,67 @@ def test_cfg_mix_matches_oracle(dtype, B, V):
             assert np.array_equal(got, p[0::2].float().numpy())
 
 
+def _rows_are_the_sources(cache, K, V, pos):
+    """Every row the one-layer cache holds, both planes of every unit, is the source's row of that slot's position, bit for
+    bit.  pos: the exported table [B, H, slots]."""
+    c = cache.cfg
+    B, H, d, S = c.n_seqs, c.n_heads, c.head_dim, c.n_init_sink
+    W, M = cache.layer_budget(0)
+    sem = torch.from_numpy(cache.head_type[0] == ssd.SSD_SEMANTIC)
+    base = (-cache.mem.data_ptr()) % 256
+    off = base
+    for kind, rows in ((False, S + W), (True, M + c.stage_cap)):
+        heads = torch.nonzero(sem == kind).flatten().cuda()
+        size = B * len(heads) * 2 * rows * d * K.element_size()
+        units = cache.mem[off:off + size].view(K.dtype).view(B, len(heads), 2, rows, d)
+        off = base + (off - base + size + 255) // 256 * 256
+        at = pos[:, heads, :rows].long()
+        for plane, src in ((0, K), (1, V)):
+            want = torch.gather(src[:, heads], 2, at.clamp_min(0)[..., None].expand(-1, -1, -1, d))
+            same = (units[:, :, plane] == want).all(dim=-1) | (at < 0)
+            assert bool(same.all()), ("semantic" if kind else "spatial", "KV"[plane], torch.nonzero(~same)[:4].tolist())
+
+
+def _dense_source_selection(B, H, n, scores, dtype="bf16", d=64, M=48, W=20, R=1, heads=False):
+    from paper_2510_18716_amd.binding import make_config
+    say("dense-source selection", B, H, n, scores, dtype, d, "M", M, "per-head", heads)
+    S = 1
+    g = torch.Generator(device="cuda").manual_seed(n)
+    u = torch.rand((B, H, n), generator=g, device="cuda")
+    score = {"spread": -torch.log(u.clamp_min(1e-6)), "few": (u * 5).floor() * 0.25, "equal": torch.full_like(u, 0.7),
+             "zero": torch.zeros_like(u), "wide": torch.exp2(60 * u - 40)}[scores].contiguous()
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    K = torch.randn((B, H, n, d), generator=g, device="cuda", dtype=tdt)
+    V = torch.randn((B, H, n, d), generator=g, device="cuda", dtype=tdt)
+    ht = np.zeros((1, H), np.uint8)
+    ht[0, H // 2:] = ssd.SSD_SEMANTIC
+    own = np.where(ht[0] == ssd.SSD_SEMANTIC, M, W)
+    if heads:
+        own = np.maximum(1, own - np.arange(H) % 5 * (own // 6))     # the first head of each type has the largest
+        own[0], own[H // 2] = W, M
+    cache = ssd.Cache(make_config(1, B, H, d, dtype, W, S, M, R, R + 2), ht, head_budget=own[None] if heads else None)
+    ssd.ssd_compress_kv(cache, 0, 1, K, V, score, n)
+    table = cache.export(0)
+    _rows_are_the_sources(cache, K, V, table[0])
+    pos, count, kept_score = (t.cpu().numpy() for t in table)
+    sc = score.cpu().numpy()
+    n_cand = n - min(n, R)
+    for b in range(0, B, 7):
+        for h in range(H):
+            if h < H // 2:
+                want = sorted(set(range(min(S, n))) | set(range(max(S, n - own[h]), n)))
+                assert sorted(p for p in pos[b, h] if p >= 0) == want
+            else:
+                order = np.lexsort((np.arange(n_cand), -sc[b, h, :n_cand]))[:own[h]]
+                heavy = sorted(int(i) for i in order)
+                want = heavy + list(range(n_cand, n))
+                assert [int(p) for p in pos[b, h][:len(heavy)]] == heavy
+                assert [int(p) for p in pos[b, h][M:M + n - n_cand]] == want[len(heavy):]
+                assert np.array_equal(kept_score[b, h][:len(heavy)], sc[b, h][heavy])
+            assert count[b, h] == len(want)
+    return cache, V, pos
+
+
 @pytest.mark.parametrize("B,H", [(2, 4), (40, 16)])              # few units: a wide workgroup each; many: the narrow one
 @pytest.mark.parametrize("n", [5, 64, 70, 257, 300, 1024, 1500, 4096])
 @pytest.mark.parametrize("scores", ["spread", "few", "equal", "zero", "wide"])
@@ -230,42 +291,26 @@ def test_dense_source_selection_is_the_sorted_one(B, H, n, scores):
     """The kept set of the dense-source mode is what a sort by (score, lower position first) keeps, exactly, whatever the
     scores look like to a radix descent: long-tailed, a handful of distinct values, all equal, all zero, 60 binary
     orders of magnitude; the kept rows are the source's, bit for bit, in ascending order of position."""
-    from paper_2510_18716_amd.binding import make_config
-    if B * H > 512 and n > 1024:
-        pytest.skip("the same code at more memory")
-    M, R, W, S, d = 48, 1, 20, 1, 64
-    say("dense-source selection", B, H, n, scores)
-    g = torch.Generator(device="cuda").manual_seed(n)
-    u = torch.rand((B, H, n), generator=g, device="cuda")
-    score = {"spread": -torch.log(u.clamp_min(1e-6)), "few": (u * 5).floor() * 0.25, "equal": torch.full_like(u, 0.7),
-             "zero": torch.zeros_like(u), "wide": torch.exp2(60 * u - 40)}[scores].contiguous()
-    K = torch.randn((B, H, n, d), generator=g, device="cuda").to(torch.bfloat16)
-    V = torch.randn((B, H, n, d), generator=g, device="cuda").to(torch.bfloat16)
-    ht = np.zeros((1, H), np.uint8)
-    ht[0, H // 2:] = ssd.SSD_SEMANTIC
-    cache = ssd.Cache(make_config(1, B, H, d, "bf16", W, S, M, R, R + 2), ht)
-    ssd.ssd_compress_kv(cache, 0, 1, K, V, score, n)
-    pos, count, kept_score = (t.cpu().numpy() for t in cache.export(0))
+    cache, V, pos = _dense_source_selection(B, H, n, scores)
+    d = V.shape[-1]
     q = torch.zeros((1, B, H, d), dtype=torch.bfloat16, device="cuda")
     out = torch.empty_like(q)
     ssd.ssd_decode_attn(cache, 0, 1, q, out, False)               # zero query: the mean of the kept rows
-    torch.cuda.synchronize()
-    sc, Vh, got = score.cpu().numpy(), V.float().cpu().numpy(), out.float().cpu().numpy()[0]
-    n_cand = n - min(n, R)
+    got = out.float().cpu().numpy()[0]
     for b in range(0, B, 7):
+        Vb = V[b].float().cpu().numpy()
         for h in range(H):
-            if h < H // 2:
-                want = sorted(set(range(min(S, n))) | set(range(max(S, n - W), n)))
-                assert sorted(p for p in pos[b, h] if p >= 0) == want
-            else:
-                order = np.lexsort((np.arange(n_cand), -sc[b, h, :n_cand]))[:M]
-                heavy = sorted(int(i) for i in order)
-                want = heavy + list(range(n_cand, n))
-                assert [int(p) for p in pos[b, h][:len(heavy)]] == heavy
-                assert [int(p) for p in pos[b, h][M:M + n - n_cand]] == want[len(heavy):]
-                assert np.array_equal(kept_score[b, h][:len(heavy)], sc[b, h][heavy])
-            assert count[b, h] == len(want)
-            np.testing.assert_allclose(got[b, h], Vh[b, h][want].mean(axis=0), atol=2e-2, rtol=1e-2)
+            want = sorted(int(p) for p in pos[b, h] if p >= 0)
+            np.testing.assert_allclose(got[b, h], Vb[h][want].mean(axis=0), atol=2e-2, rtol=1e-2)
+
+
+@pytest.mark.parametrize("dtype,d,heads", [("bf16", 128, False), ("f32", 128, False), ("f32", 64, True), ("bf16", 128, True)])
+@pytest.mark.parametrize("B,H", [(2, 4), (32, 16), (27, 19)])    # 512 units are the last few
+@pytest.mark.parametrize("n,M,R", [(40, 48, 1), (256, 30, 0), (257, 48, 1), (257, 300, 1), (258, 48, 1), (260, 255, 8), (2049, 48, 1), (2050, 48, 1)])
+def test_dense_source_at_the_edges_of_its_shapes(dtype, d, heads, B, H, n, M, R):
+    """256 candidates (n - R), ranked by counting, and one more; a prompt just longer than that and kept whole; 2048 and one
+    more; rows of 16 and of 32 fragments; budgets per head."""
+    _dense_source_selection(B, H, n, "spread", dtype, d, M, W=20, R=R, heads=heads)
 
 
 def _mix_case(n, V, dtype, gamma):
