@@ -218,11 +218,19 @@ struct NoHook { __device__ __forceinline__ void operator()() const {} };
 // PAD: every chunk issues its full 2 * CH loads and consumes them all (see `load` and `compute`); this is what
 // launches of few rounds want.  Without it loads and arithmetic past the end are skipped, which is slightly
 // better when many rounds of waves hide each other's waits anyway (the full-cache kernel).
-// PEEL (with PAD): the last chunk is computed outside the loop, so none is requested in vain while the loop's requests stay
-// unconditional.  Where a unit has one wave and one workgroup: 2048 units of 66 rows 15.4 -> 14.7 us per launch, with budgets of
-// 32..96 per head 16.3 -> 16.1.  Not elsewhere: 4096 units under Algorithm 2 lose 1.7 %, with budgets per head 2.4 %, parts
-// of a split call with two waves per unit 3.5 %.
-template <typename T, int D, int CH, bool ZBUF, bool MASS, typename Hook = NoHook, bool PAD = true, bool PEEL = true>
+// LAST (with PAD), where the last chunk is computed, so that none is requested in vain behind it while the loop's requests
+// stay unconditional:
+//   LAST_OUTSIDE  outside the loop.  Where a unit has one wave and one workgroup: 2048 units of 66 rows 15.4 -> 14.7 us per
+//                 launch, with budgets of 32..96 per head 16.3 -> 16.1.  It takes about 30 registers (fused step, bf16, d = 128: 133
+//                 in place of 103), a wave per SIMD: two launches of 2048 such units side by side take 23.4 us for 24.0 all the
+//                 same.  Not elsewhere: 4096 units under Algorithm 2 lose 1.7 %, with budgets per head 2.4 %, parts of a split
+//                 call with two waves per unit 3.5 %.
+//   LAST_OF_ONE   outside the loop if it is the only one (7B shape, two streams: 737 -> 730 us per step).
+//   LAST_IN_LOOP  in the loop; a chunk is requested behind it and dropped.  The attention alone, four units per workgroup:
+//                 the second copy of the arithmetic costs more than the request (16384 units of 16 rows 28.8 us, 30.2 with
+//                 LAST_OF_ONE; 8192 of 64 45.7 and 46.7).
+enum { LAST_IN_LOOP, LAST_OF_ONE, LAST_OUTSIDE };
+template <typename T, int D, int CH, bool ZBUF, bool MASS, typename Hook = NoHook, bool PAD = true, int LAST = LAST_IN_LOOP>
 static __device__ __forceinline__ void stream_rows(const char *__restrict__ Kb, const char *__restrict__ Vb,
                                                   int row_bytes, const Segs &sg, int row_begin, int row_end,
                                                   int first_iter, int iter_stride,
@@ -302,7 +310,7 @@ static __device__ __forceinline__ void stream_rows(const char *__restrict__ Kb, 
     for (int i = 0; i < CH; ++i) { ka[i] = va[i] = kb[i] = vb[i] = make_uint4(0, 0, 0, 0); }
     load(it, ka, va);
     after_first_issue();
-    if constexpr (PAD && PEEL) {
+    if constexpr (PAD && LAST == LAST_OUTSIDE) {
         for (;;) {
             if (it + chunk_iters >= n_iter) { compute(it, ka, va); return; }
             load(it + chunk_iters, kb, vb);
@@ -314,9 +322,8 @@ static __device__ __forceinline__ void stream_rows(const char *__restrict__ Kb, 
             it += chunk_iters;
         }
     }
-    if (PAD && it + chunk_iters >= n_iter) {       // one chunk is all there is: no second request to drop (7B shape: 737 -> 730 us)
-        compute(it, ka, va);
-        return;
+    if constexpr (PAD && LAST == LAST_OF_ONE) {
+        if (it + chunk_iters >= n_iter) { compute(it, ka, va); return; }
     }
     for (;;) {                                     // PAD: the chunk after the last one is requested too (clamped) and dropped
         if (PAD || it + chunk_iters < n_iter) load(it + chunk_iters, kb, vb);

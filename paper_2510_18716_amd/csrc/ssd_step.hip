@@ -313,8 +313,9 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
     // The row a compression after every token may promote is known beforehand: with one candidate in the row buffer that
     // is not the new token (one_old), its oldest row.  Fetched with the scores it is in registers when the selection has
     // decided; read only then, its round trip to memory ends the launch whenever one unit of it promotes (7B shape, two
-    // streams: 742 -> 737 us per step).
-    const bool one_old = compress && t_c - t_R == 1 && (!FUSED || t_R > 0);
+    // streams: 742 -> 737 us per step).  Units of few rows feel the row more than the wait: 3072 units of 17 rows 9.07 -> 9.4
+    // us, from 32 rows or 8192 units on it gains.  The attention alone never compresses and does without (106 -> 96 registers).
+    const bool one_old = FUSED && compress && t_c - t_R == 1 && t_R > 0;
     uint4 pre_row = make_uint4(0, 0, 0, 0);               // lanes 0..LPR-1: the K row, LPR..2*LPR-1: the V row (LPR <= 32)
 
     // Runs once, right after the stream's first loads have been issued, so that nothing here delays them: the
@@ -347,15 +348,18 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
                 pre_score[k] = u.score[slot];
                 pre_pos[k] = u.pos[slot];
             }
-            const char *plane = (lane / LPR) & 1 ? u.V : u.K;             // unconditional (like the scores): a slot of the unit in any case
-            pre_row = *reinterpret_cast<const uint4 *>(plane + (size_t)(t_M + t_base) * (size_t)t_row_bytes + (size_t)sub * 16u);
+            if constexpr (FUSED) {
+                const char *plane = (lane / LPR) & 1 ? u.V : u.K;         // unconditional (like the scores): a slot of the unit in any case
+                pre_row = *reinterpret_cast<const uint4 *>(plane + (size_t)(t_M + t_base) * (size_t)t_row_bytes + (size_t)sub * 16u);
+            }
         }
     };
-    constexpr bool PEEL = WPB == 1 && SHARE == 1;         // up to 2048 units, a wave each (see stream_rows)
+    // (one unit per workgroup: up to 2048 units, a wave each, and launches whose logits and selection scratch leave LDS for no more)
+    constexpr int LAST = SHARE > 1 || (FUSED && WPB > 1) ? LAST_OF_ONE : WPB == 1 ? LAST_OUTSIDE : LAST_IN_LOOP;
     if (want_z)
-        stream_rows<T, D, CH, true, false, decltype(after_first_issue), true, PEEL>(u.K, u.V, a.g.row_bytes, sg, 0, sg.total, part, SHARE, q, a.qscale, sm, zbuf, 0, 0, after_first_issue);
+        stream_rows<T, D, CH, true, false, decltype(after_first_issue), true, LAST>(u.K, u.V, a.g.row_bytes, sg, 0, sg.total, part, SHARE, q, a.qscale, sm, zbuf, 0, 0, after_first_issue);
     else
-        stream_rows<T, D, CH, false, false, decltype(after_first_issue), true, PEEL>(u.K, u.V, a.g.row_bytes, sg, 0, sg.total, part, SHARE, q, a.qscale, sm, nullptr, 0, 0, after_first_issue);
+        stream_rows<T, D, CH, false, false, decltype(after_first_issue), true, LAST>(u.K, u.V, a.g.row_bytes, sg, 0, sg.total, part, SHARE, q, a.qscale, sm, nullptr, 0, 0, after_first_issue);
     if (FUSED && part == 0) {
         // The new token, from the registers it was loaded into, is folded into lane group 0's softmax as
         // one more row (index sg.total).
