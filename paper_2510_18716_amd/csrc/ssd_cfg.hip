@@ -7,8 +7,8 @@
 // image vocabulary the launch itself (64 prompts of 16384: 8.4 MB, 1.6 us at the rate of a large read).  Each lane takes
 // 16-byte fragments of the two rows (coalesced) and writes fp32.  Rows of a length that breaks the 16-byte alignment are
 // read and written in the same pieces, element-aligned (the hardware takes a 16-byte access at any element boundary);
-// the last, shorter piece of a row goes element by element, all of its loads in flight together.  Rows of at most 64 pieces
-// share a workgroup.
+// the last, shorter piece of a row goes element by element, all of its loads in flight together.  Short rows share
+// a workgroup.
 // Measured, against one element per lane with a division each for unaligned rows and flat pieces with a division each for
 // aligned ones: 256 prompts of 47911 (bf16) 20.0 -> 17.5 us (4.8 TB/s); 256 of 65536 22.5 -> 22.7; 64 prompts of 16384 stay at 3.5 us,
 // the launch.  Short rows: 65536 prompts of 16 3.5 us (30 with a workgroup of its own for each row), 16384 of 257 9.2 -> 7.7.
@@ -107,8 +107,11 @@ static hipError_t launch_mix_few(const CfgArgs &a, hipStream_t s) {
 template <typename T, bool ALIGNED>
 static hipError_t launch_mix(CfgArgs a, hipStream_t s) {
     const int want = a.V / Elem<T>::VEC + (ALIGNED ? 0 : 1);   // pieces of a row, the shorter last one included
-    // (rows of 65 to 128 pieces are faster with a workgroup each, half of it idle: 16384 prompts of 1024, bf16, 20.5 us against 23.1)
-    a.lanes_log2 = want > 64 ? 8 : 0;
+    // A workgroup of its own for a row of at most 128 pieces leaves half of it idle: 4096 prompts of 512 (fp32) 4.1 us shared, 4.7
+    // alone; 16384 of 132 4.8 and 9.7.  Where HBM bounds the launch, bf16 rows (half of whose traffic is stores of two pieces per lane) gain
+    // by it: 16384 of 1024 23.2 us shared, 20.9 alone; 8192 of 640 7.8 and 7.5; 8192 of 520 6.5 and 6.9.
+    const bool alone = want > 128 || (sizeof(T) == 2 && want >= 64 && (long long)a.V * a.n_prompts > 5000000);
+    a.lanes_log2 = alone ? 8 : 0;
     while (a.lanes_log2 < 8 && 1 << a.lanes_log2 < want) ++a.lanes_log2;
     const int rows = 256 >> a.lanes_log2, gx = want / 256 + (want % 256 ? 1 : 0);
     const int gy = a.n_prompts / rows + (a.n_prompts % rows ? 1 : 0);
