@@ -559,8 +559,8 @@ static void fill_head_order(const ssd_cache *c, int l, const LayerState &before,
 }
 
 // One launch of the variant (WPB units per workgroup, or one unit shared by SHARE waves) that the call asks for.  One
-// layer: the short argument block (four wave-loads per chunk, which is what the library picks; the other chunk sizes
-// exist for sweeps and take the long block).
+// layer: the short argument block (four or five wave-loads per chunk, which is what the library picks; the other chunk
+// sizes exist for sweeps and take the long block).
 template <typename T, int D, int CH, int WPB, int SHARE>
 static void launch_variant(const StepArgs &full, const HeadOrder *ho, dim3 blocks, size_t lds, int layers, bool fused, hipStream_t s) {
     const dim3 threads(WPB * SHARE * 64);
@@ -609,12 +609,21 @@ static hipError_t launch_step(StepArgs &full, const HeadOrder *ho, const LaunchS
     int wpb = shape.wpb ? shape.wpb : (units <= 2048 ? 1 : 4);
     // Several waves per unit (codes 12 and 14: two and four) where one wave per unit leaves wave slots empty:
     //  * few and long units (the high-resolution shape, 2048 units of 129 to 385 rows): four, 41.0 -> 38.1 us;
-    //  * 768 units per call or fewer, every one longer than two chunks: four waves, and five wave-loads per chunk where
-    //    that takes a wave a chunk fewer (65 to 80 rows of 256 bytes: one chunk, everything a unit needs requested at
-    //    once).  With one wave per unit such a launch is three waves on each CU going through a chain of round trips.
-    //    1B shape, W = M = 64, us per launch: 256 units 6.8 -> 5.8, 512 units 7.7 -> 7.1, 768 units 8.7 -> 8.5, budgets of
-    //    32..96 per head at 512 units 9.0 -> 7.9; 1024 units lose (9.9 -> 10.8), and so do short ones (25 rows, 512
-    //    units: 5.4 -> 5.7).  By the units of the whole call, so that the parts of a split call take what it would take.
+    //  * 512 units per call or fewer, both head types longer than two chunks: four waves.  With one wave per unit such a
+    //    launch is two waves on each CU going through a chain of round trips.  us per launch, one wave and four (bf16,
+    //    d = 128, fused, W = M = rows): 33 rows, 32 units 4.9 and 4.3, 512 units 5.7 and 5.3; 64 rows, 256 units 6.3 and 5.5,
+    //    512 units 7.2 and 6.4; plain attention of 64 rows, 512 units 6.7 and 6.3.  With budgets per head what the largest
+    //    head of each type streams counts: 512 units, budgets of 32..96 8.2 and 7.6, of 1..64 6.6 and 6.2, of 1..40 5.4 and 5.5.
+    //    25 rows lose (512 units: 5.4 and 5.7).  By the units of the whole call, so that the parts of a split call take
+    //    what it would take.
+    //  * up to 768 such units if four waves take each in one chunk of five wave-loads (below; not with the rotary step),
+    //    or if they have 96 rows or more.  Others lose: 576 units of 33 rows 5.95 and 6.3, 768 of 40 6.7 and 6.9, of 80 9.5 and
+    //    9.75; rotary, 768 of 64 9.55 and 9.9.  1024 units of 64 rows 9.9 and 10.8: four waves each are more than the three per SIMD
+    //    that the registers allow.
+    //  * with four waves in a call of up to 768 units, five wave-loads per chunk where that takes a wave a chunk fewer and
+    //    leaves at most two loads of its last chunk unused: 65 to 80 rows of 256 bytes are one chunk, everything a unit
+    //    needs requested at once (512 units of 66 rows: 7.2 us with four loads, 6.5 with five; 128 rows 11.1 and 10.8).  With
+    //    three unused it loses (plain attention, 512 units of 256 rows: 14.9 and 15.6).
     //  * parts of a split call, two launches in flight: two waves for parts of 1025 to 2048 units (7B shape,
     //    128 sequences on two streams: 0.705 -> 0.687 ms per step), four for parts of 513 to 1024 units (64
     //    sequences: 0.415 -> 0.385 ms).  Alone on the chip such launches are faster with one wave per unit
@@ -624,9 +633,13 @@ static hipError_t launch_step(StepArgs &full, const HeadOrder *ho, const LaunchS
         constexpr int RPW = 1024 / (D * (int)sizeof(T));  // rows per wave-load
         const int shortest = max_sp_heads == 0 ? a.se.total : max_se_heads == 0 ? a.sp.total : a.se.total < a.sp.total ? a.se.total : a.sp.total;
         const int loads = ((longest + RPW - 1) / RPW + 3) / 4;                // of one of four waves
-        if (call_units <= 768 && shortest > 8 * RPW) {
+        const int chunks = (loads + 4) / 5;
+        const bool long_enough = shortest > 8 * RPW;
+        const bool five = chunks < (loads + 3) / 4 && 5 * chunks - loads <= 2;
+        const bool small = call_units <= 512 || (call_units <= 768 && (longest >= 96 || (five && chunks == 1 && !a.rope_layout)));
+        if (small && long_enough) {
             wpb = 14;
-            if (!shape.ch && (loads + 4) / 5 < (loads + 3) / 4) ch = 5;
+            if (five && !shape.ch) ch = 5;
         } else if (longest >= 96 && !heads) wpb = 14;     // (budgets per head: `longest` is the largest head's, most units are shorter)
         else if (concurrent && units > 1024) wpb = 12;
         else if (concurrent && units > 512) wpb = 14;

@@ -480,8 +480,7 @@ def test_few_long_heads_beside_many_short_ones(fused):
                                                  ("bf16", 128, 81, 4, 4), ("bf16", 128, 129, 5, 5), ("bf16", 64, 130, 5, 5),
                                                  ("f32", 64, 66, 5, 5), ("f32", 128, 33, 5, 5)])
 def test_small_calls_give_a_unit_four_waves_and_one_chunk_if_it_fits(dtype, d, rows, ch, ch3):
-    """Calls of at most 768 units: four waves per unit, and five loads per chunk where that saves a chunk; one chunk holds 4 *
-    ch loads of 1 KB.  `rows`: what the units stream beside the new token; the three calls stream the new one as well (ch3)."""
+    """Small calls: four waves per unit, and five loads per chunk where that saves a chunk; one chunk holds 4 * ch loads of 1 KB.  `rows`: what the units stream beside the new token; the three calls stream the new one as well (ch3)."""
     base = workload.Workload("small-call-%d" % rows, L=2, prompts=2, H=6, d=d, dtype=dtype, n0=9, grid_h=4, grid_w=rows // 2, W=rows,
                              M=rows - 1, S=1, R=1, C=3, cadence=1, seed=300 + rows, plain=True)
     for fused in (False, True):
@@ -495,6 +494,20 @@ def test_small_calls_give_a_unit_four_waves_and_one_chunk_if_it_fits(dtype, d, r
     c = _full_compare(base.replace(name=base.name + "-heads", W=rows, M=rows, head_budget=hb.tolist()), lpc=1, k_units=12, export_every=7,
                       fused=True)
     assert c.last_launch_shape()[1] == 14
+
+
+@pytest.mark.parametrize("dtype,d,rows,prompts,rope,shape", [
+    ("bf16", 128, 40, 32, 0, (4, 14)), ("bf16", 128, 40, 33, 0, (4, 1)),                       # 512 units and 528
+    ("bf16", 128, 65, 48, 0, (5, 14)), ("bf16", 128, 65, 48, 1, (4, 1)), ("bf16", 128, 65, 49, 0, (4, 1)),    # 768 in one chunk, 784
+    ("bf16", 128, 81, 48, 0, (4, 1)), ("bf16", 128, 100, 48, 1, (4, 14)), ("bf16", 128, 129, 48, 0, (5, 14)),
+    ("f32", 128, 33, 40, 0, (5, 14)), ("f32", 128, 41, 40, 0, (4, 1)), ("bf16", 64, 70, 36, 0, (4, 1)),
+    ("bf16", 128, 257, 2, 0, (4, 14)), ("bf16", 128, 273, 2, 0, (5, 14))])                    # three and two loads of the last chunk unused
+def test_calls_around_512_and_768_units(dtype, d, rows, prompts, rope, shape):
+    """Which launch a call of 16 units per prompt takes, and its results."""
+    wl = workload.Workload("call-of-%d-units" % (16 * prompts), L=1, prompts=prompts, H=8, d=d, dtype=dtype, n0=9, grid_h=4, grid_w=rows // 2, W=rows,
+                           M=rows - 1, S=1, R=1, C=3, cadence=1, seed=500 + rows, plain=True)
+    c = _full_compare(wl, lpc=1, k_units=8, export_every=23, device_gen=True, fused=True, rope=rope)
+    assert c.last_launch_shape()[:2] == shape
 
 
 @pytest.mark.parametrize("fused", [False, True], ids=["three-calls", "fused-step"])
