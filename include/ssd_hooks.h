@@ -41,9 +41,12 @@ int ssd_cache_spatial_slot(const ssd_cache *cache, int layer, int head, int posi
  * kernel, which the library otherwise picks from the launch size.  Results
  * change by rounding only: ch and the number of wavefronts per unit set the
  * order of the fp32 softmax sums (the library's own choice is ch = 4 and one
- * wavefront, two or four as the launch size says, or ch = 5 and four, which only
- * the library takes); units per workgroup and new_rows change nothing.  (0, 0, 0) restores the library's choice.
- *   ch       : wave-wide loads of K (and of V) per chunk: 0, 1, 2, 4
+ * wavefront, two or four as the launch size says, or ch = 5 and four); units
+ * per workgroup and new_rows change nothing.  (0, 0, 0) restores the library's
+ * choice.  Launches with the rotary step or budgets per head exist with ch = 4
+ * and 5 only; they take 4 for 1 and 2.
+ *   ch       : wave-wide loads of K (and of V) per chunk: 0, 1, 2, 4, and 5
+ *              with wpb = 14
  *   wpb      : units per workgroup: 0, 1, 2, 4; 12 / 14 = one unit per workgroup
  *              shared by 2 / 4 wavefronts
  *   new_rows : fused step: 1 / 2 = store the new token's rows at the start of /
@@ -54,7 +57,7 @@ int ssd_cache_set_launch_shape(ssd_cache *cache, int ch, int wpb, int new_rows);
 
 /*
  * The shape the cache's newest attention / step launch took, in the codes of
- * ssd_cache_set_launch_shape: out3 = { ch, wpb, new_rows } (all 0 before the
+ * ssd_cache_set_launch_shape, which accepts it: out3 = { ch, wpb, new_rows } (all 0 before the
  * first launch).  Lets a test check which results must be equal bit for bit.
  */
 int ssd_cache_last_launch_shape(const ssd_cache *cache, int32_t out3[3]);

@@ -605,7 +605,7 @@ static hipError_t launch_step(StepArgs &full, const HeadOrder *ho, const LaunchS
     // token's rows are stored after the stream (see the kernel).
     const long long units = (long long)H * B * layers;
     a.late_new_store = shape.new_rows == 1 ? 0 : shape.new_rows == 2 ? 1 : (units > 2048 && units <= 16384 ? 1 : 0);
-    int ch = shape.ch && !heads && !a.rope_layout ? shape.ch : 4;
+    int ch = shape.ch && (shape.ch == 5 || (!heads && !a.rope_layout)) ? shape.ch : 4;
     int wpb = shape.wpb ? shape.wpb : (units <= 2048 ? 1 : 4);
     // Several waves per unit (codes 12 and 14: two and four) where one wave per unit leaves wave slots empty:
     //  * few and long units (the high-resolution shape, 2048 units of 129 to 385 rows): four, 41.0 -> 38.1 us;
@@ -826,7 +826,7 @@ using namespace ssd;
 extern "C" int ssd_cache_set_launch_shape(ssd_cache *cache, int ch, int wpb, int new_rows) {
     clear_error();
     if (!cache) return fail(SSD_ERR_INVALID_ARG, "cache is NULL");
-    if ((ch != 0 && ch != 1 && ch != 2 && ch != 4) || (wpb != 0 && wpb != 1 && wpb != 2 && wpb != 4 && wpb != 12 && wpb != 14) ||
+    if ((ch != 0 && ch != 1 && ch != 2 && ch != 4 && !(ch == 5 && wpb == 14)) || (wpb != 0 && wpb != 1 && wpb != 2 && wpb != 4 && wpb != 12 && wpb != 14) ||
         new_rows < 0 || new_rows > 2)
         return fail(SSD_ERR_INVALID_ARG, "launch shape (%d, %d, %d) is not one the library has", ch, wpb, new_rows);
     cache->shape = LaunchShape{ch, wpb, new_rows};

@@ -575,6 +575,17 @@ def test_launch_shape_hook_accepts_only_shapes_the_library_has():
     assert ssd.lib.ssd_cache_last_launch_shape(a.handle, None) == ssd.SSD_ERR_INVALID_ARG
 
 
+def test_launch_shape_hook_accepts_every_shape_the_library_takes_by_itself():
+    """Five loads per chunk come with four wavefronts per unit and with nothing else."""
+    a = ssd.Cache(make_config(1, 2, 4, 64, "f32", 5, 1, 4, 1, 3), _ht(1, 4), device=None)
+    for rows in (0, 1, 2):
+        a.set_launch_shape(5, 14, rows)
+    for wpb in (0, 1, 2, 4, 12):
+        with pytest.raises(ssd.SsdError) as e:
+            a.set_launch_shape(5, wpb, 0)
+        assert e.value.code == ssd.SSD_ERR_INVALID_ARG
+
+
 def test_dense_split_hook_rejects_bad_split_counts_before_any_launch():
     lib = ssd.lib
     ok = (FAKE, FAKE, FAKE, FAKE, 1, 1, 64, ssd.SSD_F32, 8, 4, 0.0, None, None, 1, 0, 32)

@@ -496,6 +496,26 @@ def test_small_calls_give_a_unit_four_waves_and_one_chunk_if_it_fits(dtype, d, r
     assert c.last_launch_shape()[1] == 14
 
 
+@pytest.mark.parametrize("rope,heads", [(0, False), (1, False), (0, True), (1, True)])
+def test_a_reported_launch_shape_pins_the_same_results(rope, heads):
+    """What ssd_cache_last_launch_shape reports, handed to ssd_cache_set_launch_shape, gives the same launch: every bit equal."""
+    wl = workload.Workload("pinned", L=1, prompts=2, H=6, d=128, dtype="bf16", n0=9, grid_h=4, grid_w=33, W=66, M=66, S=1, R=1, C=3, cadence=1,
+                           seed=21, plain=True, head_budget=[[66, 40, 50, 33, 45, 66]] if heads else None)
+    ht = workload.head_map(wl)
+    data = workload.generate(wl, device="cuda", head_type=ht)
+    sched, units, last = workload.compress_schedule(wl), sample_units(wl, ht, 10 ** 9), [wl.n_total - 1]
+    a, b = (make_cache(wl, ht, torch.device("cuda")) for _ in range(2))
+    for c in (a, b):
+        gpu_decode(wl, data, ht, sched, units, p_end=last[0], fused=True, rope=rope, cache=c, shadow=False)
+    o1, e1, _ = gpu_decode(wl, data, ht, sched, units, export_steps=last, p_begin=last[0], fused=True, rope=rope, cache=a, shadow=False)
+    shape = a.last_launch_shape()
+    assert shape[:2] == (5, 14)
+    o2, e2, _ = gpu_decode(wl, data, ht, sched, units, export_steps=last, p_begin=last[0], fused=True, rope=rope, cache=b, shape=shape, shadow=False)
+    assert b.last_launch_shape() == shape
+    assert np.array_equal(o1, o2)
+    assert all(np.array_equal(x, y) for x, y in zip(e1[last[0]]["post"], e2[last[0]]["post"]))
+
+
 @pytest.mark.parametrize("dtype,d,rows,prompts,rope,shape", [
     ("bf16", 128, 40, 32, 0, (4, 14)), ("bf16", 128, 40, 33, 0, (4, 1)),                       # 512 units and 528
     ("bf16", 128, 65, 48, 0, (5, 14)), ("bf16", 128, 65, 48, 1, (4, 1)), ("bf16", 128, 65, 49, 0, (4, 1)),    # 768 in one chunk, 784
