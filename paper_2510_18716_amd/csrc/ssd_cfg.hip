@@ -109,8 +109,8 @@ static hipError_t launch_mix(CfgArgs a, hipStream_t s) {
     const int want = a.V / Elem<T>::VEC + (ALIGNED ? 0 : 1);   // pieces of a row, the shorter last one included
     // A workgroup of its own for a row of at most 128 pieces leaves half of it idle: 4096 prompts of 512 (fp32) 4.1 us shared, 4.7
     // alone; 16384 of 132 4.8 and 9.7.  Where HBM bounds the launch, bf16 rows (half of whose traffic is stores of two pieces per lane) gain
-    // by it: 16384 of 1024 23.2 us shared, 20.9 alone; 8192 of 640 7.8 and 7.5; 8192 of 520 6.5 and 6.9.
-    const bool alone = want > 128 || (sizeof(T) == 2 && want >= 64 && (long long)a.V * a.n_prompts > 5000000);
+    // by it: 16384 of 1024 23.2 us shared, 20.9 alone; 4096 of 1000 6.5 and 6.2; 4096 of 640 5.0 and 5.2.
+    const bool alone = want > 128 || (sizeof(T) == 2 && want >= 64 && (long long)a.V * a.n_prompts > 4000000);
     a.lanes_log2 = alone ? 8 : 0;
     while (a.lanes_log2 < 8 && 1 << a.lanes_log2 < want) ++a.lanes_log2;
     const int rows = 256 >> a.lanes_log2, gx = want / 256 + (want % 256 ? 1 : 0);

@@ -335,11 +335,11 @@ def test_cfg_mix_more_prompts_than_one_grid_dimension_holds(V):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n,V", [(1, 1), (3, 7), (85714, 7), (85715, 7), (150001, 4), (4099, 257), (9001, 67), (2333, 515), (601, 1030), (5, 8), (999, 8),
-                                 (1001, 24), (70, 512), (67, 520), (33, 264), (9765, 512), (9766, 512), (9767, 513), (37, 1024), (37, 1032), (37, 516), (1, 600001),
+                                 (1001, 24), (70, 512), (67, 520), (33, 264), (7812, 512), (7813, 512), (7813, 513), (37, 1024), (37, 1032), (37, 516), (1, 600001),
                                  (2, 4 * 65537 * 4)])
 def test_cfg_mix_short_rows_and_little_work(dtype, n, V):
     """Unaligned rows on both sides of 600000 elements in all (one element per lane; pieces), rows of 1 to 128 pieces that share
-    a workgroup and of 129 that do not, bf16 rows of 64 on both sides of 5000000 elements in all, every remainder of a piece,
+    a workgroup and of 129 that do not, bf16 rows of 64 on both sides of 4000000 elements in all, every remainder of a piece,
     a last workgroup with rows missing, rows longer than a grid's first pass."""
     say("cfg mix", dtype, n, V)
     _mix_case(n, V, dtype, 5.0)
