@@ -147,13 +147,18 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
+# torch's own accessors of the current stream's raw handle and device; not part of its public interface, so they may be missing
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream=None) -> Optional[int]:
-    """Raw handle of `stream`, or of torch's current stream.  The handle itself is asked for: torch.cuda.current_stream()
-    builds a stream object and is_available() counts devices, 2.5 us of a call that takes 5."""
+    """Raw handle of `stream`, or of torch's current stream.  The handle itself is asked for where torch lets it be:
+    torch.cuda.current_stream() builds a stream object and is_available() counts devices, 2.5 us of a call that takes 5."""
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
-    if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+        return _raw_stream(_raw_device())
     if torch.cuda.is_available():
         return torch.cuda.current_stream().cuda_stream
     return None

@@ -345,8 +345,13 @@ def test_cfg_mix_short_rows_and_little_work(dtype, n, V):
     _mix_case(n, V, dtype, 5.0)
 
 
-def test_binding_takes_torchs_current_stream():
+@pytest.mark.parametrize("missing", [None, "_raw_stream", "_raw_device"])
+def test_binding_takes_torchs_current_stream(missing, monkeypatch):
+    """Also where torch does not have the accessors of the raw handle."""
+    from paper_2510_18716_amd import binding
     from paper_2510_18716_amd.binding import _stream
+    if missing:
+        monkeypatch.setattr(binding, missing, None)
     side = torch.cuda.Stream()
     assert (_stream() or 0) == torch.cuda.current_stream().cuda_stream
     with torch.cuda.stream(side):
