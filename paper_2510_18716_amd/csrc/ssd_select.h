@@ -36,11 +36,20 @@ static __device__ __forceinline__ void lds_sync() {
 }
 
 // Order this wave's earlier global stores before its later global loads and stores (rows, scores and
-// positions that one lane wrote and another lane of the same wave is about to read or overwrite).
+// positions that one lane wrote and another lane of the same wave is about to read), and wait for them.
 static __device__ __forceinline__ void wave_global_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// Order this wave's earlier global stores before its later ones to the same addresses by other lanes.  The memory
+// operations of one wave reach an address in the order they were issued, so this emits no wait: it keeps the compiler from
+// changing that order.
+static __device__ __forceinline__ void wave_store_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 template <bool WAVE> static __device__ __forceinline__ void unit_sync() {

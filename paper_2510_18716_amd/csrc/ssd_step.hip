@@ -497,6 +497,7 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
     if (n_move <= 0) return;
     if (one_old) {                                        // n_move == 1: it is that row, and e_idx >= 0 unless the heavy slots are not full yet
         const int to = ev_heavy ? e_idx : t_m;
+        wave_store_order();                               // the evicted row's lane has just stored its score where lane 0 is about to store
         if (lane < 2 * LPR) *reinterpret_cast<uint4 *>((lane < LPR ? u.K : u.V) + (size_t)to * t_row_bytes + (size_t)sub * 16u) = pre_row;
         const unsigned long long c0 = __shfl(my_key[0], t_m & 63), c1 = __shfl(my_key[1], t_m & 63);
         const unsigned long long key = t_m < 64 ? c0 : c1;
