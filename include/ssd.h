@@ -258,6 +258,10 @@ int ssd_compress_kv(ssd_cache *cache, int layer_begin, int layer_end,
  *   n_units   : >= 1;  n_src : 1 .. 4096 (as ssd_compress_kv);  d : 64 or 128
  *   dtype     : ssd_dtype;  softmax_scale : 0 selects 1/sqrt(d)
  *   score_out : dev float [n_units, n_src], overwritten
+ * Q and K must give finite logits; the library does not check this.  A logit
+ * that is NaN counts as masked in prompts of more than 128 tokens; in shorter
+ * ones it makes the score of every key that its query attends to NaN, and may
+ * do so to the unit's other keys.  Other units keep their scores.
  * The products run on the matrix cores with fp32 accumulation; the sum over i
  * is taken in a fixed order (bit-reproducible).
  */
@@ -284,8 +288,10 @@ int ssd_cfg_mix(const void *p, int n_seqs, int V, int dtype, float gamma, float 
  * mode of ssd_compress_kv, with their results: the same kept sets, outputs
  * and scores equal to the rounding of the fp32 sums (the new token enters the
  * softmax from registers as the last term of its sum, not at its slot).  Each (sequence, head)
- * is handled by one wavefront from append to selection, so the three steps
- * of Algorithm 1 cost one pass over the head's rows.
+ * is handled by one wavefront from append to selection -- in small launches
+ * and in launches of a few long heads beside many short ones two or four share
+ * its rows, and the first of them carries on to the selection -- so the three
+ * steps of Algorithm 1 cost one pass over the head's rows.
  *   q, k_new, v_new, out : dev [layer_end - layer_begin, B, H, d], cache dtype
  * Errors as for the three separate calls (overflow is checked first and
  * leaves every layer unchanged).
@@ -397,7 +403,11 @@ int ssd_cache_export(ssd_cache *cache, int layer, int32_t *pos, int32_t *count,
  *              both NULL to skip.  Visual rows start at vis_start; w is the
  *              recency window of the metric (the paper uses 32).
  *   workspace : dev scratch of at least ssd_dense_workspace_bytes(B, H, d, n) bytes,
- *               256-byte aligned (partial results of the split over rows)
+ *               256-byte aligned: the partial results of the split over rows.
+ *               n < 256 or B * H >= 8192 is one split and needs none.  Every
+ *               other shape is refused without it, also where the launch it
+ *               takes keeps the partial results in LDS (most with B * H >= 256):
+ *               what a call must bring follows from its shape alone
  */
 size_t ssd_dense_workspace_bytes(int B, int H, int d, int n);
 int ssd_dense_decode_attn(const void *q, const void *K, const void *V, void *out,
@@ -414,12 +424,13 @@ int ssd_dense_decode_attn(const void *q, const void *K, const void *V, void *out
  * its own copy until the process ends).  The call allocates nothing and frees nothing.
  *   - The device of `stream` must be the calling thread's current device (the scratch is looked up per device,
  *     once, at the first call on that device).
- *   - A shape whose partial results (B * H * splits * (4 + d) floats, splits as ssd_dense_decode_attn picks them)
- *     exceed the scratch is refused with SSD_ERR_INVALID_ARG before anything is enqueued; B * H >= 8192 needs no
- *     scratch at all.
- *   - All calls on one GPU share that GPU's scratch and leave their partial results in it: two calls that may
- *     run at the same time on one GPU (different streams, different threads) race and must not be made; calls
- *     on one stream are ordered and safe.  Nothing in it has to start at zero.
+ *   - A shape whose partial results (B * H * splits * (4 + d) floats, where splits is the smallest of
+ *     ceil(8192 / (B * H)), n / 128 and 64, but at least 1) exceed the scratch is refused with
+ *     SSD_ERR_INVALID_ARG before anything is enqueued, also where the launch it would take keeps them in LDS; one
+ *     split (n < 256 or B * H >= 8192) needs no scratch at all.
+ *   - All calls on one GPU share that GPU's scratch and may leave their partial results in it: two calls that may
+ *     run at the same time on one GPU (different streams, different threads) race and must not be made, whatever
+ *     launches they would take; calls on one stream are ordered and safe.  Nothing in it has to start at zero.
  */
 #define SSD_DENSE_STATIC_SCRATCH_BYTES (8u << 20)
 int ssd_dense_decode_attn_static(const void *q, const void *K, const void *V, void *out,

@@ -290,6 +290,8 @@ static int dense_run(const void *q, const void *K, const void *V, void *out, int
     a.qscale = (softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)d)) * LOG2E;
     a.ws = static_cast<float *>(workspace);
     if (a.splits > 1) {
+        // by the shape alone, also where dense_shared_kernel takes it and leaves it untouched: what a caller has to bring and
+        // what is refused must not change with the dispatch below
         const size_t need = (size_t)a.n_units * a.splits * (4 + d) * sizeof(float);
         if (static_scratch) {
             if (need > SCRATCH_BYTES)

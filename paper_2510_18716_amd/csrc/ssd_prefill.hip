@@ -7,10 +7,10 @@
 //
 // This is the one step of the path that is a dense contraction (an n x n x d product per unit), so
 // it runs on the matrix cores: 32 x 32 output tiles of Q K^T with v_mfma_f32_32x32x16_bf16 (bf16
-// inputs, 8 k-values per lane and step) or v_mfma_f32_32x32x2_f32 (fp32 inputs).  Both operands
-// are read straight from their row-major [n, d] layout: lane l supplies row (l mod 32) and the
-// k-slice selected by (l div 32), the same slice for Q and K, so no transpose or LDS staging is
-// needed.  A tile's 32 x 32 results sit 16 per lane: column = l mod 32, row = 8*(v/4) + 4*(l/32) + v%4.
+// inputs, 8 k-values per lane and step) or v_mfma_f32_32x32x2_f32 (fp32 inputs).  Both operands keep their
+// row-major [n, d] layout on the way, from memory or through LDS: lane l supplies row (l mod 32) and the k-slice
+// selected by (l div 32), the same slice for Q and K, so nothing is transposed.
+// A tile's 32 x 32 results sit 16 per lane: column = l mod 32, row = 8*(v/4) + 4*(l/32) + v%4.
 //
 // One workgroup per unit at a time.
 // Prompts of up to 128 tokens (one block per wave; the case the decode path's prompts fall in): the workgroup

@@ -107,6 +107,21 @@ def test_prefill_scores_long_prompts_take_a_logit_that_is_no_number_as_masked(dt
     assert float(got[0, 37]) == 0.0 and float(got[0, n - 1]) == 0.0
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [40, 64, 128])
+def test_prefill_scores_short_prompts_pass_a_logit_that_is_no_number_on(dtype, n):
+    """Up to 128 tokens a query with such a logit makes the score of every key it attends to NaN; another unit keeps its own."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(n)
+    q, k = (torch.randn((2, n, 64), generator=g).to(tdt) for _ in range(2))
+    q[0, 20, 3] = float("nan")
+    out = torch.empty((2, n), device="cuda")
+    ssd.ssd_prefill_scores(q.cuda(), k.cuda(), 2, n, 64, dtype, out)
+    got = out.cpu()
+    assert bool(torch.isnan(got[0, :21]).all())
+    _check_scores(got[1].numpy(), oracle.prefill_scores(q[1].float().numpy(), k[1].float().numpy(), 0.125), "the other unit")
+
+
 def test_prefill_scores_bit_reproducible():
     g = torch.Generator().manual_seed(5)
     q = torch.randn((40, 200, 128), generator=g).to(torch.bfloat16).cuda()

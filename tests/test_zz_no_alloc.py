@@ -42,9 +42,10 @@ def _both(B, H, d, dtype, n_cap, n, seed, vis_start, w):
 
 @pytest.mark.gpu
 def test_static_scratch_entry_point_equals_the_workspace_entry_point_on_two_calls_in_a_row():
-    # first call: 256 units in 5 row splits (2.7 MB of the scratch in use); second call: a smaller input, 24 units
-    # in 2 splits, which finds the first call's partial results still in the scratch; third: one split, no scratch
-    shapes = [(8, 32, 128, "bf16", 700, 640, 64, 32), (4, 6, 64, "f32", 300, 257, 9, 32), (2, 3, 128, "bf16", 70, 67, 0, 16)]
+    # first call: 240 units in 5 row splits (0.63 MB of the scratch in use); second call: a smaller input, 24 units
+    # in 2 splits, which finds the first call's partial results still in the scratch; third: one split, no scratch; last:
+    # 256 units in 5 splits, whose partial results meet in LDS
+    shapes = [(8, 30, 128, "bf16", 700, 640, 64, 32), (4, 6, 64, "f32", 300, 257, 9, 32), (2, 3, 128, "bf16", 70, 67, 0, 16), (8, 32, 128, "bf16", 700, 640, 64, 32)]
     for i, (B, H, d, dtype, n_cap, n, vis_start, w) in enumerate(shapes):
         (o_s, f_s, t_s), (o_w, f_w, t_w), (q, K, V) = _both(B, H, d, dtype, n_cap, n, 100 + i, vis_start, w)
         assert np.array_equal(o_s, o_w), ("outputs differ", i, float(np.abs(o_s - o_w).max()))
