@@ -2,8 +2,8 @@
 // the threshold rule of Eq. (3).
 //
 // One workgroup per (layer, head).  Each thread sums the ratios far/tot of a fixed, strided subset of the P*T terms; the
-// partial sums are added over each wave in registers and over the waves in order, so the result does not depend on
-// scheduling and is bit-reproducible.  Offline: not on the per-token path.
+// partial sums are added in 64 bits, over each wave in registers and over the waves in order, so the result does not
+// depend on scheduling and is bit-reproducible.  Offline: not on the per-token path.
 // Bound: HBM, every term's two floats are read once (2 x 35 MB at the 7B shape with 16 profiled sequences).  A thread
 // takes its terms UNROLL pieces at a time, all 2 * UNROLL loads in flight together, the pieces counted through the P
 // rows of T terms as one run; a piece is four terms where T is a multiple of four (at any float's address: the same sums in
@@ -28,11 +28,23 @@ template <int VEC> static __device__ __forceinline__ Piece<VEC> load_piece(const
     return r;
 }
 
-// first: the head of workgroup 0 (a launch holds at most 2^32 threads)
+// Sum over the 64 lanes of a wave, in registers; every lane gets it.
+static __device__ __forceinline__ double as_f64(unsigned long long v) { return __longlong_as_double((long long)v); }
+static __device__ __forceinline__ double wave_sum_f64(double x) {
+    auto bits = [](double v) { return (unsigned long long)__double_as_longlong(v); };
+    x += as_f64(dpp_u64<0xB1>(bits(x)));       // quad_perm [1,0,3,2]
+    x += as_f64(dpp_u64<0x4E>(bits(x)));       // quad_perm [2,3,0,1]
+    x += as_f64(dpp_u64<0x141>(bits(x)));      // row_half_mirror
+    x += as_f64(dpp_u64<0x140>(bits(x)));      // row_mirror: 16 lanes done
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+}
+
+// first: the head of workgroup 0 (a launch holds at most 2^32 threads); inv: 1 / (P * T)
 template <int VEC, int THREADS, int UNROLL>
 __global__ __launch_bounds__(THREADS) void classify_kernel(const float *__restrict__ far, const float *__restrict__ tot, int first,
-                                                           int P, int H, int T, float tau, float *s_out, uint8_t *type_out) {
-    __shared__ float part[THREADS / 64];
+                                                           int P, int H, int T, double inv, float tau, float *s_out, uint8_t *type_out) {
+    __shared__ double part[THREADS / 64];
     const int head = first + (int)blockIdx.x;
     const int l = head / H, h = head % H;
     const int tid = threadIdx.x;
@@ -64,19 +76,18 @@ __global__ __launch_bounds__(THREADS) void classify_kernel(const float *__restri
 #pragma unroll
             for (int e = 0; e < VEC; ++e) acc[e] += in[k] && den[k].v[e] > 0.f ? num[k].v[e] / den[k].v[e] : 0.f;
     }
-    float mine = acc[0];
+    // a thread's few terms are summed in fp32, everything beyond in 64 bits
+    double mine = acc[0];
 #pragma unroll
-    for (int e = 1; e < VEC; ++e) mine += acc[e];
-    // over the wave in registers, over the waves through LDS
-    float half0, half1;
-    halves_pair(group_sum<32>(mine), half0, half1);
-    if ((tid & 63) == 0) part[tid >> 6] = half0 + half1;
+    for (int e = 1; e < VEC; ++e) mine += (double)acc[e];
+    mine = wave_sum_f64(mine);
+    if ((tid & 63) == 0) part[tid >> 6] = mine;
     __syncthreads();
     if (tid == 0) {
-        float sum = part[0];
+        double sum = part[0];
 #pragma unroll
         for (int w = 1; w < THREADS / 64; ++w) sum += part[w];
-        const float s = sum / ((float)P * (float)T);
+        const float s = (float)(sum * inv);
         if (s_out) s_out[head] = s;
         if (type_out) type_out[head] = s > tau ? SSD_SEMANTIC : SSD_SPATIAL;
     }
@@ -85,7 +96,8 @@ __global__ __launch_bounds__(THREADS) void classify_kernel(const float *__restri
 // Pieces per head up to which a workgroup is 256 threads with one piece each in flight.  With more, 512 threads with four:
 // 64 heads of 2304 pieces 7.0 -> 4.7 us, 960 heads 13.4 and 13.8, 4096 heads 49 -> 45.  With fewer, four pieces are requested
 // in vain and half the waves have nothing to do: 960 heads of 16 pieces 3.2 us against 3.9, of 576 5.8 against 7.0; 1280 heads of 16
-// 3.5 against 4.7; 32768 heads of 16 23 against 59, of 576 87 against 146.
+// 3.5 against 4.7; 32768 heads of 16 23 against 59, of 576 87 against 146.  (All with the waves' sums in fp32; in 64 bits each
+// takes 0.1 to 0.2 us more, 32768 heads 2.5, and the error against 64 bits falls from 5e-8 to the result's own rounding, 2.3e-8.)
 static constexpr int LITTLE = 1024;
 
 template <int VEC, int THREADS, int UNROLL>
@@ -93,7 +105,7 @@ static hipError_t launch_classify(const float *far, const float *tot, int heads,
     constexpr int MOST = (int)(0xffffffffu / THREADS);     // workgroups of one launch
     for (int first = 0; first < heads; first += MOST) {
         const int n = heads - first < MOST ? heads - first : MOST;
-        hipLaunchKernelGGL((classify_kernel<VEC, THREADS, UNROLL>), dim3((unsigned)n), dim3(THREADS), 0, s, far, tot, first, P, H, T, tau, s_out, type_out);
+        hipLaunchKernelGGL((classify_kernel<VEC, THREADS, UNROLL>), dim3((unsigned)n), dim3(THREADS), 0, s, far, tot, first, P, H, T, 1.0 / ((double)P * T), tau, s_out, type_out);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || heads - first <= MOST) return e;
     }

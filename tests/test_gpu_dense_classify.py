@@ -284,6 +284,21 @@ def test_classify_around_the_line_between_its_two_shapes(P, T):
     assert torch.equal(s, again)
 
 
+@pytest.mark.parametrize("P,T", [(1, 576), (16, 576), (16, 575), (8, 2400)])
+def test_classify_rounds_once(P, T):
+    """The error of 960 results against 64 bits is that of their own rounding to fp32 (2.4e-8 of the value, root mean square, over
+    evenly spread mantissas); a thread's fp32 sums of some five terms each add little, and nothing is summed in fp32 beyond."""
+    say("classify", P, T)
+    L, H = 30, 32
+    g = torch.Generator(device="cuda").manual_seed(P + T)
+    tot = 0.2 + 0.8 * torch.rand((L, P, H, T), generator=g, device="cuda")
+    far = tot * torch.rand((L, 1, H, 1), generator=g, device="cuda") * torch.rand((L, P, H, T), generator=g, device="cuda")
+    s, ty = torch.empty((L, H), device="cuda"), torch.empty((L, H), dtype=torch.uint8, device="cuda")
+    ssd.ssd_classify_heads(far, tot, L, P, H, T, 0.25, s, ty)
+    ref = (far.double() / tot.double()).mean(dim=(1, 3))
+    assert float((s.double() - ref).norm() / ref.norm()) < 3.5e-8
+
+
 def test_classify_more_heads_than_one_launch_holds():
     """A launch holds 2^32 threads: 8388607 workgroups of 512, 16777215 of 256."""
     L, H = 131073, 128
