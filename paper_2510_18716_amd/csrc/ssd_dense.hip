@@ -93,6 +93,10 @@ template <typename T, int D, int CH, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void dense_shared_kernel(DenseArgs a) {
     constexpr int VEC = Elem<T>::VEC;
     constexpr int LPR = D / VEC;
+    // Sums start anew every 64 rows: whatever rows a wave takes, the error of fp32 sums stays below what two launches with a split per 128
+    // rows have (256 units of 4096 rows, fp32, against 64 bits: 3.2e-7 there, 4.0e-7 here without the folds, 3.0e-7 with them, at the
+    // same time)
+    constexpr int FOLD = 64 / (CH * (64 / LPR));
     __shared__ float part[WAVES][4 + D];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -107,7 +111,7 @@ __global__ __launch_bounds__(WAVES * 64) void dense_shared_kernel(DenseArgs a) {
     Softmax<VEC> sm;
     sm.init();
     if (r_begin < r_end)
-        stream_rows<T, D, CH, false, true, NoHook, false>(Kb, Vb, a.row_bytes, sg, r_begin, r_end, 0, 1, q, a.qscale, sm, nullptr, a.vis_start, a.far_last);
+        stream_rows<T, D, CH, false, true, NoHook, false, LAST_IN_LOOP, FOLD>(Kb, Vb, a.row_bytes, sg, r_begin, r_end, 0, 1, q, a.qscale, sm, nullptr, a.vis_start, a.far_last);
     merge_groups<VEC, LPR, true>(sm);
     if (lane == 0) { part[wave][0] = sm.m; part[wave][1] = sm.l; part[wave][2] = sm.far; part[wave][3] = sm.tot; }
     if (lane < LPR) {
@@ -178,20 +182,20 @@ static int pick_splits(int units, int n) {
 // Just above one and two workgroups per compute unit some units have a workgroup more than the others, and the launch lasts as
 // long as they do; smaller workgroups even that out (bf16, d = 128, us):
 //   units of rows   two launches   2 waves   4 waves   8 waves
-//   264 of 1500         41.4         53.3      40.5      46.2
-//   352 of  640         25.1         25.7      21.5      22.9
-//   384 of 1500         58.1         56.5      48.5      49.7
-//   448 of  520         25.5         23.7      22.9      21.6
-//   528 of 1500         71.9         65.0      75.8      72.3
-//   640 of 1000         58.6         52.0      55.1      53.9
-//   704 of  640         44.2         36.8      37.8      36.4
-// Up to 31 units above a multiple of 256 with long rows the two launches stay: their pieces are smaller still (fp32, d = 128, 272
-// of 1500: 73.7, 78.3 with 4 waves; 784 of 2368: 301, 310 with 2, 313 with 8).
+//   264 of 1500         41.7         54.4      40.2      46.4
+//   352 of  640         25.9         26.1      21.5      22.9
+//   384 of 1500         58.0         57.7      48.6      50.0
+//   448 of  520         24.8         23.8      22.3      21.8
+//   528 of 1500         72.8         65.5      77.3      73.3
+//   640 of 1000         58.7         52.0      55.4      53.3
+//   704 of  640         45.5         38.3      38.2      36.8
+// Up to 31 units above a multiple of 256 with long rows the two launches stay: their pieces are smaller still (fp32, d = 128: 272
+// of 1500 73.8, with 4 waves 77.8; 784 of 2368 302, with 2 or 8 waves 313).
 static int pick_shared(int units, int n, int row_bytes, int splits) {
     if (units < 256 || splits < 2) return 0;
     if (units > 512 && units <= 640) return 2;
     const int over = units % 256;
-    if (over > 0 && over < 32 && (long long)n * row_bytes >= 700000) return 0;      // 272 of 1000 (512 kB): 28.8 in four waves, 29.2 in two launches
+    if (over > 0 && over < 32 && (long long)n * row_bytes >= 700000) return 0;      // 272 of 1000 in bf16 (256 kB): 28.8 with 4 waves, 29.5 in two launches
     if (units > 256 && units <= 384) return 4;
     return n >= 512 && splits >= 4 ? 8 : splits >= 3 ? 4 : 2;
 }

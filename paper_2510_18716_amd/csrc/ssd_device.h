@@ -230,7 +230,9 @@ struct NoHook { __device__ __forceinline__ void operator()() const {} };
 //                 the second copy of the arithmetic costs more than the request (16384 units of 16 rows 28.8 us, 30.2 with
 //                 LAST_OF_ONE; 8192 of 64 45.7 and 46.7).
 enum { LAST_IN_LOOP, LAST_OF_ONE, LAST_OUTSIDE };
-template <typename T, int D, int CH, bool ZBUF, bool MASS, typename Hook = NoHook, bool PAD = true, int LAST = LAST_IN_LOOP>
+// FOLD: chunks after which the running sums are added to a second set and start again at zero (0: never), so that the rounding
+// of a sum over many rows is that of FOLD chunks' rows plus that of the few folds (without PAD).
+template <typename T, int D, int CH, bool ZBUF, bool MASS, typename Hook = NoHook, bool PAD = true, int LAST = LAST_IN_LOOP, int FOLD = 0>
 static __device__ __forceinline__ void stream_rows(const char *__restrict__ Kb, const char *__restrict__ Vb,
                                                   int row_bytes, const Segs &sg, int row_begin, int row_end,
                                                   int first_iter, int iter_stride,
@@ -303,6 +305,22 @@ static __device__ __forceinline__ void stream_rows(const char *__restrict__ Kb, 
         sm.m = m_new;
     };
 
+    Softmax<VEC> total;
+    int left = FOLD;
+    // sm.m never falls, so the second set is the one to rescale
+    auto fold = [&]() {
+        const float f = fast_exp2(total.m - sm.m);
+        total.l = fmaf(total.l, f, sm.l);
+        if (MASS) { total.far = fmaf(total.far, f, sm.far); total.tot = fmaf(total.tot, f, sm.tot); }
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) total.acc[e] = fmaf(total.acc[e], f, sm.acc[e]);
+        total.m = sm.m;
+        sm.init();
+        sm.m = total.m;
+        left = FOLD;
+    };
+    if (FOLD > 0) total.init();
+
     int it = first_iter;
     if (it >= n_iter) { after_first_issue(); return; }
     uint4 ka[CH], va[CH], kb[CH], vb[CH];
@@ -325,6 +343,7 @@ static __device__ __forceinline__ void stream_rows(const char *__restrict__ Kb, 
     if constexpr (PAD && LAST == LAST_OF_ONE) {
         if (it + chunk_iters >= n_iter) { compute(it, ka, va); return; }
     }
+    static_assert(FOLD == 0 || (!PAD && FOLD % 2 == 0), "folds happen every second chunk at most, in the loop below");
     for (;;) {                                     // PAD: the chunk after the last one is requested too (clamped) and dropped
         if (PAD || it + chunk_iters < n_iter) load(it + chunk_iters, kb, vb);
         compute(it, ka, va);
@@ -334,6 +353,11 @@ static __device__ __forceinline__ void stream_rows(const char *__restrict__ Kb, 
         compute(it, kb, vb);
         it += chunk_iters;
         if (it >= n_iter) break;
+        if (FOLD > 0 && (left -= 2) <= 0) fold();  // wave-uniform
+    }
+    if (FOLD > 0) {
+        fold();
+        sm = total;
     }
 }
 
