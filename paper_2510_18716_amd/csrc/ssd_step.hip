@@ -356,10 +356,15 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
     };
     // (one unit per workgroup: up to 2048 units, a wave each, and launches whose logits and selection scratch leave LDS for no more)
     constexpr int LAST = SHARE > 1 || (FUSED && WPB > 1) ? LAST_OF_ONE : WPB == 1 ? LAST_OUTSIDE : LAST_IN_LOOP;
+    // The attention alone gets the row size as a constant: the 64-bit multiply-add that a variable becomes reads a register it does
+    // not need, the allocator put a score still on its way there, and the first chunk was waited for before the second was
+    // requested (128 fp32 units of 24 and 178 to 205 rows, append and attention of a token: 11.2 us, now 10.9).  The fused step has no
+    // such wait and loses by the shift (512 units of 66 rows 7.1 -> 7.35 us; 7B shape, two streams: 731 -> 740 us per step).
+    const int row_bytes = FUSED ? a.g.row_bytes : D * (int)sizeof(T);
     if (want_z)
-        stream_rows<T, D, CH, true, false, decltype(after_first_issue), true, LAST>(u.K, u.V, a.g.row_bytes, sg, 0, sg.total, part, SHARE, q, a.qscale, sm, zbuf, 0, 0, after_first_issue);
+        stream_rows<T, D, CH, true, false, decltype(after_first_issue), true, LAST>(u.K, u.V, row_bytes, sg, 0, sg.total, part, SHARE, q, a.qscale, sm, zbuf, 0, 0, after_first_issue);
     else
-        stream_rows<T, D, CH, false, false, decltype(after_first_issue), true, LAST>(u.K, u.V, a.g.row_bytes, sg, 0, sg.total, part, SHARE, q, a.qscale, sm, nullptr, 0, 0, after_first_issue);
+        stream_rows<T, D, CH, false, false, decltype(after_first_issue), true, LAST>(u.K, u.V, row_bytes, sg, 0, sg.total, part, SHARE, q, a.qscale, sm, nullptr, 0, 0, after_first_issue);
     if (FUSED && part == 0) {
         // The new token, from the registers it was loaded into, is folded into lane group 0's softmax as
         // one more row (index sg.total).
