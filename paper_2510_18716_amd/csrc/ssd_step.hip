@@ -314,7 +314,7 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
     // is not the new token (one_old), its oldest row.  Fetched with the scores it is in registers when the selection has
     // decided; read only then, its round trip to memory ends the launch whenever one unit of it promotes (7B shape, two
     // streams: 742 -> 737 us per step).  Units of few rows feel the row more than the wait: 3072 units of 17 rows 9.07 -> 9.4
-    // us, from 32 rows or 8192 units on it gains.  The attention alone never compresses and does without (106 -> 96 registers).
+    // us, from 32 rows or 8192 units on it gains.  The attention alone never compresses and does without (106 -> 93 registers).
     const bool one_old = FUSED && compress && t_c - t_R == 1 && t_R > 0;
     uint4 pre_row = make_uint4(0, 0, 0, 0);               // lanes 0..LPR-1: the K row, LPR..2*LPR-1: the V row (LPR <= 32)
 
