@@ -291,8 +291,8 @@ __global__ __launch_bounds__(64 * KT) void prefill_scores_short_kernel(PrefillAr
 // maxima, 16 multiply-adds and 16 adds, sweep 2 16 exponentials and 32 multiply-adds: 300 cycles of a SIMD each,
 // beside 256 of its matrix core (d = 128, bf16).  Keeping a whole row's exponentials instead of taking them twice
 // would need 192 KB of registers per 32 queries at 1500 tokens.  Measured at 256 units of 1500 tokens (bf16, d = 128):
-// 839 -> 195 us (counters: vector ALUs 44 % busy, matrix cores 31 %; the rest is the waves of a SIMD waiting for each
-// other at the stages' barriers).  One wave per query block with all operands read from memory in fragment layout,
+// 839 -> 195 us (counters: of the cycles its waves are resident the vector ALUs are busy in 50 %, the matrix cores in 35 %; the
+// rest is the waves of a SIMD waiting for each other at the stages' barriers).  One wave per query block with all operands read from memory in fragment layout,
 // which is what the 839 us were, touched 32 rows per load.  Tried on this form, no faster: 16 waves of one tile, 12 of
 // two, stages of 128 rows, three stages with the next fragments read ahead, held tiles brought in through LDS, and
 // one logarithm of the sum per query in place of maximum and 1 / sum (which doubles the error against 64 bits).
