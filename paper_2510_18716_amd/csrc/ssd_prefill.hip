@@ -20,9 +20,8 @@
 // while working on the current one.  This form is bound by HBM: at n = 64, d = 128 a unit does 1 MFLOP on 32 KB,
 // and what used to hold it back was the softmax bookkeeping on the vector ALUs (about 1100 instructions per
 // wave with the queries along the registers, about 400 now), not the matrix cores or the memory.
-// Longer prompts take two sweeps over the tiles on or below the diagonal -- the rows' maxima and sums, then the
-// column sums -- in which one operand stays in registers and the other streams through LDS
-// (prefill_scores_long_kernel).  Nothing is added across waves but in a fixed order (bit-reproducible, no atomics).
+// Longer prompts take two sweeps over the tiles on or below the diagonal -- the rows' sums, then the column sums -- in
+// which one operand stays in registers and the other streams through LDS (prefill_scores_long_kernel).  Nothing is added across waves but in a fixed order (bit-reproducible, no atomics).
 #include <cmath>
 #include <type_traits>
 
@@ -65,6 +64,7 @@ struct PrefillArgs {
     int n;
     int row_bytes;
     float qscale;        // softmax scale * log2(e)
+    int cut[5];          // long prompts: workgroup y of a unit takes the keys of tiles [cut[y], cut[y + 1])
 };
 
 static __device__ __forceinline__ void write_scores(const PrefillArgs &a, const float *colsum, int waves, int unit) {
@@ -277,228 +277,348 @@ __global__ __launch_bounds__(64 * KT) void prefill_scores_short_kernel(PrefillAr
 
 // ---- prompts of more than 128 tokens ----------------------------------------------------------------------------
 //
-// Two sweeps over the 32 x 32 tiles on or below the diagonal, the same loop with the operands' roles exchanged:
-//   sweep 1, K Q^T: queries stay, keys stream.  A lane pair (l, l + 32) owns one query, the tile's keys lie along
-//            its registers: running maximum and sum of a query never leave the lane until one exchange at the end.
-//   sweep 2, Q K^T: keys stay, queries stream.  A lane pair owns one key, the tile's queries lie along its
-//            registers: the key's column sum never leaves the lane until one exchange at the end; the queries'
-//            maxima and 1 / sums come from LDS as broadcasts.
-// The operand that stays sits in registers (NS tiles per wave, fragment layout); the one that streams passes through
-// LDS, STAGE rows at a time, fetched once per workgroup with coalesced loads a stage ahead and read by every wave, so a
-// wave reads a streamed fragment once for its NS tiles.  A workgroup holds WAVES * NS tiles at a time and its waves
-// pair tile w with tile WAVES * NS - 1 - w, so all of them meet the diagonal after the same amount of work.
-// What bounds it: the vector ALUs' share.  Per tile and lane sweep 1 takes 16 exponentials (8 cycles each), 8 three-way
-// maxima, 16 multiply-adds and 16 adds, sweep 2 16 exponentials and 32 multiply-adds: 300 cycles of a SIMD each,
-// beside 256 of its matrix core (d = 128, bf16).  Keeping a whole row's exponentials instead of taking them twice
-// would need 192 KB of registers per 32 queries at 1500 tokens.  Measured at 256 units of 1500 tokens (bf16, d = 128):
-// 839 -> 195 us (counters: of the cycles its waves are resident the vector ALUs are busy in 50 %, the matrix cores in 35 %; the
-// rest is the waves of a SIMD waiting for each other at the stages' barriers).  One wave per query block with all operands read from memory in fragment layout,
-// which is what the 839 us were, touched 32 rows per load.  Tried on this form, no faster: 16 waves of one tile, 12 of
-// two, stages of 128 rows, three stages with the next fragments read ahead, held tiles brought in through LDS, and
-// one logarithm of the sum per query in place of maximum and 1 / sum (which doubles the error against 64 bits).
+// Two sweeps over the 32 x 32 tiles on or below the diagonal, both taken as K Q^T: a lane has two queries of a tile and eight of
+// its keys for each, so a query lies in the four lanes l, l + 16, l + 32, l + 48.
+//   sweep 1: queries stay, keys stream.  A query's sum of exponentials never leaves its lanes until one exchange at the end.
+//   sweep 2: keys stay, queries stream.  Every lane adds up its own queries' probabilities, key by key; the 16 lanes of a key
+//            meet every eight tiles.  A streamed query's maximum and 1 / sum are two registers of its lane.
+// The operand that stays sits in registers (NS tiles per wave, fragment layout); the one that streams passes through LDS, a
+// stage of up to four tiles (32 KB) at a time in two buffers, requested from memory straight into LDS while the stage before
+// it is worked on, across the ends of groups and of sweeps as well.  Fragment f of 16 bytes of row r sits at f ^ r (low bits),
+// so that the 16 rows that one pass of a 16-byte LDS access reads hit the 64 banks exactly once.
+//
+// The reference that a query's exponentials are taken against is the largest logit of its first streamed tile and stays: a
+// maximum per tile, the rescaling and the chain through both are a fifth of the vector ALUs' work.  A later logit may
+// exceed it by up to 100 powers of two without a loss (fp32 keeps its relative precision); where one does by more, or is not a
+// number, the group of held tiles is taken again with a maximum and a test per tile (CAREFUL).
+//
+// What bounds it: a 32 x 32 x 128 product takes a SIMD 256 cycles of its matrix core and 16 exponentials (8 cycles each), 16
+// multiply-adds and 16 adds per lane, 260 cycles of its vector ALUs, beside each other where two waves alternate.  The loop by
+// itself, with random data, takes 200 ns per product: what a large bf16 matrix product takes on this card, which clocks lower
+// under such loads (160 ns with zeros).  256 units of 1500 tokens (bf16, d = 128): 839 us with all operands read from memory in
+// fragment layout, 195 with 32 x 32 products and column sums that crossed lanes per tile (whose LDS reads and barriers the
+// waves spent half their time on), 163 now; of these 113 are the loop, the rest groups' beginnings (a held tile's loads touch a row
+// per lane) and diagonals (waves that have less to do wait).  Error against 64 bits 4.3e-8 -> 3.6e-8 (n = 256: 4.7e-8 both).
+// Few units: up to 128 leave half of the compute units idle, so two or three workgroups share a unit's keys; each goes through sweep 1
+// for the queries that see any of its keys, so the gain is less than their number (32 units of 1500 tokens: 168 -> 141 us in one
+// piece, 120 in two, 105 in three; four 105).
+// More than 256 units: four waves per workgroup, two workgroups on a compute unit fill each other's waits and no round is left half empty
+// (300 units of 1500 tokens: 354 us before, 307 with eight waves, 293 with four; 512 of 640: 103, 87, 80).
+// NS = 3 where it takes a group less than NS = 2 (256 units of 640 tokens 51.0 and 45.2 us, of 1000 90.8 and 92.2).
+template <int ROW> static constexpr int long_stage_tiles() { return 1024 / ROW < 4 ? 1024 / ROW : 4; }
+
 static __device__ __forceinline__ void arrived(uint4 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
-static __device__ __forceinline__ void arrived(float &v) { asm volatile("" : "+v"(v)); }
 
-template <typename T> struct LongShape;
-template <> struct LongShape<bf16_t> { static constexpr int NS = 2, STAGE = 64; };
-template <> struct LongShape<float> { static constexpr int NS = 1, STAGE = 32; };      // (fp32 fragments take twice the registers and LDS)
+// Products of 16 x 16 with 32 bf16 (16x16x32) or 4 x 4 fp32 (16x16x4) k-values per 16-byte fragment: lane l supplies row l mod 16 of its
+// operand and the k-slice of its fragment, l / 16 of four; results: column l mod 16, rows 4 (l / 16) .. + 3.  Not the 32 x 32 forms: a
+// chain of those that starts anew (addend zero) with other operands costs 170 to 190 ns per 32 x 32 x 128 where it
+// should be 110 (two waves per SIMD; 16 x 16: 110, and 130 for 190 with random data, which the card clocks lower).
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+template <typename T> static __device__ __forceinline__ f32x4_t mma_fragment(const uint4 &a, const uint4 &b, f32x4_t c);
+template <> __device__ __forceinline__ f32x4_t mma_fragment<bf16_t>(const uint4 &a, const uint4 &b, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+template <> __device__ __forceinline__ f32x4_t mma_fragment<float>(const uint4 &a, const uint4 &b, f32x4_t c) {
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+}
 
-template <typename T, int D, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void prefill_scores_long_kernel(PrefillArgs a) {
-    typedef typename Mma<T>::Frag Frag;
-    constexpr int NK = D / Mma<T>::KSTEP;
-    constexpr int NS = LongShape<T>::NS, STAGE = LongShape<T>::STAGE;
+// Sums over the 16 lanes of a row: lane l ends up with the sum of x[u], u = 4 bit3(l) + 2 bit2(l) + bit0(l).  The steps in which a
+// rounding is one of a whole sum are taken in double.
+template <int CTRL> static __device__ __forceinline__ double dpp_d(double v) {
+    return __longlong_as_double((long long)dpp_u64<CTRL>((unsigned long long)__double_as_longlong(v)));
+}
+static __device__ __forceinline__ double sums_over_16_lanes(const float (&x)[8], int lane) {
+    float y[4];
+    double r[2];
+    const bool b3 = (lane & 8) != 0, b2 = (lane & 4) != 0, b0 = (lane & 1) != 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) y[u] = (b3 ? x[u + 4] : x[u]) + dpp_f<0x128>(b3 ? x[u] : x[u + 4]);         // row_ror:8
+#pragma unroll
+    for (int u = 0; u < 2; ++u) r[u] = (double)(b2 ? y[u + 2] : y[u]) + (double)dpp_f<0x141>(b2 ? y[u] : y[u + 2]);      // row_half_mirror
+    const double q = (b0 ? r[1] : r[0]) + dpp_d<0xB1>(b0 ? r[0] : r[1]);                                    // quad_perm [1,0,3,2]
+    return q + dpp_d<0x4E>(q);                                                                              // quad_perm [2,3,0,1]
+}
+
+template <typename T, int D, int WAVES, int NS>
+__global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill_scores_long_kernel(PrefillArgs a) {
+    constexpr bool AHEAD = sizeof(T) == 2 && NS < 4 && WAVES <= 8;         // fragments a tile ahead (registers: fp32 fragments take twice as many)
     constexpr int ROW = D * (int)sizeof(T);
-    constexpr int STRIDE = ROW + 16;                       // conflict-free both ways, as in the short kernel
-    constexpr int FPR = ROW / 16;
-    constexpr int THREADS = 64 * WAVES;
-    constexpr int NF = STAGE * FPR / THREADS;              // 16-byte fragments per thread and stage
-    static_assert(NF * THREADS == STAGE * FPR, "a stage divides evenly over the workgroup");
+    constexpr int FPR = ROW / 16;                          // 16-byte fragments per row
+    constexpr int NK = FPR / 4;                            // ... per lane and 16 rows of an operand's tile
+    constexpr int ST = long_stage_tiles<ROW>();
+    constexpr int STAGE_BYTES = ST * 32 * ROW;
+    static_assert(STAGE_BYTES % 1024 == 0 && 64 % FPR == 0, "a stage is brought in by wave-wide transfers of whole rows");
     constexpr int HELD = WAVES * NS;                       // tiles the workgroup holds at a time
+    constexpr float LARGE = 1.2676506e30f;                 // 2^100
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int half = lane >> 5;
-    const int l32 = lane & 31;
+    const int l16 = lane & 15, quarter = lane >> 4;
     const int n = a.n;
     const int n_tiles = (n + 31) / 32;
-    float *row_max = reinterpret_cast<float *>(lds_raw + 2 * STAGE * STRIDE);        // [n_tiles * 32]
-    float *row_inv = row_max + n_tiles * 32;                                         // 1 / sum; 0 for queries beyond n
+    float2 *stat = reinterpret_cast<float2 *>(lds_raw + 2 * STAGE_BYTES);           // [n_tiles * 32]: maximum (or reference) and 1 / sum; 1 / sum = 0 beyond n
     const size_t unit_off = (size_t)blockIdx.x * (size_t)n * (size_t)ROW;
+    const char *Qu = a.Q + unit_off, *Ku = a.K + unit_off;
+    auto swizzle = [](int row) { return (FPR == 8 ? row >> 1 : row) & (FPR == 8 ? 7 : 15); };
 
-    auto sweep = [&](auto second, const char *held_base, const char *stream_base) {
-        constexpr bool COLS = decltype(second)::value;     // sweep 2
-        for (int first = 0; first < n_tiles; first += HELD) {
-            int tile[NS];
-            Frag keep[NS][NK];
+    // Where a wave's tiles lie in a group: w and HELD - 1 - w, so that all waves meet the diagonal after the same amount of work
+    // (NS == 2); counted back and forth so that the waves of a SIMD (w, w + 4, ...) also share it evenly within a stage.
+    const int place = (w & ~3) + ((w & 4) ? 3 - (w & 3) : w & 3);
+
+    // Request of one stage, from memory straight into LDS: the wave's share of transfers of 1 KB, lane i's 16 bytes to the i-th
+    // place.  Which fragment sits there is the swizzle's choice.  The compiler does not count these transfers: `landed` waits for them.
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds_raw;
+    auto request = [&](const char *base, int tile, int buf) {
+        for (int i = w; i < STAGE_BYTES / 1024; i += WAVES) {
+            const int row = i * (64 / FPR) + lane / FPR;   // of the stage
+            int r = tile * 32 + row;
+            r = r < n ? r : n - 1;                         // rows past the end repeat the last one
+            const uint32_t from = (uint32_t)r * ROW + (uint32_t)((lane % FPR) ^ swizzle(row)) * 16u;
+            const uint32_t to = __builtin_amdgcn_readfirstlane(lds_base + buf * STAGE_BYTES + i * 1024);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(to), "v"(from), "s"(base) : "memory");
+        }
+    };
+    auto landed = [&]() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); };
+    const int frag0 = l16 * ROW + (quarter ^ swizzle(l16)) * 16;                     // of a tile's first fragment, and ^ 64 ks; + 16 rows
+    auto fragments = [&](int buf, int j, uint4 (&fr)[2][NK]) {
+        const int at = buf * STAGE_BYTES + j * (32 * ROW) + frag0;
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int ks = 0; ks < NK; ++ks) fr[g][ks] = *reinterpret_cast<const uint4 *>(lds_raw + ((at ^ (ks * 64)) + g * (16 * ROW)));
+    };
+
+    // Stages in the order they are needed: of sweep 1, held tiles from `begin` on, streamed tiles 0 .. the last held one; of sweep 2,
+    // held tiles [begin, stop), streamed tiles from the first held one on.  ahead_*: the stage to request next.
+    const int begin = a.cut[blockIdx.y], stop = a.cut[blockIdx.y + 1];      // this workgroup's keys, in tiles
+    if (begin >= stop) return;
+    int ahead_sweep = 0, ahead_first = begin, ahead_tile = 0;
+    int cur = 0;                                           // LDS buffer of the stage at hand
+    auto request_next = [&](int buf) {
+        if (ahead_sweep > 1) return;
+        request(ahead_sweep ? Qu : Ku, ahead_tile, buf);
+        ahead_tile += ST;
+        if (ahead_tile >= (ahead_sweep == 0 && ahead_first + HELD < n_tiles ? ahead_first + HELD : n_tiles)) {
+            ahead_first += HELD;
+            if (ahead_first >= (ahead_sweep ? stop : n_tiles)) { ++ahead_sweep; ahead_first = begin; }
+            ahead_tile = ahead_sweep ? ahead_first : 0;
+        }
+    };
+    // One group of held tiles; its first stage is requested.  Returns false if a sum is not what the fast form can stand for.
+    auto group = [&](auto cols, auto careful, int first, int end) __attribute__((always_inline)) -> bool {
+        constexpr bool COLS = decltype(cols)::value, CAREFUL = decltype(careful)::value;
+        const char *held_base = COLS ? Ku : Qu;
+        int tile[NS];
+        uint4 keep[NS][2][NK];
+        landed();
+        __syncthreads();                                   // the first stage is in LDS (and the statistics are), the other buffer is free
+        request_next(cur ^ 1);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            tile[s] = first + s * WAVES + (s & 1 ? WAVES - 1 - place : place);
+            if (tile[s] >= end) tile[s] = n_tiles;         // none
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                int row = tile[s] * 32 + g * 16 + l16;
+                row = row < n ? row : n - 1;
+#pragma unroll
+                for (int ks = 0; ks < NK; ++ks) keep[s][g][ks] = *reinterpret_cast<const uint4 *>(held_base + (size_t)row * ROW + (4 * ks + quarter) * 16);
+            }
+        }
+        // wait for them here: left pending across the loop below, every use of them would wait for the newest request as well
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int i = 0; i < 2 * NK; ++i) arrived(keep[s][i / NK][i % NK]);
+        float ref[NS][2], sum[NS][2];                      // sweep 1: of the lane's two queries, reference (log2 domain) and sum
+        float acc[COLS ? NS : 1][8];                       // sweep 2: per key, the sum over the lane's queries of the last tiles,
+        double whole[COLS ? NS : 1];                       //   and of the lane's key over all lanes and tiles
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int g = 0; g < 2; ++g) { ref[s][g] = NEG_BIG; sum[s][g] = 0.f; }
+#pragma unroll
+        for (int s = 0; s < (COLS ? NS : 1); ++s) {
+            whole[s] = 0.;
+#pragma unroll
+            for (int v = 0; v < 8; ++v) acc[s][v] = 0.f;
+        }
+
+        const int from = COLS ? first : 0;                                            // streamed tiles [from, to)
+        const int to = COLS ? n_tiles : first + HELD < end ? first + HELD : end;
+        // One streamed tile against one held tile.  Value 8 g + 4 k + v of a lane: query 16 g + l mod 16, key 16 k + 4 (l / 16) + v.
+        auto product = [&](const uint4 (&fr)[2][NK], int s, float (&c)[16]) {
+            f32x4_t x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < NK; ++ks)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[i] = COLS ? mma_fragment<T>(keep[s][i & 1][ks], fr[i >> 1][ks], x[i]) : mma_fragment<T>(fr[i & 1][ks], keep[s][i >> 1][ks], x[i]);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) c[i] = x[i >> 2][i & 3];
+        };
+        auto absorb = [&](float (&c)[16], int t, int s, const float2 (&qs)[2]) {
+            if (t == tile[s]) {                            // the diagonal tile: masked where key > query
+#pragma unroll
+                for (int i = 0; i < 16; ++i) c[i] = ((i >> 2) & 1) * 16 + quarter * 4 + (i & 3) <= (i >> 3) * 16 + l16 ? c[i] : -INFINITY;
+            }
+            if constexpr (CAREFUL) {                       // a logit that is not a number counts as masked
+#pragma unroll
+                for (int i = 0; i < 16; ++i) c[i] = c[i] == c[i] ? c[i] : -INFINITY;
+            }
+            if constexpr (!COLS) {
+                if (CAREFUL || t == 0) {
+#pragma unroll
+                    for (int g = 0; g < 2; ++g) {
+                        float mx = c[8 * g];
+#pragma unroll
+                        for (int i = 1; i < 8; ++i) mx = __builtin_elementwise_maximum(mx, c[8 * g + i]);        // NaN if one of them is
+                        const float m_new = fmaxf(ref[s][g], mx * a.qscale);         // qscale > 0; finite also where all keys are masked
+                        sum[s][g] *= fast_exp2(ref[s][g] - m_new);
+                        ref[s][g] = m_new;
+                    }
+                }
+            }
+            // all of one kind before any of the next: an exponential's result is not there for the next instruction
+#pragma unroll
+            for (int i = 0; i < 16; ++i) c[i] = fmaf(c[i], a.qscale, COLS ? -qs[i >> 3].x : -ref[s][i >> 3]);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) c[i] = fast_exp2(c[i]);
+            if constexpr (!COLS) {
+#pragma unroll
+                for (int h = 4; h >= 1; h >>= 1)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        if ((i & 7) < h) c[i] += c[i + h];
+                sum[s][0] += c[0];
+                sum[s][1] += c[8];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[s][i & 7] = fmaf(c[i], qs[i >> 3].y, acc[s][i & 7]);
+            }
+        };
+        auto process = [&](int t, const uint4 (&fr)[2][NK], const float2 (&qs)[2]) {     // one streamed tile against the tiles this wave holds
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                tile[s] = first + (s == 0 ? w : HELD - 1 - w);
-                int row = tile[s] * 32 + l32;
-                row = row < n ? row : n - 1;               // rows past the end repeat the last one
-#pragma unroll
-                for (int ks = 0; ks < NK; ++ks) keep[s][ks] = Mma<T>::load(held_base + (size_t)row * ROW, ks, half);
+                if (!(t < to && tile[s] < n_tiles && (COLS ? t >= tile[s] : t <= tile[s]))) continue;    // above the diagonal (wave-uniform)
+                float c[16];
+                product(fr, s, c);
+                absorb(c, t, s, qs);
             }
-            // wait for them here: left pending across the loop below, every use of them would wait for the newest
-            // request as well, which is the stage ahead
+        };
+        auto stats = [&](int t, float2 (&qs)[2]) {
 #pragma unroll
-            for (int s = 0; s < NS; ++s)
-#pragma unroll
-                for (int ks = 0; ks < NK; ++ks) arrived(keep[s][ks]);
-            // sweep 1: of the lane's query, running maximum (log2 domain) and sum; sweep 2: of the lane's key, the
-            // column sum as a compensated pair (one term per tile)
-            float st0[NS], st1[NS];
-#pragma unroll
-            for (int s = 0; s < NS; ++s) { st0[s] = COLS ? 0.f : NEG_BIG; st1[s] = 0.f; }
+            for (int g = 0; g < 2; ++g) qs[g] = COLS ? stat[(t < n_tiles ? t : n_tiles - 1) * 32 + g * 16 + l16] : make_float2(0.f, 0.f);
+        };
 
-            const int from = COLS ? first * 32 : 0;                                   // streamed rows [from, to)
-            const int to = COLS ? n : (first + HELD) * 32 < n ? (first + HELD) * 32 : n;
-            u32x4_nt_t ahead[NF];
-            auto fetch = [&](int row0) {
-#pragma unroll
-                for (int i = 0; i < NF; ++i) {
-                    const int f = (int)threadIdx.x + i * THREADS;
-                    int r = row0 + f / FPR;
-                    r = r < n ? r : n - 1;
-                    ahead[i] = *reinterpret_cast<const u32x4_nt_t *>(stream_base + (size_t)r * ROW + (f % FPR) * 16);
-                }
-            };
-            auto stash = [&](int buf) {
-#pragma unroll
-                for (int i = 0; i < NF; ++i) {
-                    const int f = (int)threadIdx.x + i * THREADS;
-                    *reinterpret_cast<u32x4_nt_t *>(lds_raw + buf * (STAGE * STRIDE) + (f / FPR) * STRIDE + (f % FPR) * 16) = ahead[i];
-                }
-            };
-            auto fragments = [&](int buf, int sub, Frag (&fr)[NK]) {
-                const unsigned char *frow = lds_raw + buf * (STAGE * STRIDE) + (sub * 32 + l32) * STRIDE;
-#pragma unroll
-                for (int ks = 0; ks < NK; ++ks) fr[ks] = lds_frag<T>(frow, ks, half);
-            };
-            auto product = [&](const Frag (&fr)[NK], int s) {
-                f32x16_t c = {0.f};
-#pragma unroll
-                for (int ks = 0; ks < NK; ++ks) c = Mma<T>::mma(fr[ks], keep[s][ks], c);
-                return c;
-            };
-            // rm, ri: maxima and 1 / sums of the tile's queries, register by register (sweep 2)
-            // A logit that is not a number counts as masked; the tests for it look at one value per lane and tile.
-            auto absorb = [&](f32x16_t &c, int s, const float (&rm)[16], const float (&ri)[16]) {
-                float p0 = 0.f, p1 = 0.f;
-                auto drop_nan = [&]() {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) c[v] = c[v] == c[v] ? c[v] : -INFINITY;
-                };
-                if constexpr (!COLS) {
-                    auto tile_max = [&]() {
-                        float mx = c[0];
-#pragma unroll
-                        for (int v = 1; v < 16; ++v) mx = __builtin_elementwise_maximum(mx, c[v]);       // NaN if one of them is
-                        return mx;
-                    };
-                    float mx = tile_max();
-                    if (__any(mx != mx)) { drop_nan(); mx = tile_max(); }
-                    const float m_new = fmaxf(st0[s], mx * a.qscale);                 // qscale > 0; finite also where all keys are masked
-#pragma unroll
-                    for (int v = 0; v < 16; v += 2) {
-                        p0 += fast_exp2(fmaf(c[v], a.qscale, -m_new));
-                        p1 += fast_exp2(fmaf(c[v + 1], a.qscale, -m_new));
-                    }
-                    st1[s] = fmaf(st1[s], fast_exp2(st0[s] - m_new), p0 + p1);
-                    st0[s] = m_new;
-                } else {
-#pragma unroll
-                    for (int v = 0; v < 16; v += 2) {
-                        p0 = fmaf(fast_exp2(fmaf(c[v], a.qscale, -rm[v])), ri[v], p0);
-                        p1 = fmaf(fast_exp2(fmaf(c[v + 1], a.qscale, -rm[v + 1])), ri[v + 1], p1);
-                    }
-                    if (__any(p0 + p1 != p0 + p1)) {
-                        drop_nan();
-                        p0 = p1 = 0.f;
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) p0 = fmaf(fast_exp2(fmaf(c[v], a.qscale, -rm[v])), ri[v], p0);
-                    }
-                    // st0 + st1 += p0 + p1 without losing what st0 cannot hold (terms are not negative, so sums over
-                    // thousands of queries would otherwise drift by a rounding per tile)
-                    const float add = (p0 + p1) + st1[s];
-                    const float sum = st0[s] + add;
-                    st1[s] = add - (sum - st0[s]);
-                    st0[s] = sum;
-                }
-            };
-            auto streamed = [&](int buf, int sub, int t) {          // one streamed tile against the tiles this wave holds
-                bool on[NS], any = false;                  // on or below the diagonal (wave-uniform)
-#pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    on[s] = t < n_tiles && tile[s] < n_tiles && (COLS ? t >= tile[s] : t <= tile[s]);
-                    any = any || on[s];
-                }
-                if (!any) return;
-                Frag fr[NK];
-                fragments(buf, sub, fr);
-                float rm[16], ri[16];
-                if constexpr (COLS) {
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const float4 x = *reinterpret_cast<const float4 *>(row_max + t * 32 + 8 * g + 4 * half);
-                        const float4 y = *reinterpret_cast<const float4 *>(row_inv + t * 32 + 8 * g + 4 * half);
-                        ri[4 * g] = y.x; ri[4 * g + 1] = y.y; ri[4 * g + 2] = y.z; ri[4 * g + 3] = y.w;
-                        rm[4 * g] = x.x; rm[4 * g + 1] = x.y; rm[4 * g + 2] = x.z; rm[4 * g + 3] = x.w;
-                    }
-                }
-#pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    if (!on[s]) continue;
-                    f32x16_t c = product(fr, s);
-                    // register v of the tile is streamed row 8*(v/4) + 4*half + v%4; the diagonal tile is masked where key > query
-                    if (t == tile[s]) {
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            const int r = (v >> 2) * 8 + half * 4 + (v & 3);
-                            c[v] = (COLS ? l32 <= r : r <= l32) ? c[v] : -INFINITY;
-                        }
-                    }
-                    absorb(c, s, rm, ri);
-                }
-            };
-            fetch(from);
-            __syncthreads();                               // everybody is done with the buffers (and, sweep 2, the statistics are written)
-            stash(0);
-            int cur = 0;
-            for (int row0 = from; row0 < to; row0 += STAGE, cur ^= 1) {
+        uint4 fa[2][NK];
+        float2 qa[2];
+        for (int t0 = from; t0 < to; t0 += ST) {
+            if (t0 != from) {
+                landed();
                 __syncthreads();                           // this stage is in LDS, the other buffer is free
-                const bool more = row0 + STAGE < to;
-                if (more) fetch(row0 + STAGE);
-                for (int sub = 0; sub < STAGE / 32; ++sub) streamed(cur, sub, row0 / 32 + sub);
-                if (more) stash(cur ^ 1);
             }
+            if (t0 != from) request_next(cur ^ 1);
+            if constexpr (AHEAD) {
+                uint4 fb[2][NK];
+                float2 qb[2];
+                fragments(cur, 0, fa);
+                stats(t0, qa);
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                if (tile[s] >= n_tiles) continue;
-                const int row = tile[s] * 32 + l32;        // this lane's query or key
-                float x, y;
-                if constexpr (!COLS) {
-                    halves_pair(st0[s], x, y);
-                    const float m_row = fmaxf(x, y);
-                    halves_pair(st1[s] * fast_exp2(st0[s] - m_row), x, y);
-                    if (half == 0) {
-                        row_max[row] = m_row;
-                        row_inv[row] = row < n && x + y > 0.f ? 1.0f / (x + y) : 0.f;      // (0: every logit of the query masked)
+                for (int j = 0; j < ST; j += 2) {
+                    fragments(cur, j + 1, fb);
+                    stats(t0 + j + 1, qb);
+                    process(t0 + j, fa, qa);
+                    if (j + 2 < ST) {
+                        fragments(cur, j + 2, fa);
+                        stats(t0 + j + 2, qa);
                     }
-                } else {
-                    halves_pair(st0[s], x, y);
-                    if (half == 0 && row < n) a.score_out[(size_t)blockIdx.x * (size_t)n + row] = x + y;
+                    process(t0 + j + 1, fb, qb);
+                }
+            } else {
+#pragma unroll 1
+                for (int j = 0; j < ST; ++j) {
+                    fragments(cur, j, fa);
+                    stats(t0 + j, qa);
+                    process(t0 + j, fa, qa);
+                }
+            }
+            cur ^= 1;
+            // every eight tiles the lanes meet: a sum over all of a long prompt's tiles in one register would lose a rounding per tile
+            if (COLS && (((t0 + ST - from) & 7) == 0 || t0 + ST >= to)) {
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    if (tile[s] >= t0 + ST) continue;      // nothing added yet (wave-uniform)
+                    whole[s] += sums_over_16_lanes(acc[s], lane);
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) acc[s][v] = 0.f;
                 }
             }
         }
+        bool good = true;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (tile[s] >= n_tiles) continue;
+            if constexpr (!COLS) {
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    const float m_row = across_groups_max<16>(ref[s][g]);
+                    const float total = across_groups_sum<16>(sum[s][g] * fast_exp2(ref[s][g] - m_row));
+                    const int row = tile[s] * 32 + g * 16 + l16;
+                    good = good && total < LARGE;
+                    if (quarter == 0) stat[row] = make_float2(m_row, row < n && total > 0.f ? 1.0f / total : 0.f);       // (0: every logit of the query masked)
+                }
+            } else {
+                const int u = ((lane >> 3) & 1) * 4 + ((lane >> 2) & 1) * 2 + (lane & 1);
+                const int key = tile[s] * 32 + (u >> 2) * 16 + quarter * 4 + (u & 3);
+                good = good && whole[s] < LARGE;
+                if ((lane & 2) == 0 && key < n) a.score_out[(size_t)blockIdx.x * (size_t)n + key] = (float)whole[s];
+            }
+        }
+        return good;
     };
-    sweep(std::false_type{}, a.Q + unit_off, a.K + unit_off);
-    sweep(std::true_type{}, a.K + unit_off, a.Q + unit_off);
+    request_next(cur);
+    auto sweep = [&](auto cols, int end) {
+        constexpr bool COLS = decltype(cols)::value;
+        for (int first = begin; first < end; first += HELD) {
+            const bool good = group(cols, std::false_type{}, first, end);
+            if (__syncthreads_or(!good)) {                 // again, tile by tile with care
+                landed();                                  // what the next group's first stage has brought makes way
+                __syncthreads();
+                ahead_sweep = COLS ? 1 : 0;
+                ahead_first = first;
+                ahead_tile = COLS ? first : 0;
+                request_next(cur);
+                group(cols, std::true_type{}, first, end);
+            }
+        }
+    };
+    sweep(std::false_type{}, n_tiles);
+    sweep(std::true_type{}, stop);
+}
+
+// Where the keys' tiles [0, n_tiles) are cut so that `parts` workgroups of one unit take about equally long: part p does sweep 1
+// over the queries from cut[p] on and sweep 2 over its own keys, in tiles n^2 / 2 - cut[p]^2 / 2 and as many as lie below them.
+static void cut_long(int n_tiles, int parts, int (&cut)[5]) {
+    auto cost = [&](int from, int to) { return (long long)n_tiles * n_tiles - (long long)from * from + (long long)(n_tiles - from) * (n_tiles - from) - (long long)(n_tiles - to) * (n_tiles - to); };
+    for (long long limit = (long long)n_tiles * n_tiles;; limit += (limit >> 6) + 1) {       // the smallest limit that all parts keep, within 2 %
+        int at = 0;
+        for (int p = 0; p < parts; ++p) {
+            cut[p] = at;
+            while (at < n_tiles && cost(cut[p], at + 1) <= limit) ++at;
+        }
+        cut[parts] = n_tiles;
+        if (at >= n_tiles) return;
+    }
 }
 
 // LDS of the long kernel: two stages of the streamed operand and the queries' statistics.
-template <typename T> static size_t long_lds_bytes(int n, int row_bytes) {
-    return 2 * (size_t)LongShape<T>::STAGE * (size_t)(row_bytes + 16) + (size_t)((n + 31) / 32 * 32) * 2 * sizeof(float);
+template <int ROW> static size_t long_lds_bytes(int n) {
+    return 2 * (size_t)long_stage_tiles<ROW>() * 32 * ROW + (size_t)((n + 31) / 32 * 32) * 2 * sizeof(float);
 }
 
 // Grid of a kernel whose workgroups walk the units with a stride of the grid size: as many workgroups as are
@@ -545,7 +665,11 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
     const int waves = n_blocks < 4 ? n_blocks : 4;
     const size_t lds_short = short_lds_bytes(waves, n_src, a.row_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const dim3 grid((unsigned)n_units), block(64u * waves);
+    const dim3 block(64u * waves);
+    // long prompts (the reasons stand at the kernel): workgroups per unit, and whether a wave holds three tiles rather than two
+    const int parts = n_units <= 85 ? 3 : n_units <= 128 ? 2 : 1;
+    auto three = [&](int w) { return (n_blocks + 3 * w - 1) / (3 * w) < (n_blocks + 2 * w - 1) / (2 * w); };
+    cut_long(n_blocks, parts, a.cut);
     hipError_t attr = hipSuccess;
     // more than 64 KB of dynamic LDS has to be asked for (the longest short prompts in fp32: 70 KB of the CU's 160 KB)
 #define SSD_PREFILL_SHORT(T_, D_, KT_)                                                                                          \
@@ -560,19 +684,23 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
             else hipLaunchKernelGGL((prefill_scores_short_kernel<T_, D_, KT_>), g, block, lds_short, s, a);                     \
         }                                                                                                                       \
     } while (0)
-#define SSD_PREFILL_LONG(T_, D_, WAVES_)                                                                                         \
+#define SSD_PREFILL_LONG(T_, D_, WAVES_, NS_)                                                                                    \
     do {                                                                                                                        \
-        const void *fn = reinterpret_cast<const void *>(&prefill_scores_long_kernel<T_, D_, WAVES_>);                           \
-        const size_t lds = long_lds_bytes<T_>(n_src, a.row_bytes);                                                              \
+        const void *fn = reinterpret_cast<const void *>(&prefill_scores_long_kernel<T_, D_, WAVES_, NS_>);                      \
+        const size_t lds = long_lds_bytes<D_ * (int)sizeof(T_)>(n_src);                                                         \
         if (lds > 65536) attr = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                  \
-        if (attr == hipSuccess) hipLaunchKernelGGL((prefill_scores_long_kernel<T_, D_, WAVES_>), grid, dim3(64 * WAVES_), lds, s, a); \
+        if (attr == hipSuccess)                                                                                                 \
+            hipLaunchKernelGGL((prefill_scores_long_kernel<T_, D_, WAVES_, NS_>), dim3((unsigned)n_units, (unsigned)parts), dim3(64 * WAVES_), lds, s, a); \
     } while (0)
 #define SSD_PREFILL(T_, D_)                                                                                          \
     do {                                                                                                             \
+        constexpr bool wide = sizeof(T_) == 4;             /* fp32 fragments: one tile per wave */                   \
         if (n_blocks <= 2) SSD_PREFILL_SHORT(T_, D_, 2);                                                             \
         else if (n_blocks <= 4) SSD_PREFILL_SHORT(T_, D_, 4);                                                        \
-        else if (n_blocks <= 8) SSD_PREFILL_LONG(T_, D_, 4);                                                         \
-        else SSD_PREFILL_LONG(T_, D_, 8);                                                                            \
+        else if (n_units <= 256 && three(8)) SSD_PREFILL_LONG(T_, D_, 8, (wide ? 1 : 3));                            \
+        else if (n_units <= 256) SSD_PREFILL_LONG(T_, D_, 8, (wide ? 1 : 2));                                        \
+        else if (three(4)) SSD_PREFILL_LONG(T_, D_, 4, (wide ? 1 : 3));                                              \
+        else SSD_PREFILL_LONG(T_, D_, 4, (wide ? 1 : 2));                                                            \
     } while (0)
     if (dtype == SSD_BF16) {
         if (d == 128) SSD_PREFILL(bf16_t, 128); else SSD_PREFILL(bf16_t, 64);

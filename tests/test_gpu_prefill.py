@@ -107,6 +107,49 @@ def test_prefill_scores_long_prompts_take_a_logit_that_is_no_number_as_masked(dt
     assert float(got[0, 37]) == 0.0 and float(got[0, n - 1]) == 0.0
 
 
+def _scores_in_64_bits(q, k):
+    n = q.shape[1]
+    after = torch.ones((n, n), dtype=torch.bool, device=q.device).triu(1)
+    return torch.stack([torch.softmax((a.double() @ b.double().T / np.sqrt(q.shape[2])).masked_fill_(after, -np.inf), dim=-1).sum(dim=0)
+                        for a, b in zip(q, k)])
+
+
+@pytest.mark.parametrize("dtype,d,n", [("bf16", 128, 129), ("bf16", 64, 385), ("bf16", 128, 513), ("bf16", 128, 769), ("f32", 64, 257), ("f32", 128, 160), ("bf16", 64, 1025)])
+@pytest.mark.parametrize("units", [1, 85, 86, 128, 129, 256, 257])
+def test_prefill_scores_long_prompts_by_number_of_units(dtype, d, n, units):
+    """Where a unit's keys are shared by three, two and one workgroup and where workgroups get smaller; two and three tiles per
+    wave.  Tolerance as for the edges above."""
+    say("units", dtype, d, n, units)
+    g = torch.Generator(device="cuda").manual_seed(n + units)
+    q, k = (torch.randn((units, n, d), generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32) for _ in range(2))
+    out = torch.full((units + 1, n), -5.0, device="cuda")
+    ssd.ssd_prefill_scores(q, k, units, n, d, dtype, out)
+    at = sorted({0, units // 2, units - 1})
+    ref = _scores_in_64_bits(q[at], k[at])
+    assert bool((out[units] == -5.0).all()) and bool(torch.isfinite(out[:units]).all())
+    assert float(((out[at].double() - ref).abs() / ref.clamp_min(1e-3)).max()) < 1e-5
+    assert float((out[:units].double().sum(dim=1) / n - 1.0).abs().max()) < 1e-6     # every query gives away a mass of 1
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [200, 600, 1100])
+@pytest.mark.parametrize("rise", [20.0, 60.0, 200.0, 2000.0])
+def test_prefill_scores_long_prompts_whose_logits_rise_late(dtype, n, rise):
+    """Keys from 100 on whose logits lie 20 to 2000 above those of all before them, and from 150 on as far below again: 60 is
+    within what a query's first reference can stand for (2^100), 200 is not.  Tolerance: a logit of rise / 2 is a sum of 64 products,
+    each partial sum rounded by up to 2^-24 of it, in a probability's numerator as in its denominator."""
+    say("rise", dtype, n, rise)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, k = (0.1 * torch.randn((3, n, 64), generator=g, device="cuda") for _ in range(2))
+    q[:, :, 0], k[:, :, 0] = 16.0, -0.25 * rise
+    k[:, 100:150, 0] = 0.25 * rise
+    q, k = (x.to(torch.bfloat16 if dtype == "bf16" else torch.float32) for x in (q, k))
+    out = torch.empty((3, n), device="cuda")
+    ssd.ssd_prefill_scores(q, k, 3, n, 64, dtype, out)
+    ref = _scores_in_64_bits(q, k)
+    assert float(((out.double() - ref).abs() / ref.clamp_min(1e-3)).max()) < 64 * 2.0 ** -24 * rise
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n", [40, 64, 128])
 def test_prefill_scores_short_prompts_pass_a_logit_that_is_no_number_on(dtype, n):
