@@ -42,6 +42,7 @@ struct StepHot {
     int zcap;            // floats of LDS per wave for the logits of a semantic unit
     int wave_lds;        // bytes of LDS per wave (logits + selection scratch)
     int sem_first;       // semantic units have more rows than spatial ones: dispatch them first
+    int by_xcd;          // sequences (a multiple of 16, or none) whose units are dealt to the XCDs two sequences at a time
     int seq_off;         // first sequence of this launch (a launch may cover a part of the batch only)
     int late_new_store;  // fused append: store the new token's rows after the stream instead of at its start
     int n_att, nc;       // budgets per head: tokens the attention sees, tokens held at the last compression,
@@ -121,7 +122,7 @@ static __device__ __forceinline__ void fetch_args(int lrel, StepHot &a, LayerDes
     SSD_P(q, const char *); SSD_P(out, char *); SSD_P(k_new, const char *); SSD_P(v_new, const char *);
     a.qscale = __uint_as_float(SSD_W(offsetof(StepHot, qscale)));
     SSD_I(layer_off); SSD_I(new_slot_sp); SSD_I(new_slot_se); SSD_I(new_pos); SSD_I(accumulate); SSD_I(do_compress);
-    SSD_I(m); SSD_I(c); SSD_I(base); SSD_I(R); SSD_I(lpr); SSD_I(zcap); SSD_I(wave_lds); SSD_I(sem_first); SSD_I(seq_off);
+    SSD_I(m); SSD_I(c); SSD_I(base); SSD_I(R); SSD_I(lpr); SSD_I(zcap); SSD_I(wave_lds); SSD_I(sem_first); SSD_I(by_xcd); SSD_I(seq_off);
     SSD_I(late_new_store); SSD_I(n_att); SSD_I(nc); SSD_I(row_buffer); SSD_I(rope_layout);
     SSD_P(rope_cos, const float *); SSD_P(rope_sin, const float *);
     SSD_I(sp.start[0]); SSD_I(sp.start[1]); SSD_I(sp.start[2]); SSD_I(sp.len[0]); SSD_I(sp.len[1]); SSD_I(sp.len[2]); SSD_I(sp.total);
@@ -253,12 +254,24 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
         local = sem_unit ? sem_below : h - sem_below;
     } else {
         sem_unit = ((blockIdx.z & 1) == 0) == (a.sem_first != 0);
-        local = blockIdx.x * WPB + w;                     // index among the heads of this type in this layer
+        // Workgroups go round the eight XCDs.  With a multiple of eight of them per sequence each XCD would touch every
+        // sequence's units, and every page of the layer; dealt two whole sequences (1 MB of the 1B shape's units) at a
+        // time, an eighth.  One sequence at a time gains half as much, four as much as two; all of an XCD's sequences in one piece
+        // costs up to 2 %.  us per launch (bf16, d = 128): 512 units of 66 rows 6.45 -> 6.20, 2048 of 18 7.15 -> 6.80, 2048 of 129 to 385
+        // 34.7 -> 33.8; 4096 of 66 25.76 and 25.70.  Beside another part's launch, whose units the XCDs have to do with as well, it
+        // changes nothing or loses (7B shape on two streams 727 -> 736 us per step).
+        int x = blockIdx.x, y = blockIdx.y;
+        if (y < a.by_xcd) {                               // exchange x mod 8 with bits 1..3 of y
+            const int xcd = x & 7;
+            x = (x & ~7) | ((y >> 1) & 7);
+            y = (y & ~15) | (xcd << 1) | (y & 1);
+        }
+        local = x * WPB + w;                              // index among the heads of this type in this layer
         if (local >= (sem_unit ? ld.n_se : ld.n_sp)) return;
         const uint64_t m0 = sem_unit ? ld.sem_mask[0] : ~ld.sem_mask[0];
         const uint64_t m1 = sem_unit ? ld.sem_mask[1] : ~ld.sem_mask[1];
         h = kth_set_bit(m0, m1, local);                   // spatial heads: bits above H are never reached (local < n_sp)
-        seq = a.seq_off + blockIdx.y;
+        seq = a.seq_off + y;
     }
     const int rem = seq * a.g.H + h;
     const UnitRef u = unit_ref_local(a.g, ld, seq, sem_unit, local);
@@ -671,11 +684,13 @@ static hipError_t launch_step(StepArgs &full, const HeadOrder *ho, const LaunchS
     a.wave_lds = (int)(((size_t)a.zcap * 4 + (a.do_compress ? select_lds_bytes(M, n_cand, n_old) + 16 : 0) + 15) / 16 * 16);
     while (wpb > 1 && wpb < 10 && (size_t)wpb * a.wave_lds > 60000) wpb >>= 1;
     const size_t lds = (size_t)wpb * a.wave_lds;
+    const int type_groups = wpb > 10 ? max_type_heads : (max_type_heads + wpb - 1) / wpb;                  // workgroups per sequence and type
+    a.by_xcd = !heads && !concurrent && type_groups % 8 == 0 ? B & ~15 : 0;
     *used = LaunchShape{ch, wpb, a.late_new_store ? 2 : 1};
     const dim3 blocks = heads ? dim3((unsigned)RANK_GROUPS, (unsigned)B, (unsigned)(((H + wpb - 1) / wpb + RANK_GROUPS - 1) / RANK_GROUPS))   // rank order, see the kernel
-                              : dim3((unsigned)((max_type_heads + wpb - 1) / wpb), (unsigned)B, (unsigned)(2 * layers));
+                              : dim3((unsigned)type_groups, (unsigned)B, (unsigned)(2 * layers));
     // wpb codes 12 and 14: one unit per workgroup, shared by 2 or 4 waves
-#define SSD_SHARED(CH_, SHARE_) if (ch == CH_ && wpb == 10 + SHARE_) { launch_variant<T, D, CH_, 1, SHARE_>(full, ho, heads ? dim3((unsigned)RANK_GROUPS, (unsigned)B, (unsigned)((H + RANK_GROUPS - 1) / RANK_GROUPS)) : dim3((unsigned)max_type_heads, (unsigned)B, (unsigned)(2 * layers)), (size_t)a.wave_lds + SHARE_ * (2 + D) * sizeof(float), layers, fused, s); return hipGetLastError(); }
+#define SSD_SHARED(CH_, SHARE_) if (ch == CH_ && wpb == 10 + SHARE_) { launch_variant<T, D, CH_, 1, SHARE_>(full, ho, heads ? dim3((unsigned)RANK_GROUPS, (unsigned)B, (unsigned)((H + RANK_GROUPS - 1) / RANK_GROUPS)) : blocks, (size_t)a.wave_lds + SHARE_ * (2 + D) * sizeof(float), layers, fused, s); return hipGetLastError(); }
     SSD_SHARED(2, 2) SSD_SHARED(4, 2) SSD_SHARED(2, 4) SSD_SHARED(4, 4) SSD_SHARED(5, 4)
 #undef SSD_SHARED
 #define SSD_CASE(CH_, WPB_) if (ch == CH_ && wpb == WPB_) { launch_variant<T, D, CH_, WPB_, 1>(full, ho, blocks, lds, layers, fused, s); return hipGetLastError(); }

@@ -541,6 +541,17 @@ def test_selection_with_few_evictions_among_many_candidates(fused):
         _full_compare(wl, fused=fused, export_every=1)
 
 
+@pytest.mark.parametrize("prompts,H,frac,rows,lpc", [(8, 16, 0.5, 9, 1), (9, 16, 0.5, 40, 1), (19, 32, 0.25, 33, 1), (19, 16, 0.5, 20, None), (7, 16, 0.5, 9, 1),
+                                                     (43, 64, 0.5, 9, 1), (66, 32, 0.75, 12, None)])
+def test_units_dealt_to_the_xcds(prompts, H, frac, rows, lpc):
+    """A multiple of eight workgroups per sequence and head type: whole blocks of 16 sequences are dealt two at a time, the rest and
+    fewer as they come; one and four units per workgroup, one layer and several per call."""
+    wl = workload.Workload("dealt-%d-%d" % (prompts, H), L=2, prompts=prompts, H=H, d=128, dtype="bf16", n0=rows, grid_h=2, grid_w=5, W=rows, M=rows - 1,
+                           S=1, R=1, C=2, cadence=1, seed=900 + prompts, plain=True, spatial_frac=frac)
+    for fused in (False, True):
+        _full_compare(wl, lpc=lpc, k_units=48, export_every=4, device_gen=True, fused=fused)
+
+
 def test_determinism_same_inputs_same_bits():
     wl = workload.config(2).replace(name="cfg2-determinism", L=2, prompts=4, grid_h=6)
     ht = workload.head_map(wl)
