@@ -541,6 +541,18 @@ def test_selection_with_few_evictions_among_many_candidates(fused):
         _full_compare(wl, fused=fused, export_every=1)
 
 
+@pytest.mark.parametrize("dtype,d,M,R,heads", [("f32", 64, 126, 1, False), ("bf16", 128, 127, 1, False), ("f32", 64, 128, 1, False), ("bf16", 128, 128, 0, False),
+                                               ("f32", 128, 129, 2, False), ("bf16", 64, 191, 1, False), ("f32", 64, 192, 0, False),
+                                               ("bf16", 128, 321, 1, False), ("f32", 64, 200, 1, True), ("bf16", 128, 128, 0, True)])
+def test_one_eviction_among_any_number_of_candidates(dtype, d, M, R, heads):
+    """Compression after every token evicts one of M + 1, settled in registers however many there are: around 64, 128, 192 and
+    320 candidates, with the new token among them (R = 0) and not, and with heads of fewer than M."""
+    own = [[5, M, max(1, M - 70), M // 2], [5, M // 2, M, M - 1]] if heads else None
+    wl = workload.Workload("one-eviction-M%d-R%d" % (M, R), L=2, prompts=1, H=4, d=d, dtype=dtype, n0=M - 6, grid_h=4, grid_w=6, W=5 if not heads else M,
+                           M=M, S=1, R=R, C=R + 1, cadence=1, seed=700 + M, plain=True, spatial_frac=0.25, head_budget=own)
+    _full_compare(wl, fused=True, lpc=1, export_every=1)
+
+
 @pytest.mark.parametrize("prompts,H,frac,rows,lpc", [(8, 16, 0.5, 9, 1), (9, 16, 0.5, 40, 1), (19, 32, 0.25, 33, 1), (19, 16, 0.5, 20, None), (7, 16, 0.5, 9, 1),
                                                      (43, 64, 0.5, 9, 1), (66, 32, 0.75, 12, None)])
 def test_units_dealt_to_the_xcds(prompts, H, frac, rows, lpc):
