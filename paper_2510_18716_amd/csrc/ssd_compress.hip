@@ -55,6 +55,7 @@ template <int LAYERS, bool HEADS> struct DenseSrcArgs {
     int n_src;
     int R;
     int lpr;
+    int dealt;              // units (a multiple of 512, or none) that go to the XCDs 64 neighbours at a time
     HeadsOf<HEADS> ht;      // budgets per head
 };
 
@@ -156,7 +157,8 @@ __global__ __launch_bounds__(THREADS, THREADS == 1024 ? 8 : 1) void compress_den
     __shared__ unsigned long long keys[RANK ? THREADS : 1], share[RANK ? 1 : 2 * WAVES];
     __shared__ int hist[RANK ? 1 : 260], count[KPT * WAVES];
     const int BH = a.g.B * a.g.H;
-    const int unit = blockIdx.x;
+    int unit = blockIdx.x;                                    // workgroups go round the eight XCDs: dealt, an XCD has 1 MB of neighbouring units
+    if (unit < a.dealt) unit = (unit & ~511) + ((unit & 7) << 6) + ((unit >> 3) & 63);
     const int lrel = LAYERS == 1 ? 0 : unit / BH;
     const int rem = LAYERS == 1 ? unit : unit % BH;
     const UnitRef u = unit_ref(a.g, a.lm.layer[lrel], rem / a.g.H, rem % a.g.H);
@@ -315,6 +317,10 @@ static hipError_t launch_dense_source(const ssd_cache *cache, int lb, int le, in
     // with 73 registers).  More units: room for no more candidates than there may be (2048 units of 1024 tokens 51.8 us with 8 per
     // thread, 58.3 with 16).
     const dim3 grid(units);
+    // Many units of few rows: with neighbours on one XCD each XCD meets an eighth of the source's pages (scores and compression together,
+    // 4096 units of 64 tokens 59.2 -> 56.5 us, of 120 129.6 -> 128.2, 2880 of 64 44.7 -> 43.9).  Longer units have pages to
+    // themselves (2048 of 1024 tokens 742 and 759), and fewer gain nothing (2048 of 96 49.3 both, 768 of 200 47.3 and 48.0).
+    a.dealt = units >= 2560 && (size_t)n_src * a.g.row_bytes <= 32768 ? (int)(units & ~511u) : 0;
     if (n_cand <= 256 && (n_src <= 256 || n_cand > cache->Ml[lb])) hipLaunchKernelGGL((compress_dense_kernel<256, 1, LAYERS, HEADS>), grid, dim3(256), lds, s, a);
     else if (units <= 512) hipLaunchKernelGGL((compress_dense_kernel<1024, 4, LAYERS, HEADS>), grid, dim3(1024), lds, s, a);
     else if (n_cand <= 2048) hipLaunchKernelGGL((compress_dense_kernel<256, 8, LAYERS, HEADS>), grid, dim3(256), lds, s, a);

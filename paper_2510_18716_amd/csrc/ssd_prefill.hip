@@ -155,7 +155,8 @@ static __device__ __forceinline__ int column_sum_key_row(int lane) {       // th
 // A workgroup takes units blockIdx.x, blockIdx.x + gridDim.x, ... (the grid is sized to what the chip holds at
 // once): the next unit's rows are requested as soon as this unit's have left the registers for LDS, so the
 // memory pipe stays busy while the matrix cores and the softmax arithmetic work on the current unit.
-template <typename T, int D, int KT>
+// KEEP: K is read like what will be needed again (when, and why, stands at the launch).
+template <typename T, int D, int KT, bool KEEP>
 __global__ __launch_bounds__(64 * KT) void prefill_scores_short_kernel(PrefillArgs a) {
     typedef typename Mma<T>::Frag Frag;
     constexpr int NK = D / Mma<T>::KSTEP;
@@ -193,7 +194,8 @@ __global__ __launch_bounds__(64 * KT) void prefill_scores_short_kernel(PrefillAr
         for (int i = 0; i < NF; ++i) {
             int f = (int)threadIdx.x + i * step;
             f = f < n_frag ? f : n_frag - 1;
-            kv[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt_t *>(Ku + (size_t)f * 16));
+            const u32x4_nt_t *p = reinterpret_cast<const u32x4_nt_t *>(Ku + (size_t)f * 16);
+            kv[i] = KEEP ? *p : __builtin_nontemporal_load(p);
         }
     };
     const u32x4_nt_t zero = {0u, 0u, 0u, 0u};
@@ -661,6 +663,11 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
     a.n = n_src;
     a.row_bytes = d * (dtype == SSD_F32 ? 4 : 2);
     a.qscale = (softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)d)) * LOG2E;
+    // Short prompts: a prompt's compression follows and reads K again.  Without the non-temporal hint K stays in the memory-side cache.
+    // Scores and compression together, us: 4096 units of 64 tokens 61.0 -> 59.2, of 120 143.6 -> 129.6, 2880 of 64 45.4 -> 44.7; without
+    // the hint on Q as well 61.3 and 131.4.  Where K about fits the L2s the hint on both is better (512 units of 64 tokens 13.95 and
+    // 14.33, 2048 of 64 33.3 and 33.7).
+    const bool keep_k = (size_t)n_units * (size_t)n_src * (size_t)a.row_bytes >= ((size_t)40 << 20);
     const int n_blocks = (n_src + 31) / 32;
     const int waves = n_blocks < 4 ? n_blocks : 4;
     const size_t lds_short = short_lds_bytes(waves, n_src, a.row_bytes);
@@ -672,17 +679,21 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
     cut_long(n_blocks, parts, a.cut);
     hipError_t attr = hipSuccess;
     // more than 64 KB of dynamic LDS has to be asked for (the longest short prompts in fp32: 70 KB of the CU's 160 KB)
-#define SSD_PREFILL_SHORT(T_, D_, KT_)                                                                                          \
+#define SSD_PREFILL_SHORT_AS(T_, D_, KT_, KEEP_)                                                                                \
     do {                                                                                                                        \
-        const void *fn = reinterpret_cast<const void *>(&prefill_scores_short_kernel<T_, D_, KT_>);                             \
+        const void *fn = reinterpret_cast<const void *>(&prefill_scores_short_kernel<T_, D_, KT_, KEEP_>);                      \
         if (lds_short > 65536) attr = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_short);      \
         int per_cu = 0;                                                                                                         \
         if (attr == hipSuccess) attr = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, (int)block.x, lds_short);      \
         if (attr == hipSuccess) {                                                                                               \
             const dim3 g = resident_grid(n_units, per_cu);                                                                      \
             if (g.x == 0) attr = hipErrorInvalidValue;                                                                          \
-            else hipLaunchKernelGGL((prefill_scores_short_kernel<T_, D_, KT_>), g, block, lds_short, s, a);                     \
+            else hipLaunchKernelGGL((prefill_scores_short_kernel<T_, D_, KT_, KEEP_>), g, block, lds_short, s, a);              \
         }                                                                                                                       \
+    } while (0)
+#define SSD_PREFILL_SHORT(T_, D_, KT_)                                                                                          \
+    do {                                                                                                                        \
+        if (keep_k) SSD_PREFILL_SHORT_AS(T_, D_, KT_, true); else SSD_PREFILL_SHORT_AS(T_, D_, KT_, false);                     \
     } while (0)
 #define SSD_PREFILL_LONG(T_, D_, WAVES_, NS_)                                                                                    \
     do {                                                                                                                        \
@@ -710,6 +721,7 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
 #undef SSD_PREFILL
 #undef SSD_PREFILL_LONG
 #undef SSD_PREFILL_SHORT
+#undef SSD_PREFILL_SHORT_AS
     if (attr != hipSuccess) return hip_fail(attr, "prefill score kernel attribute");
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "prefill score launch");
