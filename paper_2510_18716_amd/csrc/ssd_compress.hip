@@ -127,7 +127,7 @@ static __device__ __forceinline__ void store_once(char *p, const uint4 &v) {
 // trip per fragment.  Neither side is touched again by this launch, so both carry the non-temporal hint.
 // Bound: HBM, rows read and written once.  7B shape, 4096 units, 64 source tokens, 41 kept on average (172 MB): 42.8 us
 // with single fragments, 38 with batches of four (two: 42), 35 with the stores non-temporal as well (4.9 TB/s, what a plain copy
-// reaches; loads without the hint: 75).  256 units of 1500 tokens, 320 kept by the semantic half: 154 us with
+// reaches; loads without the hint: 75), 30 where the scoring kernel has left K in the memory-side cache and units are dealt to the XCDs.  256 units of 1500 tokens, 320 kept by the semantic half: 154 us with
 // single fragments and ranks by counting, 19.8 now.
 template <int THREADS, int BATCH, typename Map>
 static __device__ __forceinline__ void copy_fragments(int n_frag, int tid, Map map) {
