@@ -289,10 +289,15 @@ __global__ __launch_bounds__(64 * KT) void prefill_scores_short_kernel(PrefillAr
 // it is worked on, across the ends of groups and of sweeps as well.  Fragment f of 16 bytes of row r sits at f ^ r (low bits),
 // so that the 16 rows that one pass of a 16-byte LDS access reads hit the 64 banks exactly once.
 //
-// The reference that a query's exponentials are taken against is the largest logit of its first streamed tile and stays: a
-// maximum per tile, the rescaling and the chain through both are a fifth of the vector ALUs' work.  A later logit may
-// exceed it by up to 100 powers of two without a loss (fp32 keeps its relative precision); where one does by more, or is not a
-// number, the group of held tiles is taken again with a maximum and a test per tile (CAREFUL).
+// The reference that a query's exponentials are taken against is the largest logit of its first streamed tile, one for the four lanes
+// that share the query, and stays while it can: a maximum per tile, the rescaling and the chain through both are a fifth of the vector
+// ALUs' work.  Logits above it cost precision -- an argument x of an exponential is rounded to 2^-24 x, where against a running maximum
+// the heavy terms' arguments stay near zero -- so a tile that would bring a lane's sum to 2^20 or makes it no number is taken again with
+// the reference renewed.  Error against 64 bits over a running maximum's (fp32 and bf16, 200 to 1500 tokens): logits that rise
+// by 2^16 to 2^28 0.98 on average and 1.12 at most, by 2^40 to 2^90 0.99 and 1.08; with that line at 2^100 1.01 and 1.13, 1.06 and 1.23.
+// 256 units of 1500 tokens, logits that rise by 2^24: 169 us, 166 where nothing rises (164 without the test); taking whole groups of
+// held tiles again 271.  (The lanes' sums are of one scale: with a reference per lane, a lane whose first keys lie 2^126 below the
+// others' would lose what it has added up since.)
 //
 // What bounds it: a 32 x 32 x 128 product takes a SIMD 256 cycles of its matrix core and 16 exponentials (8 cycles each), 16
 // multiply-adds and 16 adds per lane, 260 cycles of its vector ALUs, beside each other where two waves alternate.  The loop by
@@ -354,7 +359,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
     constexpr int STAGE_BYTES = ST * 32 * ROW;
     static_assert(STAGE_BYTES % 1024 == 0 && 64 % FPR == 0, "a stage is brought in by wave-wide transfers of whole rows");
     constexpr int HELD = WAVES * NS;                       // tiles the workgroup holds at a time
-    constexpr float LARGE = 1.2676506e30f;                 // 2^100
+    constexpr float LARGE = 1048576.f;                     // 2^20, see above
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -409,7 +414,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
             ahead_tile = ahead_sweep ? ahead_first : 0;
         }
     };
-    // One group of held tiles; its first stage is requested.  Returns false if a sum is not what the fast form can stand for.
+    // One group of held tiles; its first stage is requested.  Returns false if a column sum is not a number (CAREFUL: never).
     auto group = [&](auto cols, auto careful, int first, int end) __attribute__((always_inline)) -> bool {
         constexpr bool COLS = decltype(cols)::value, CAREFUL = decltype(careful)::value;
         const char *held_base = COLS ? Ku : Qu;
@@ -463,53 +468,80 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
 #pragma unroll
             for (int i = 0; i < 16; ++i) c[i] = x[i >> 2][i & 3];
         };
-        auto absorb = [&](float (&c)[16], int t, int s, const float2 (&qs)[2]) {
-            if (t == tile[s]) {                            // the diagonal tile: masked where key > query
+        auto mask = [&](float (&c)[16], int t, int s) {     // the diagonal tile: masked where key > query
+            if (t == tile[s]) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) c[i] = ((i >> 2) & 1) * 16 + quarter * 4 + (i & 3) <= (i >> 3) * 16 + l16 ? c[i] : -INFINITY;
             }
-            if constexpr (CAREFUL) {                       // a logit that is not a number counts as masked
+        };
+        auto drop_nan = [&](float (&c)[16]) {               // a logit that is not a number counts as masked
 #pragma unroll
-                for (int i = 0; i < 16; ++i) c[i] = c[i] == c[i] ? c[i] : -INFINITY;
-            }
-            if constexpr (!COLS) {
-                if (CAREFUL || t == 0) {
+            for (int i = 0; i < 16; ++i) c[i] = c[i] == c[i] ? c[i] : -INFINITY;
+        };
+        // all of one kind before any of the next: an exponential's result is not there for the next instruction
+        auto exponentials = [&](float (&c)[16], float m0, float m1) {
 #pragma unroll
-                    for (int g = 0; g < 2; ++g) {
-                        float mx = c[8 * g];
-#pragma unroll
-                        for (int i = 1; i < 8; ++i) mx = __builtin_elementwise_maximum(mx, c[8 * g + i]);        // NaN if one of them is
-                        const float m_new = fmaxf(ref[s][g], mx * a.qscale);         // qscale > 0; finite also where all keys are masked
-                        sum[s][g] *= fast_exp2(ref[s][g] - m_new);
-                        ref[s][g] = m_new;
-                    }
-                }
-            }
-            // all of one kind before any of the next: an exponential's result is not there for the next instruction
-#pragma unroll
-            for (int i = 0; i < 16; ++i) c[i] = fmaf(c[i], a.qscale, COLS ? -qs[i >> 3].x : -ref[s][i >> 3]);
+            for (int i = 0; i < 16; ++i) c[i] = fmaf(c[i], a.qscale, i < 8 ? -m0 : -m1);
 #pragma unroll
             for (int i = 0; i < 16; ++i) c[i] = fast_exp2(c[i]);
-            if constexpr (!COLS) {
+        };
+        auto row_sums = [&](float (&c)[16]) {               // into c[0] and c[8]
 #pragma unroll
-                for (int h = 4; h >= 1; h >>= 1)
+            for (int h = 4; h >= 1; h >>= 1)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        if ((i & 7) < h) c[i] += c[i + h];
-                sum[s][0] += c[0];
-                sum[s][1] += c[8];
-            } else {
+                for (int i = 0; i < 16; ++i)
+                    if ((i & 7) < h) c[i] += c[i + h];
+        };
+        // A tile of sweep 1 with the queries' references renewed: the first one, and one that the references cannot stand for.
+        auto renew = [&](const uint4 (&fr)[2][NK], int t, int s) {
+            float c[16];
+            product(fr, s, c);
+            mask(c, t, s);
+            drop_nan(c);
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[s][i & 7] = fmaf(c[i], qs[i >> 3].y, acc[s][i & 7]);
+            for (int g = 0; g < 2; ++g) {
+                float mx = c[8 * g];
+#pragma unroll
+                for (int i = 1; i < 8; ++i) mx = fmaxf(mx, c[8 * g + i]);
+                const float m_new = fmaxf(ref[s][g], across_groups_max<16>(mx) * a.qscale);      // qscale > 0; finite also where all keys are masked
+                sum[s][g] *= fast_exp2(ref[s][g] - m_new);
+                ref[s][g] = m_new;
             }
+            exponentials(c, ref[s][0], ref[s][1]);
+            row_sums(c);
+            sum[s][0] += c[0];
+            sum[s][1] += c[8];
         };
         auto process = [&](int t, const uint4 (&fr)[2][NK], const float2 (&qs)[2]) {     // one streamed tile against the tiles this wave holds
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 if (!(t < to && tile[s] < n_tiles && (COLS ? t >= tile[s] : t <= tile[s]))) continue;    // above the diagonal (wave-uniform)
-                float c[16];
-                product(fr, s, c);
-                absorb(c, t, s, qs);
+                if constexpr (COLS) {
+                    float c[16];
+                    product(fr, s, c);
+                    mask(c, t, s);
+                    if constexpr (CAREFUL) drop_nan(c);
+                    exponentials(c, qs[0].x, qs[1].x);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[s][i & 7] = fmaf(c[i], qs[i >> 3].y, acc[s][i & 7]);
+                } else {
+                    float sum0 = LARGE, sum1 = LARGE;
+                    if (t != 0) {
+                        float c[16];
+                        product(fr, s, c);
+                        mask(c, t, s);
+                        exponentials(c, ref[s][0], ref[s][1]);
+                        row_sums(c);
+                        sum0 = sum[s][0] + c[0];
+                        sum1 = sum[s][1] + c[8];
+                    }
+                    if (__any(!(__builtin_elementwise_maximum(sum0, sum1) < LARGE))) {     // (NaN if one of them is)
+                        renew(fr, t, s);
+                    } else {
+                        sum[s][0] = sum0;
+                        sum[s][1] = sum1;
+                    }
+                }
             }
         };
         auto stats = [&](int t, float2 (&qs)[2]) {
@@ -571,13 +603,12 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
                     const float m_row = across_groups_max<16>(ref[s][g]);
                     const float total = across_groups_sum<16>(sum[s][g] * fast_exp2(ref[s][g] - m_row));
                     const int row = tile[s] * 32 + g * 16 + l16;
-                    good = good && total < LARGE;
                     if (quarter == 0) stat[row] = make_float2(m_row, row < n && total > 0.f ? 1.0f / total : 0.f);       // (0: every logit of the query masked)
                 }
             } else {
                 const int u = ((lane >> 3) & 1) * 4 + ((lane >> 2) & 1) * 2 + (lane & 1);
                 const int key = tile[s] * 32 + (u >> 2) * 16 + quarter * 4 + (u & 3);
-                good = good && whole[s] < LARGE;
+                good = good && whole[s] == whole[s];
                 if ((lane & 2) == 0 && key < n) a.score_out[(size_t)blockIdx.x * (size_t)n + key] = (float)whole[s];
             }
         }
@@ -588,14 +619,15 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
         constexpr bool COLS = decltype(cols)::value;
         for (int first = begin; first < end; first += HELD) {
             const bool good = group(cols, std::false_type{}, first, end);
-            if (__syncthreads_or(!good)) {                 // again, tile by tile with care
-                landed();                                  // what the next group's first stage has brought makes way
-                __syncthreads();
-                ahead_sweep = COLS ? 1 : 0;
-                ahead_first = first;
-                ahead_tile = COLS ? first : 0;
-                request_next(cur);
-                group(cols, std::true_type{}, first, end);
+            if constexpr (COLS) {
+                if (__syncthreads_or(!good)) {             // again, with a test per logit
+                    landed();                              // what the next group's first stage has brought makes way
+                    __syncthreads();
+                    ahead_sweep = 1;
+                    ahead_first = ahead_tile = first;
+                    request_next(cur);
+                    group(cols, std::true_type{}, first, end);
+                }
             }
         }
     };

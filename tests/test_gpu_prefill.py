@@ -135,8 +135,8 @@ def test_prefill_scores_long_prompts_by_number_of_units(dtype, d, n, units):
 @pytest.mark.parametrize("n", [200, 600, 1100])
 @pytest.mark.parametrize("rise", [20.0, 60.0, 200.0, 2000.0])
 def test_prefill_scores_long_prompts_whose_logits_rise_late(dtype, n, rise):
-    """Keys from 100 on whose logits lie 20 to 2000 above those of all before them, and from 150 on as far below again: 60 is
-    within what a query's first reference can stand for (2^100), 200 is not.  Tolerance: a logit of rise / 2 is a sum of 64 products,
+    """Keys from 100 on whose logits lie 20 to 2000 above those of all before them, and from 150 on as far below again: more than a
+    query's first reference can stand for, and more than fp32 holds at all.  Tolerance: a logit of rise / 2 is a sum of 64 products,
     each partial sum rounded by up to 2^-24 of it, in a probability's numerator as in its denominator."""
     say("rise", dtype, n, rise)
     g = torch.Generator(device="cuda").manual_seed(n)
@@ -148,6 +148,59 @@ def test_prefill_scores_long_prompts_whose_logits_rise_late(dtype, n, rise):
     ssd.ssd_prefill_scores(q, k, 3, n, 64, dtype, out)
     ref = _scores_in_64_bits(q, k)
     assert float(((out.double() - ref).abs() / ref.clamp_min(1e-3)).max()) < 64 * 2.0 ** -24 * rise
+
+
+def _scores_of_given_logits(z, dtype):
+    """z [units, n]: the logit (log2 domain) every query of a unit gives key j, exact in fp32.  The kernel's scores and those in 64 bits."""
+    units, n = z.shape
+    q = torch.zeros((units, n, 64), device="cuda")
+    k = torch.zeros((units, n, 64), device="cuda")
+    rest = z.clone()
+    for i in range(3):                                            # three bf16 pieces hold the 24 bits
+        q[:, :, i] = 1.0
+        k[:, :, i] = rest.to(torch.bfloat16).float()
+        rest = rest - k[:, :, i]
+    assert not bool(rest.any())
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    out = torch.empty((units, n), device="cuda")
+    ssd.ssd_prefill_scores(q.to(tdt), k.to(tdt), units, n, 64, dtype, out, float(np.log(2.0)))
+    after = torch.arange(n, device="cuda")
+    ref = torch.empty((units, n), dtype=torch.float64, device="cuda")
+    for u in range(units):
+        p = torch.where(after[None, :] <= after[:, None], z[u].double()[None, :], torch.tensor(-np.inf, dtype=torch.float64, device="cuda"))
+        ref[u] = torch.softmax(p * np.log(2.0), dim=-1).sum(dim=0)
+    return out.double(), ref
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("low", [-127.0, -126.25, -130.0, -60.0])
+@pytest.mark.parametrize("key", [36, 41, 46, 96])
+def test_prefill_scores_long_prompts_two_keys_far_above_all_others(dtype, low, key):
+    """Key 0 and one later key, of this or that lane, share every query's mass; all others lie up to 2^130 below.  Tolerance: the probabilities
+    are exact halves and the others' sums below 2^-50, so only sums over up to 300 queries are rounded."""
+    z = torch.full((2, 300), low, device="cuda")
+    z[:, 0] = 0.0
+    z[0, key] = 0.0
+    got, ref = _scores_of_given_logits(z, dtype)
+    say("two keys", dtype, low, key, got[0, [0, key]].tolist())
+    assert float(((got - ref).abs() / ref.clamp_min(1e-3)).max()) < 1e-6
+    assert float((got.sum(dim=1) / 300 - 1.0).abs().max()) < 1e-6
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [200, 600])
+@pytest.mark.parametrize("rise", [12, 19, 24, 60, 90, 99])
+def test_prefill_scores_long_prompts_lose_no_precision_to_a_late_rise(dtype, n, rise):
+    """From key 100 on logits, each known exactly, spread over one power of two that lies `rise` above the first ones.  A query's sum
+    stays below 2^20 or is taken again with a running maximum, so an exponential's argument is below 2^5 and rounded by up to
+    2^-20: 3.8e-7 rms of its probability, and as much in the sum it is divided by; with arguments of 60 to 100 it would be 2^-18."""
+    g = torch.Generator(device="cuda").manual_seed(n + rise)
+    z = torch.floor(torch.rand((3, n), generator=g, device="cuda") * 2.0 ** 23) * 2.0 ** -23
+    z[:, :100] = -float(rise)
+    got, ref = _scores_of_given_logits(z, dtype)
+    heavy = ((got - ref) / ref)[:, 100:n - 10]
+    say("late rise", dtype, n, rise, "rms", float(heavy.square().mean().sqrt()), "max", float(heavy.abs().max()))
+    assert float(heavy.square().mean().sqrt()) < 6e-7
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
