@@ -263,7 +263,8 @@ int ssd_compress_kv(ssd_cache *cache, int layer_begin, int layer_end,
  * ones it makes the score of every key that its query attends to NaN, and may
  * do so to the unit's other keys.  Other units keep their scores.
  * The products run on the matrix cores with fp32 accumulation; the sum over i
- * is taken in a fixed order (bit-reproducible).
+ * is taken in a fixed order: a unit's scores are the same to the bit in every
+ * call, whatever number of units it has.
  */
 int ssd_prefill_scores(const void *Q, const void *K, int n_units, int n_src, int d,
                        int dtype, float softmax_scale, float *score_out, void *stream);

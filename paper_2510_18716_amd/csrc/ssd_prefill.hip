@@ -357,6 +357,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
     constexpr int NK = FPR / 4;                            // ... per lane and 16 rows of an operand's tile
     constexpr int ST = long_stage_tiles<ROW>();
     constexpr int STAGE_BYTES = ST * 32 * ROW;
+    static_assert((ST & (ST - 1)) == 0 && 8 % ST == 0, "eight tiles are whole stages");
     static_assert(STAGE_BYTES % 1024 == 0 && 64 % FPR == 0, "a stage is brought in by wave-wide transfers of whole rows");
     constexpr int HELD = WAVES * NS;                       // tiles the workgroup holds at a time
     constexpr float LARGE = 1048576.f;                     // 2^20, see above
@@ -399,7 +400,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
     };
 
     // Stages in the order they are needed: of sweep 1, held tiles from `begin` on, streamed tiles 0 .. the last held one; of sweep 2,
-    // held tiles [begin, stop), streamed tiles from the first held one on.  ahead_*: the stage to request next.
+    // held tiles [begin, stop), streamed tiles from the first held one's stage on (stages lie at multiples of ST, see the fold below).
+    // ahead_*: the stage to request next.
     const int begin = a.cut[blockIdx.y], stop = a.cut[blockIdx.y + 1];      // this workgroup's keys, in tiles
     if (begin >= stop) return;
     int ahead_sweep = 0, ahead_first = begin, ahead_tile = 0;
@@ -411,7 +413,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
         if (ahead_tile >= (ahead_sweep == 0 && ahead_first + HELD < n_tiles ? ahead_first + HELD : n_tiles)) {
             ahead_first += HELD;
             if (ahead_first >= (ahead_sweep ? stop : n_tiles)) { ++ahead_sweep; ahead_first = begin; }
-            ahead_tile = ahead_sweep ? ahead_first : 0;
+            ahead_tile = ahead_sweep ? ahead_first & ~(ST - 1) : 0;
         }
     };
     // One group of held tiles; its first stage is requested.  Returns false if a column sum is not a number (CAREFUL: never).
@@ -454,7 +456,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
             for (int v = 0; v < 8; ++v) acc[s][v] = 0.f;
         }
 
-        const int from = COLS ? first : 0;                                            // streamed tiles [from, to)
+        const int from = COLS ? first & ~(ST - 1) : 0;                                // streamed tiles [from, to)
         const int to = COLS ? n_tiles : first + HELD < end ? first + HELD : end;
         // One streamed tile against one held tile.  Value 8 g + 4 k + v of a lane: query 16 g + l mod 16, key 16 k + 4 (l / 16) + v.
         auto product = [&](const uint4 (&fr)[2][NK], int s, float (&c)[16]) {
@@ -582,8 +584,9 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
                 }
             }
             cur ^= 1;
-            // every eight tiles the lanes meet: a sum over all of a long prompt's tiles in one register would lose a rounding per tile
-            if (COLS && (((t0 + ST - from) & 7) == 0 || t0 + ST >= to)) {
+            // Every eight tiles the lanes meet: a sum over all of a long prompt's tiles in one register would lose a rounding per tile.
+            // Counted from the prompt's beginning, so that a unit's scores do not depend on how its tiles are dealt to waves and workgroups.
+            if (COLS && (((t0 + ST) & 7) == 0 || t0 + ST >= to)) {
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
                     if (tile[s] >= t0 + ST) continue;      // nothing added yet (wave-uniform)
@@ -624,7 +627,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
                     landed();                              // what the next group's first stage has brought makes way
                     __syncthreads();
                     ahead_sweep = 1;
-                    ahead_first = ahead_tile = first;
+                    ahead_first = first;
+                    ahead_tile = first & ~(ST - 1);
                     request_next(cur);
                     group(cols, std::true_type{}, first, end);
                 }

@@ -203,6 +203,31 @@ def test_prefill_scores_long_prompts_lose_no_precision_to_a_late_rise(dtype, n, 
     assert float(heavy.square().mean().sqrt()) < 6e-7
 
 
+@pytest.mark.parametrize("dtype,d,n", [("bf16", 128, 129), ("bf16", 128, 300), ("bf16", 128, 640), ("bf16", 128, 1500), ("bf16", 64, 450), ("f32", 128, 330),
+                                       ("f32", 64, 700), ("f32", 128, 4096), ("bf16", 128, 2100)])
+def test_prefill_scores_of_a_unit_do_not_depend_on_the_call(dtype, d, n):
+    """A unit's scores are the same to the bit whatever number of units the call has, that is, whether two or three workgroups share
+    its keys, and how many waves and tiles a workgroup has; also where references are renewed and where a logit is no number."""
+    units = 260 if n < 2000 else 131
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, k = (torch.randn((units, n, d), generator=g, device="cuda") for _ in range(2))
+    q[1::4, :, 0], k[1::4, :, 0], k[1::4, n // 2:, 0] = 16.0, -6.0, 6.0            # rises half way
+    k[2, n // 3, 1] = float("nan")
+    q[3, n // 2, 1] = float("nan")
+    q, k = (x.to(torch.bfloat16 if dtype == "bf16" else torch.float32) for x in (q, k))
+    scores = {}
+    for u in (1, 4, 86, 129, 130, units):
+        say("units", u, dtype, d, n)
+        scores[u] = torch.empty((u, n), device="cuda")
+        ssd.ssd_prefill_scores(q, k, u, n, d, dtype, scores[u])
+    for u, sc in scores.items():
+        assert bool(torch.isfinite(sc).all())
+        assert torch.equal(sc, scores[units][:u]), (u, float((sc - scores[units][:u]).abs().max()))
+    second = torch.empty((units // 2, n), device="cuda")
+    ssd.ssd_prefill_scores(q[units - units // 2:], k[units - units // 2:], units // 2, n, d, dtype, second)
+    assert torch.equal(second, scores[units][units - units // 2:])
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n", [40, 64, 128])
 def test_prefill_scores_short_prompts_pass_a_logit_that_is_no_number_on(dtype, n):
