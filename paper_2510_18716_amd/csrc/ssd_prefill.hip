@@ -386,7 +386,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
             r = r < n ? r : n - 1;                         // rows past the end repeat the last one
             const uint32_t from = (uint32_t)r * ROW + (uint32_t)((lane % FPR) ^ swizzle(row)) * 16u;
             const uint32_t to = __builtin_amdgcn_readfirstlane(lds_base + buf * STAGE_BYTES + i * 1024);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(to), "v"(from), "s"(base) : "memory");
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(to), "v"(from), "s"(base) : "memory", "m0");
         }
     };
     auto landed = [&]() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); };

@@ -32,6 +32,19 @@ def test_library_exports_every_declared_symbol():
     assert ssd.ssd_last_error() == "" or isinstance(ssd.ssd_last_error(), str)
 
 
+def test_inline_assembly_names_the_registers_it_writes():
+    """An asm statement that writes m0 (the LDS address of a transfer from memory) by name has it among its clobbers: the compiler may
+    keep a value of its own there."""
+    import glob
+    seen = 0
+    for path in glob.glob(os.path.join(ROOT, "paper_2510_18716_amd", "csrc", "*.h*")):
+        for stmt in re.findall(r"\basm\b[^;]*;", open(path).read()):
+            if re.search(r"\b[sv]_\w+\s+m0\s*,", stmt):
+                seen += 1
+                assert '"m0"' in stmt.rsplit(":", 1)[1], (path, stmt)
+    assert seen
+
+
 def _ht(L, H, frac=0.5):
     m = np.ones((L, H), np.uint8)
     m[:, : int(H * frac)] = 0
