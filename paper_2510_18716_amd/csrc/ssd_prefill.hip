@@ -386,7 +386,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
             r = r < n ? r : n - 1;                         // rows past the end repeat the last one
             const uint32_t from = (uint32_t)r * ROW + (uint32_t)((lane % FPR) ^ swizzle(row)) * 16u;
             const uint32_t to = __builtin_amdgcn_readfirstlane(lds_base + buf * STAGE_BYTES + i * 1024);
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"            // m0 is reserved: named all the same, so that its next use sets it anew
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(to), "v"(from), "s"(base) : "memory", "m0");
+#pragma clang diagnostic pop
         }
     };
     auto landed = [&]() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); };
