@@ -292,12 +292,13 @@ __global__ __launch_bounds__(64 * KT) void prefill_scores_short_kernel(PrefillAr
 // The reference that a query's exponentials are taken against is the largest logit of its first streamed tile, one for the four lanes
 // that share the query, and stays while it can: a maximum per tile, the rescaling and the chain through both are a fifth of the vector
 // ALUs' work.  Logits above it cost precision -- an argument x of an exponential is rounded to 2^-24 x, where against a running maximum
-// the heavy terms' arguments stay near zero -- so a tile that would bring a lane's sum to 2^20 or makes it no number is taken again with
-// the reference renewed.  Error against 64 bits over a running maximum's (fp32 and bf16, 200 to 1500 tokens): logits that rise
-// by 2^16 to 2^28 0.98 on average and 1.12 at most, by 2^40 to 2^90 0.99 and 1.08; with that line at 2^100 1.01 and 1.13, 1.06 and 1.23.
-// 256 units of 1500 tokens, logits that rise by 2^24: 169 us, 166 where nothing rises (164 without the test); taking whole groups of
-// held tiles again 271.  (The lanes' sums are of one scale: with a reference per lane, a lane whose first keys lie 2^126 below the
-// others' would lose what it has added up since.)
+// the heavy terms' arguments stay near zero -- so where a stage would bring a lane's sum to 2^20 or makes it no number, the stage's tiles
+// are taken again with the reference renewed tile by tile.  Error against 64 bits over a running maximum's (fp32 and bf16, 200 to 1500
+// tokens): logits that rise by 2^16 to 2^28 0.98 on average and 1.08 at most, by 2^40 to 2^90 1.00 and 1.08; with that line at 2^100
+// 1.01 and 1.13, 1.06 and 1.23.  Tested per stage it costs nothing where nothing rises (256 units of 1500 tokens 168 us, 300 of 640 76.6;
+// tested per tile 170 and 77.2) and where all queries' logits rise by 2^24 at once 181 us (170; whole groups of held tiles taken again
+// 271).  (The lanes' sums are of one scale: with a reference per lane, a lane whose first keys lie 2^126 below the others' would lose
+// what it has added up since.)
 //
 // What bounds it: a 32 x 32 x 128 product takes a SIMD 256 cycles of its matrix core and 16 exponentials (8 cycles each), 16
 // multiply-adds and 16 adds per lane, 260 cycles of its vector ALUs, beside each other where two waves alternate.  The loop by
@@ -497,12 +498,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
                 for (int i = 0; i < 16; ++i)
                     if ((i & 7) < h) c[i] += c[i + h];
         };
-        // A tile of sweep 1 with the queries' references renewed: the first one, and one that the references cannot stand for.
-        auto renew = [&](const uint4 (&fr)[2][NK], int t, int s) {
-            float c[16];
-            product(fr, s, c);
-            mask(c, t, s);
-            drop_nan(c);
+        auto renew = [&](float (&c)[16], int s) {           // the references of a tile's queries, as far as its logits lie above them
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
                 float mx = c[8 * g];
@@ -512,42 +508,29 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
                 sum[s][g] *= fast_exp2(ref[s][g] - m_new);
                 ref[s][g] = m_new;
             }
-            exponentials(c, ref[s][0], ref[s][1]);
-            row_sums(c);
-            sum[s][0] += c[0];
-            sum[s][1] += c[8];
         };
-        auto process = [&](int t, const uint4 (&fr)[2][NK], const float2 (&qs)[2]) {     // one streamed tile against the tiles this wave holds
+        // One streamed tile against one held tile.
+        auto absorb = [&](auto renewed, const uint4 (&fr)[2][NK], int t, int s, const float2 (&qs)[2]) {
+            if (!(t < to && tile[s] < n_tiles && (COLS ? t >= tile[s] : t <= tile[s]))) return;         // above the diagonal (wave-uniform)
+            float c[16];
+            product(fr, s, c);
+            mask(c, t, s);
+            if constexpr (CAREFUL || decltype(renewed)::value) drop_nan(c);
+            if constexpr (COLS) {
+                exponentials(c, qs[0].x, qs[1].x);
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                if (!(t < to && tile[s] < n_tiles && (COLS ? t >= tile[s] : t <= tile[s]))) continue;    // above the diagonal (wave-uniform)
-                if constexpr (COLS) {
-                    float c[16];
-                    product(fr, s, c);
-                    mask(c, t, s);
-                    if constexpr (CAREFUL) drop_nan(c);
-                    exponentials(c, qs[0].x, qs[1].x);
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[s][i & 7] = fmaf(c[i], qs[i >> 3].y, acc[s][i & 7]);
-                } else {
-                    float sum0 = LARGE, sum1 = LARGE;
-                    if (t != 0) {
-                        float c[16];
-                        product(fr, s, c);
-                        mask(c, t, s);
-                        exponentials(c, ref[s][0], ref[s][1]);
-                        row_sums(c);
-                        sum0 = sum[s][0] + c[0];
-                        sum1 = sum[s][1] + c[8];
-                    }
-                    if (__any(!(__builtin_elementwise_maximum(sum0, sum1) < LARGE))) {     // (NaN if one of them is)
-                        renew(fr, t, s);
-                    } else {
-                        sum[s][0] = sum0;
-                        sum[s][1] = sum1;
-                    }
-                }
+                for (int i = 0; i < 16; ++i) acc[s][i & 7] = fmaf(c[i], qs[i >> 3].y, acc[s][i & 7]);
+            } else {
+                if (decltype(renewed)::value || t == 0) renew(c, s);
+                exponentials(c, ref[s][0], ref[s][1]);
+                row_sums(c);
+                sum[s][0] += c[0];
+                sum[s][1] += c[8];
             }
+        };
+        auto process = [&](int t, const uint4 (&fr)[2][NK], const float2 (&qs)[2]) {     // ... against the tiles this wave holds
+#pragma unroll
+            for (int s = 0; s < NS; ++s) absorb(std::false_type{}, fr, t, s, qs);
         };
         auto stats = [&](int t, float2 (&qs)[2]) {
 #pragma unroll
@@ -562,6 +545,9 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
                 __syncthreads();                           // this stage is in LDS, the other buffer is free
             }
             if (t0 != from) request_next(cur ^ 1);
+            float before[NS][2];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) { before[s][0] = sum[s][0]; before[s][1] = sum[s][1]; }
             if constexpr (AHEAD) {
                 uint4 fb[2][NK];
                 float2 qb[2];
@@ -584,6 +570,19 @@ __global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill
                     fragments(cur, j, fa);
                     stats(t0 + j, qa);
                     process(t0 + j, fa, qa);
+                }
+            }
+            if constexpr (!COLS) {                         // a sum that the references cannot stand for: the stage's tiles again
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    if (!__any(!(__builtin_elementwise_maximum(sum[s][0], sum[s][1]) < LARGE))) continue;          // (NaN if one of them is)
+                    sum[s][0] = before[s][0];
+                    sum[s][1] = before[s][1];
+#pragma unroll 1
+                    for (int j = 0; j < ST; ++j) {
+                        fragments(cur, j, fa);
+                        absorb(std::true_type{}, fa, t0 + j, s, qa);
+                    }
                 }
             }
             cur ^= 1;
