@@ -311,7 +311,14 @@ __global__ __launch_bounds__(64 * KT) void prefill_scores_short_kernel(PrefillAr
 // for the queries that see any of its keys, so the gain is less than their number (32 units of 1500 tokens: 168 -> 141 us in one
 // piece, 120 in two, 105 in three; four 105).
 // More than 256 units: four waves per workgroup, two workgroups on a compute unit fill each other's waits and no round is left half empty
-// (300 units of 1500 tokens: 354 us before, 307 with eight waves, 293 with four; 512 of 640: 103, 87, 80).
+// (d = 128, bf16: 300 units of 1500 tokens 354 us before, 307 with eight waves, 293 with four; 512 of 640 103, 87, 80).  Not where
+// LDS has room for one (rows of 256 bytes and more, from 2017 tokens on: its statistics grow with the prompt), which would leave a SIMD
+// one wave: 300 units of 2049 tokens 663 us before, 814 with four waves, 567 with eight; of 4096 2304, 2960, 2096; fp32, d = 64,
+// 300 of 2049 2720, 3101, 2709.  Nor in fp32 with d = 64, whose eight waves need so few registers that two workgroups fit as well: 300 units of 400
+// tokens 152 us with four waves, 138 with eight, 1024 of 129 76 and 67.  bf16 with d = 64 holds three workgroups of four waves, 768 units
+// at once, or, in 128 registers, two of eight, 512 units, which are better where they need no more rounds and the prompt fills
+// them: 300 units of 400 tokens 34.4 -> 31.2 us (30.6 before), of 1000 118 -> 107 (111), 1024 of 400 65.5 -> 61.1 (59), but 600 of 640
+// tokens 78.4 and 89.1, 512 of 129 12.9 and 13.8.
 // NS = 3 where it takes a group less than NS = 2 (256 units of 640 tokens 51.0 and 45.2 us, of 1000 90.8 and 92.2).
 template <int ROW> static constexpr int long_stage_tiles() { return 1024 / ROW < 4 ? 1024 / ROW : 4; }
 
@@ -350,9 +357,10 @@ static __device__ __forceinline__ double sums_over_16_lanes(const float (&x)[8],
     return q + dpp_d<0x4E>(q);                                                                              // quad_perm [2,3,0,1]
 }
 
-template <typename T, int D, int WAVES, int NS>
-__global__ __launch_bounds__(64 * WAVES, WAVES < 8 ? 2 : WAVES / 4) void prefill_scores_long_kernel(PrefillArgs a) {
-    constexpr bool AHEAD = sizeof(T) == 2 && NS < 4 && WAVES <= 8;         // fragments a tile ahead (registers: fp32 fragments take twice as many)
+// PER_SIMD: waves that the registers let a SIMD hold at least.
+template <typename T, int D, int WAVES, int NS, int PER_SIMD>
+__global__ __launch_bounds__(64 * WAVES, PER_SIMD) void prefill_scores_long_kernel(PrefillArgs a) {
+    constexpr bool AHEAD = sizeof(T) == 2 && PER_SIMD <= 2;                // fragments a tile ahead (registers: fp32 fragments take twice as many)
     constexpr int ROW = D * (int)sizeof(T);
     constexpr int FPR = ROW / 16;                          // 16-byte fragments per row
     constexpr int NK = FPR / 4;                            // ... per lane and 16 rows of an operand's tile
@@ -661,6 +669,9 @@ template <int ROW> static size_t long_lds_bytes(int n) {
     return 2 * (size_t)long_stage_tiles<ROW>() * 32 * ROW + (size_t)((n + 31) / 32 * 32) * 2 * sizeof(float);
 }
 
+// Whether a compute unit's 160 KB of LDS have no room for a second workgroup (256 bytes more each: the vote of a workgroup).
+static bool long_alone(size_t lds) { return 2 * (lds + 256) > 163840; }
+
 // Grid of a kernel whose workgroups walk the units with a stride of the grid size: as many workgroups as are
 // resident at once (workgroups per compute unit x compute units of the current device), trimmed so that every
 // workgroup gets the same number of units, give or take one at the very end.  0 on failure.
@@ -733,23 +744,26 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
     do {                                                                                                                        \
         if (keep_k) SSD_PREFILL_SHORT_AS(T_, D_, KT_, true); else SSD_PREFILL_SHORT_AS(T_, D_, KT_, false);                     \
     } while (0)
-#define SSD_PREFILL_LONG(T_, D_, WAVES_, NS_)                                                                                    \
+#define SSD_PREFILL_LONG(T_, D_, WAVES_, NS_, PER_SIMD_)                                                                         \
     do {                                                                                                                        \
-        const void *fn = reinterpret_cast<const void *>(&prefill_scores_long_kernel<T_, D_, WAVES_, NS_>);                      \
+        const void *fn = reinterpret_cast<const void *>(&prefill_scores_long_kernel<T_, D_, WAVES_, NS_, PER_SIMD_>);           \
         const size_t lds = long_lds_bytes<D_ * (int)sizeof(T_)>(n_src);                                                         \
         if (lds > 65536) attr = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                  \
         if (attr == hipSuccess)                                                                                                 \
-            hipLaunchKernelGGL((prefill_scores_long_kernel<T_, D_, WAVES_, NS_>), dim3((unsigned)n_units, (unsigned)parts), dim3(64 * WAVES_), lds, s, a); \
+            hipLaunchKernelGGL((prefill_scores_long_kernel<T_, D_, WAVES_, NS_, PER_SIMD_>), dim3((unsigned)n_units, (unsigned)parts), dim3(64 * WAVES_), lds, s, a); \
     } while (0)
 #define SSD_PREFILL(T_, D_)                                                                                          \
     do {                                                                                                             \
         constexpr bool wide = sizeof(T_) == 4;             /* fp32 fragments: one tile per wave */                   \
+        constexpr bool narrow = !wide && D_ == 64;                                                                   \
+        const bool eight = n_units <= 256 || (wide && D_ == 64) || long_alone(long_lds_bytes<D_ * (int)sizeof(T_)>(n_src)); \
         if (n_blocks <= 2) SSD_PREFILL_SHORT(T_, D_, 2);                                                             \
         else if (n_blocks <= 4) SSD_PREFILL_SHORT(T_, D_, 4);                                                        \
-        else if (n_units <= 256 && three(8)) SSD_PREFILL_LONG(T_, D_, 8, (wide ? 1 : 3));                            \
-        else if (n_units <= 256) SSD_PREFILL_LONG(T_, D_, 8, (wide ? 1 : 2));                                        \
-        else if (three(4)) SSD_PREFILL_LONG(T_, D_, 4, (wide ? 1 : 3));                                              \
-        else SSD_PREFILL_LONG(T_, D_, 4, (wide ? 1 : 2));                                                            \
+        else if (eight && three(8)) SSD_PREFILL_LONG(T_, D_, 8, (wide ? 1 : 3), 2);                                  \
+        else if (eight) SSD_PREFILL_LONG(T_, D_, 8, (wide ? 1 : 2), 2);                                              \
+        else if (narrow && n_blocks > 8 && (n_units + 511) / 512 <= (n_units + 767) / 768) SSD_PREFILL_LONG(T_, D_, 8, (wide ? 1 : 2), (narrow ? 4 : 2)); \
+        else if (three(4)) SSD_PREFILL_LONG(T_, D_, 4, (wide ? 1 : 3), 2);                                           \
+        else SSD_PREFILL_LONG(T_, D_, 4, (wide ? 1 : 2), 2);                                                         \
     } while (0)
     if (dtype == SSD_BF16) {
         if (d == 128) SSD_PREFILL(bf16_t, 128); else SSD_PREFILL(bf16_t, 64);
