@@ -725,7 +725,9 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
     // long prompts (the reasons stand at the kernel): workgroups per unit, and whether a wave holds three tiles rather than two
     const int parts = n_units <= 85 ? 3 : n_units <= 128 ? 2 : 1;
     auto three = [&](int w) { return (n_blocks + 3 * w - 1) / (3 * w) < (n_blocks + 2 * w - 1) / (2 * w); };
-    cut_long(n_blocks, parts, a.cut);
+    a.cut[0] = 0;
+    a.cut[1] = n_blocks;
+    if (parts > 1 && n_blocks > 4) cut_long(n_blocks, parts, a.cut);       // (the search takes the host 1 to 3 us)
     hipError_t attr = hipSuccess;
     // more than 64 KB of dynamic LDS has to be asked for (the longest short prompts in fp32: 70 KB of the CU's 160 KB)
 #define SSD_PREFILL_SHORT_AS(T_, D_, KT_, KEEP_)                                                                                \
