@@ -712,11 +712,17 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
     a.n = n_src;
     a.row_bytes = d * (dtype == SSD_F32 ? 4 : 2);
     a.qscale = (softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)d)) * LOG2E;
-    // Short prompts: a prompt's compression follows and reads K again.  Without the non-temporal hint K stays in the memory-side cache.
-    // Scores and compression together, us: 4096 units of 64 tokens 61.0 -> 59.2, of 120 143.6 -> 129.6, 2880 of 64 45.4 -> 44.7; without
-    // the hint on Q as well 61.3 and 131.4.  Where K about fits the L2s the hint on both is better (512 units of 64 tokens 13.95 and
-    // 14.33, 2048 of 64 33.3 and 33.7).
-    const bool keep_k = (size_t)n_units * (size_t)n_src * (size_t)a.row_bytes >= ((size_t)40 << 20);
+    // Short prompts: a prompt's compression follows and reads K again.  Without the non-temporal hint K stays in the memory-side cache for
+    // it, but first has to be let in: where the cache is full of what others wrote, that writes as much back as K has bytes.  A
+    // kernel that waits for memory anyway is slower by that and the compression gains less than it loses, so K keeps the hint where
+    // rows of 256 bytes or less fill seven eighths of their tiles.  Scores and compression of new, just written and repeated prompts, us
+    // per layer with and without the hint (4096 units, bf16, d = 128; "just written" with the writing): 64 tokens 68, 143, 66 and 72, 137,
+    // 63; of 48 61, 118, 61 and 61, 112, 56; of 100 98, 211, 94 and 97, 206, 91; fp32 of 64 160, 307, 157 and 150, 291, 143.  K of up to
+    // 537 MB in fp32 gains as well (520, 1196, 508 and 514, 1156, 508 for 16384 units of 64 tokens), bf16 of full tiles from 168 MB on
+    // does not even where it was just written (16384 of 64: 529 and 535).  With less than 40 MB, which about fits the L2s, the hint is
+    // better (512 units of 64 tokens 13.95 and 14.33).
+    const bool full_tiles = n_src * 8 > (n_src + 31) / 32 * 32 * 7;
+    const bool keep_k = (size_t)n_units * (size_t)n_src * (size_t)a.row_bytes >= ((size_t)40 << 20) && !(full_tiles && a.row_bytes <= 256);
     const int n_blocks = (n_src + 31) / 32;
     const int waves = n_blocks < 4 ? n_blocks : 4;
     const size_t lds_short = short_lds_bytes(waves, n_src, a.row_bytes);

@@ -449,10 +449,11 @@ def test_dense_source_at_the_edges_of_its_shapes(dtype, d, heads, B, H, n, M, R)
     _dense_source_selection(B, H, n, "spread", dtype, d, M, W=20, R=R, heads=heads)
 
 
-@pytest.mark.parametrize("B,H,n,dtype,d", [(80, 32, 40, "bf16", 128), (83, 31, 70, "bf16", 128), (83, 31, 33, "f32", 128), (128, 21, 65, "f32", 64)])
+@pytest.mark.parametrize("B,H,n,dtype,d", [(80, 32, 40, "bf16", 128), (83, 31, 70, "bf16", 128), (83, 31, 33, "f32", 128), (128, 21, 65, "f32", 64),
+                                             (80, 32, 64, "bf16", 128), (100, 32, 56, "bf16", 128), (100, 32, 57, "bf16", 128), (80, 32, 64, "f32", 128)])
 def test_short_prompts_of_many_units(B, H, n, dtype, d):
     """From 2560 units of up to 32 KB on neighbouring units are dealt to one XCD (2560 and 2573: whole blocks of 512 and 13 beside them),
-    and from 40 MB of keys on K is read without the hint: the same scores (tolerance as for long prompts), the sorted selection."""
+    and from 40 MB of keys on K is read without the hint unless rows of 256 bytes fill their tiles (57 of 64): the same scores (tolerance as for long prompts), the sorted selection."""
     _dense_source_selection(B, H, n, "spread", dtype, d, M=24, W=20)
     g = torch.Generator(device="cuda").manual_seed(n)
     q, k = (torch.randn((B * H, n, d), generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32) for _ in range(2))
