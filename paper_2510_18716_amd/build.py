@@ -64,8 +64,10 @@ def build(force: bool = False, verbose: bool = True) -> str:
     for src in sources():
         obj = os.path.join(OBJ, os.path.basename(src)[:-4] + ".o")
         objs.append(obj)
-        if force or not os.path.exists(obj) or os.path.getmtime(obj) < max(os.path.getmtime(src), t_hdr):
+        part_of = os.path.join(CSRC, "ssd_step.hip") if os.path.basename(src).startswith("ssd_step_") else src     # included
+        if force or not os.path.exists(obj) or os.path.getmtime(obj) < max(os.path.getmtime(src), os.path.getmtime(part_of), t_hdr):
             jobs.append([HIPCC] + FLAGS + ["-c", src, "-o", obj])
+    jobs.sort(key=lambda c: "ssd_step_" not in c[-1])                # the longest first
     with ThreadPoolExecutor(max(1, min(8, len(jobs)))) as ex:
         list(ex.map(lambda c: _run(c, verbose), jobs))
     tmp = LIB + ".tmp%d" % os.getpid()

@@ -96,7 +96,7 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 #define SSD_KERNARG __attribute__((address_space(4)))
 
-static __device__ __forceinline__ void fetch_args(int lrel, StepHot &a, LayerDesc &ld) {
+[[maybe_unused]] static __device__ __forceinline__ void fetch_args(int lrel, StepHot &a, LayerDesc &ld) {
     static_assert(sizeof(StepHot) <= 256, "the fixed part is read as four 64-byte pieces");
     static_assert(sizeof(LayerDesc) == 56, "one table entry is read as three 16-byte pieces and one of 8 bytes");
     static_assert(sizeof(StepArgsOne) >= 256 && offsetof(StepArgsOne, layer) == sizeof(StepHot) && offsetof(StepArgs, lm) == sizeof(StepHot) &&
@@ -143,7 +143,7 @@ static __device__ __forceinline__ void fetch_args(int lrel, StepHot &a, LayerDes
 }
 
 // Entry `rank` of the launch's HeadOrder (two independent scalar loads from the kernel-argument segment).
-static __device__ __forceinline__ void fetch_head_order(int rank, int &head, int &budget) {
+[[maybe_unused]] static __device__ __forceinline__ void fetch_head_order(int rank, int &head, int &budget) {
     const SSD_KERNARG char *kp = (const SSD_KERNARG char *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(StepArgsHeads, ho);
     const uint32_t wh = *reinterpret_cast<const SSD_KERNARG uint32_t *>(kp + offsetof(HeadOrder, head) + (size_t)(rank >> 2) * 4);
     const uint32_t wb = *reinterpret_cast<const SSD_KERNARG uint32_t *>(kp + offsetof(HeadOrder, budget) + (size_t)(rank >> 1) * 4);
@@ -556,33 +556,6 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
     }
 }
 
-// Largest candidate count the fused entry point ranks with a single wave; beyond it the stand-alone
-// compression kernel (a whole workgroup per head) runs after the attention.
-static constexpr int FUSED_SELECT_MAX = 1024;
-
-// Rank the heads of layer l by the rows this launch streams from their units, longest first (ties: lower head index).
-static void fill_head_order(const ssd_cache *c, int l, const LayerState &before, const LayerState &at, bool fused, HeadOrder *out) {
-    const ssd_config &cf = c->cfg;
-    const int H = cf.n_heads;
-    int rows[HMAX], idx[HMAX];
-    for (int h = 0; h < H; ++h) {
-        const int v = c->head_budget[(size_t)l * H + h];
-        idx[h] = h;
-        if (c->head_type[(size_t)l * H + h] == SSD_SEMANTIC) {
-            rows[h] = (at.m < v ? at.m : v) + at.c;
-        } else {
-            const bool rb = cf.spatial_row_buffer != 0;
-            rows[h] = fused ? ring_segs_fused(cf.n_init_sink, v, cf.stage_cap, rb, before.n, before.nc, -1).total
-                            : ring_segs(cf.n_init_sink, v, cf.stage_cap, rb, at.n, at.nc).total;
-        }
-    }
-    std::stable_sort(idx, idx + H, [&](int x, int y) { return rows[x] > rows[y]; });
-    for (int i = 0; i < HMAX; ++i) {
-        out->head[i] = (uint8_t)(i < H ? idx[i] : 0);
-        out->budget[i] = i < H ? c->head_budget[(size_t)l * H + idx[i]] : 0;
-    }
-}
-
 // One launch of the variant (WPB units per workgroup, or one unit shared by SHARE waves) that the call asks for.  One
 // layer: the short argument block (four or five wave-loads per chunk, which is what the library picks; the other chunk
 // sizes exist for sweeps and take the long block).
@@ -617,7 +590,7 @@ static void launch_variant(const StepArgs &full, const HeadOrder *ho, dim3 block
 // One launch over sequences [a.seq_off, a.seq_off + B) of the layers in `full`.  concurrent: the launch is one part of
 // a split call, so another part's launch runs beside it on another stream.
 template <typename T, int D>
-static hipError_t launch_step(StepArgs &full, const HeadOrder *ho, const LaunchShape &shape, LaunchShape *used, int H, int max_sp_heads, int max_se_heads,
+hipError_t launch_step(StepArgs &full, const HeadOrder *ho, const LaunchShape &shape, LaunchShape *used, int H, int max_sp_heads, int max_se_heads,
                               int B, int layers, long long call_units, bool fused, bool concurrent, int M, hipStream_t s) {
     StepHot &a = full.h;
     const bool heads = ho != nullptr;                     // budgets per head
@@ -710,6 +683,45 @@ static hipError_t launch_step(StepArgs &full, const HeadOrder *ho, const LaunchS
     }
 #undef SSD_CASE
     return hipErrorInvalidValue;
+}
+
+// The kernels of an element type and row length are compiled in a file of their own (ssd_step_*.hip, which include this one): there
+// are some hundred of them.  What follows is compiled here only.
+#define SSD_STEP_SIGNATURE StepArgs &, const HeadOrder *, const LaunchShape &, LaunchShape *, int, int, int, int, int, long long, bool, bool, int, hipStream_t
+#ifdef SSD_STEP_ONLY
+template hipError_t launch_step<SSD_STEP_ONLY>(SSD_STEP_SIGNATURE);
+}  // namespace ssd
+#else
+extern template hipError_t launch_step<bf16_t, 128>(SSD_STEP_SIGNATURE);
+extern template hipError_t launch_step<bf16_t, 64>(SSD_STEP_SIGNATURE);
+extern template hipError_t launch_step<float, 128>(SSD_STEP_SIGNATURE);
+extern template hipError_t launch_step<float, 64>(SSD_STEP_SIGNATURE);
+
+// Largest candidate count the fused entry point ranks with a single wave; beyond it the stand-alone
+// compression kernel (a whole workgroup per head) runs after the attention.
+static constexpr int FUSED_SELECT_MAX = 1024;
+
+// Rank the heads of layer l by the rows this launch streams from their units, longest first (ties: lower head index).
+static void fill_head_order(const ssd_cache *c, int l, const LayerState &before, const LayerState &at, bool fused, HeadOrder *out) {
+    const ssd_config &cf = c->cfg;
+    const int H = cf.n_heads;
+    int rows[HMAX], idx[HMAX];
+    for (int h = 0; h < H; ++h) {
+        const int v = c->head_budget[(size_t)l * H + h];
+        idx[h] = h;
+        if (c->head_type[(size_t)l * H + h] == SSD_SEMANTIC) {
+            rows[h] = (at.m < v ? at.m : v) + at.c;
+        } else {
+            const bool rb = cf.spatial_row_buffer != 0;
+            rows[h] = fused ? ring_segs_fused(cf.n_init_sink, v, cf.stage_cap, rb, before.n, before.nc, -1).total
+                            : ring_segs(cf.n_init_sink, v, cf.stage_cap, rb, at.n, at.nc).total;
+        }
+    }
+    std::stable_sort(idx, idx + H, [&](int x, int y) { return rows[x] > rows[y]; });
+    for (int i = 0; i < HMAX; ++i) {
+        out->head[i] = (uint8_t)(i < H ? idx[i] : 0);
+        out->budget[i] = i < H ? c->head_budget[(size_t)l * H + idx[i]] : 0;
+    }
 }
 
 struct Rope {
@@ -974,3 +986,4 @@ extern "C" int ssd_decode_step_rope(ssd_cache *cache, int layer_begin, int layer
     return run_step(cache, layer_begin, layer_end, q, k_new, v_new, out, accumulate_scores, compress, &stream, 1,
                     "decode step launch (rotary)", Rope{cos_p, sin_p, rope_layout});
 }
+#endif
