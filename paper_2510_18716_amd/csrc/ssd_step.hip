@@ -212,7 +212,8 @@ static __device__ __forceinline__ uint4 rope_fragment(const uint4 &raw, const fl
 // slots empty.  The partial sums of the waves are combined in another order than one wave adds them: outputs
 // and scores of the two forms agree to rounding, not to the bit.
 // Args: the argument block the launch carries (StepArgs: several layers).
-template <typename Args, typename T, int D, int CH, int WPB, bool FUSED, bool HEADS = false, bool ROPE = false, int SHARE = 1>
+// FAR: a compression with one buffered candidate and more than 128 in all (a launch of one layer).
+template <typename Args, typename T, int D, int CH, int WPB, bool FUSED, bool HEADS = false, bool ROPE = false, int SHARE = 1, bool FAR = false>
 __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {          // read through fetch_args
     constexpr bool MANY = std::is_same<Args, StepArgs>::value;
     static_assert(HEADS == std::is_same<Args, StepArgsHeads>::value, "budgets per head: one layer, with the head order");
@@ -446,16 +447,16 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
     const int n_old = t_c - t_R;                          // buffered tokens that become candidates
     const int n_cand = t_m + n_old;
     const int n_evict = n_cand - t_Mh;                    // <= 0: everything is kept
-    // At most one eviction (always the case when compressing after every token) is settled in registers: among any number of
-    // candidates if one is buffered, whose key is kept beside each lane's smallest, else among up to 128, whose keys are
-    // kept.  Anything else ranks all candidates through LDS.  (Above 128 everything did: 512 units of 64 rows and 129 candidates
-    // 9.9 -> 8.9 us per launch, 321 candidates 15.3 -> 13.8; 4096 units, 2 heads in 32 of 129 candidates 18.9 -> 18.3.  The smallest key
-    // beside the two kept costs calls with fewer 0.04 us; the same out of LDS, or only from 128 rows on, spilled or cost as much.
-    // Scores and positions of a third 64 rows fetched ahead as well: 0.3 us less from 127 to 191 rows, but 512 units of 66 rows 2 % slower.)
-    const bool general = compress && (n_evict >= 2 || (n_old != 1 && n_cand > 128));
+    // At most one eviction (always the case when compressing after every token) is settled in registers: among up to 128
+    // candidates, whose keys are kept, and with FAR among any number, of which a lane keeps the smallest key and the buffered one's.
+    // Anything else ranks all candidates through LDS.  (us per launch, LDS and FAR: 512 units of 64 rows and 129 candidates 9.9 and
+    // 8.9, 321 candidates 15.3 and 13.8; 4096 units, 2 heads in 32 of 129 candidates 18.9 and 18.3.  Kept beside the two keys in every
+    // call they cost those that look at fewer candidates up to 0.07.  Scores and positions of a third 64 rows fetched ahead as well: 0.3 less from
+    // 127 to 191 rows, but 512 units of 66 rows 2 % slower.)
+    const bool general = compress && (n_evict >= 2 || (n_cand > 128 && !(FAR && n_old == 1)));
     unsigned long long *keys = reinterpret_cast<unsigned long long *>(sel);
     unsigned long long my_key[2] = {~0ull, ~0ull};        // keys of rows lane and lane + 64, if candidates
-    unsigned long long least = ~0ull, promo = ~0ull;      // smallest key of the lane's candidates, and the row it belongs to; key of the first buffered one
+    unsigned long long least = ~0ull, promo = ~0ull;      // FAR: smallest key of the lane's candidates, and the row it belongs to; key of the first buffered one
     int least_row = 0;
     const int total = sg.total + (FUSED ? 1 : 0);
     // One row's share: add the probability to its running score, note position and key.
@@ -470,8 +471,10 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
         if (compress && r < n_cand) {
             key = make_key(s, is_new ? t_new_pos : pos_old);
             if (general) keys[r] = key;
-            if (key < least) { least = key; least_row = r; }
-            if (r == t_m) promo = key;
+            if constexpr (FAR) {
+                if (key < least) { least = key; least_row = r; }
+                if (r == t_m) promo = key;
+            }
         }
         return key;
     };
@@ -512,8 +515,15 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
     // candidate (the one with the smallest key), if any.
     int e_idx = -1;
     if (n_evict == 1) {
-        const unsigned long long hit = __ballot(least == wave_min_u64(least));
-        e_idx = __builtin_amdgcn_readlane(least_row, __builtin_ctzll(hit));
+        if constexpr (FAR) {
+            const unsigned long long hit = __ballot(least == wave_min_u64(least));
+            e_idx = __builtin_amdgcn_readlane(least_row, __builtin_ctzll(hit));
+        } else {
+            const unsigned long long min_key = wave_min_u64(my_key[0] < my_key[1] ? my_key[0] : my_key[1]);
+            const unsigned long long hit0 = __ballot(my_key[0] == min_key);
+            const unsigned long long hit1 = __ballot(my_key[1] == min_key);
+            e_idx = hit0 ? __builtin_ctzll(hit0) : 64 + __builtin_ctzll(hit1);
+        }
     }
     const bool ev_heavy = e_idx >= 0 && e_idx < t_m;
     const bool ev_staged = e_idx >= t_m;
@@ -523,7 +533,13 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
         const int to = ev_heavy ? e_idx : t_m;
         wave_store_order();                               // the evicted row's lane has just stored its score where lane 0 is about to store
         if (lane < 2 * LPR) *reinterpret_cast<uint4 *>((lane < LPR ? u.K : u.V) + (size_t)to * t_row_bytes + (size_t)sub * 16u) = pre_row;
-        const unsigned long long key = __shfl(promo, t_m & 63);
+        unsigned long long key;
+        if constexpr (FAR) {
+            key = __shfl(promo, t_m & 63);
+        } else {
+            const unsigned long long c0 = __shfl(my_key[0], t_m & 63), c1 = __shfl(my_key[1], t_m & 63);
+            key = t_m < 64 ? c0 : c1;
+        }
         if (lane == 0) { u.pos[to] = key_pos(key); u.score[to] = key_score(key); }
         return;
     }
@@ -547,8 +563,8 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
         const int src = k < n_move ? src_idx(k) : 0;
         const unsigned long long c0 = __shfl(my_key[0], src & 63);
         const unsigned long long c1 = __shfl(my_key[1], src & 63);
-        const unsigned long long c2 = __shfl(promo, t_m & 63);
-        const unsigned long long key = n_old == 1 ? c2 : src < 64 ? c0 : c1;
+        const unsigned long long c2 = FAR ? __shfl(promo, t_m & 63) : 0;
+        const unsigned long long key = FAR && n_old == 1 ? c2 : src < 64 ? c0 : c1;
         if (k < n_move) {
             u.pos[dst_slot(k)] = key_pos(key);
             u.score[dst_slot(k)] = key_score(key);
@@ -564,16 +580,21 @@ static void launch_variant(const StepArgs &full, const HeadOrder *ho, dim3 block
     const dim3 threads(WPB * SHARE * 64);
     const bool rope = full.h.rope_layout != 0;            // always fused (checked by the entry point)
     if constexpr (CH >= 4) {
+        const bool far = fused && full.h.do_compress && full.h.c - full.h.R == 1 && full.h.m + 1 > 128;
         if (ho) {
             const StepArgsHeads x = {full.h, full.lm.layer[0], *ho};
-            if (rope) hipLaunchKernelGGL((step_kernel<StepArgsHeads, T, D, CH, WPB, true, true, true, SHARE>), blocks, threads, lds, s, x);
+            if (rope && far) hipLaunchKernelGGL((step_kernel<StepArgsHeads, T, D, CH, WPB, true, true, true, SHARE, true>), blocks, threads, lds, s, x);
+            else if (rope) hipLaunchKernelGGL((step_kernel<StepArgsHeads, T, D, CH, WPB, true, true, true, SHARE>), blocks, threads, lds, s, x);
+            else if (far) hipLaunchKernelGGL((step_kernel<StepArgsHeads, T, D, CH, WPB, true, true, false, SHARE, true>), blocks, threads, lds, s, x);
             else if (fused) hipLaunchKernelGGL((step_kernel<StepArgsHeads, T, D, CH, WPB, true, true, false, SHARE>), blocks, threads, lds, s, x);
             else hipLaunchKernelGGL((step_kernel<StepArgsHeads, T, D, CH, WPB, false, true, false, SHARE>), blocks, threads, lds, s, x);
             return;
         }
         if (layers == 1) {
             const StepArgsOne x = {full.h, full.lm.layer[0]};
-            if (rope) hipLaunchKernelGGL((step_kernel<StepArgsOne, T, D, CH, WPB, true, false, true, SHARE>), blocks, threads, lds, s, x);
+            if (rope && far) hipLaunchKernelGGL((step_kernel<StepArgsOne, T, D, CH, WPB, true, false, true, SHARE, true>), blocks, threads, lds, s, x);
+            else if (rope) hipLaunchKernelGGL((step_kernel<StepArgsOne, T, D, CH, WPB, true, false, true, SHARE>), blocks, threads, lds, s, x);
+            else if (far) hipLaunchKernelGGL((step_kernel<StepArgsOne, T, D, CH, WPB, true, false, false, SHARE, true>), blocks, threads, lds, s, x);
             else if (fused) hipLaunchKernelGGL((step_kernel<StepArgsOne, T, D, CH, WPB, true, false, false, SHARE>), blocks, threads, lds, s, x);
             else hipLaunchKernelGGL((step_kernel<StepArgsOne, T, D, CH, WPB, false, false, false, SHARE>), blocks, threads, lds, s, x);
             return;
