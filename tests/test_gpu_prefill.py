@@ -65,8 +65,8 @@ def test_prefill_scores_largest_prompt_and_many_units():
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
 @pytest.mark.parametrize("n", [131, 160, 161, 256, 287, 512, 513, 800, 4096])
 def test_prefill_scores_long_prompts_at_tile_and_workgroup_edges(dtype, d, n):
-    """Above 128 tokens: around whole tiles, around what a workgroup of 4 (up to 256 tokens) and of 8 waves holds at a
-    time.  A unit beside the last one must stay as it was.  Tolerance: fp32 sums of up to n terms, each within a few
+    """Above 128 tokens: around whole tiles, around what workgroups hold at a time, in calls of so few units that three workgroups share
+    each.  A unit beside the last one must stay as it was.  Tolerance: fp32 sums of up to n terms, each within a few
     roundings of 2^-24 of an argument below 2^5 (4e-6), against 64 bits."""
     say("long prompt", dtype, d, n)
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
@@ -226,6 +226,36 @@ def test_prefill_scores_of_a_unit_do_not_depend_on_the_call(dtype, d, n):
     second = torch.empty((units // 2, n), device="cuda")
     ssd.ssd_prefill_scores(q[units - units // 2:], k[units - units // 2:], units // 2, n, d, dtype, second)
     assert torch.equal(second, scores[units][units - units // 2:])
+
+
+@pytest.mark.parametrize("dtype,d,n", [("bf16", 128, 200), ("bf16", 128, 400), ("bf16", 128, 800), ("bf16", 64, 400), ("bf16", 64, 600), ("bf16", 128, 1100),
+                                       ("f32", 128, 300), ("f32", 64, 600)])
+@pytest.mark.parametrize("units", [3, 129, 257, 600])
+def test_prefill_scores_long_prompts_disturbed_units_of_any_call(dtype, d, n, units):
+    """Logits that are no numbers and logits that rise late in one unit each, in calls whose workgroups share a unit's keys or not and have
+    eight or four waves, with one group of held tiles and with several.  Tolerances as for the tests of each."""
+    say("disturbed", dtype, d, n, units)
+    g = torch.Generator(device="cuda").manual_seed(n + units)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q, k = (torch.randn((units, n, d), generator=g, device="cuda") for _ in range(2))
+    late, nan, plain = 0, units - 1, units // 2
+    amp = 16.0 / np.sqrt(d)                                       # a logit is amp times what a key's element 0 holds, and a random part
+    q[late] *= 0.1
+    k[late] *= 0.1
+    q[late, :, 0], k[late, :, 0] = 16.0, -30.0 / amp
+    k[late, 100:150, 0] = 30.0 / amp
+    k[late, n - 40:, 0] = 60.0 / amp
+    q, k = q.to(tdt), k.to(tdt)
+    k[nan, 37, 5], k[nan, n - 1, 5], q[nan, 150, 3] = (float("nan"),) * 3
+    out = torch.full((units + 1, n), -5.0, device="cuda")
+    ssd.ssd_prefill_scores(q, k, units, n, d, dtype, out)
+    assert bool((out[units] == -5.0).all()) and bool(torch.isfinite(out).all())
+    ref = _scores_in_64_bits(q[[late, plain]], k[[late, plain]])
+    z = q[nan].double() @ k[nan].double().T / np.sqrt(d)
+    z = z.masked_fill(torch.isnan(z) | torch.ones((n, n), dtype=torch.bool, device="cuda").triu(1), -np.inf)
+    for u, want, tol in ((late, ref[0], 64 * 2.0 ** -24 * 90.0), (plain, ref[1], 1e-5), (nan, torch.nan_to_num(torch.softmax(z, dim=-1)).sum(dim=0), 1e-5)):
+        assert float(((out[u].double() - want).abs() / want.clamp_min(1e-3)).max()) < tol, u
+    assert float(out[nan, 37]) == 0.0 and float(out[nan, n - 1]) == 0.0
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
