@@ -127,7 +127,7 @@ static __device__ __forceinline__ void store_once(char *p, const uint4 &v) {
 // trip per fragment.  Neither side is touched again by this launch, so both carry the non-temporal hint.
 // Bound: HBM, rows read and written once.  7B shape, 4096 units, 64 source tokens, 41 kept on average (172 MB): 42.8 us
 // with single fragments, 38 with batches of four (two: 42), 35 with the stores non-temporal as well (4.9 TB/s, what a plain copy
-// reaches; loads without the hint: 75), 30 where the scoring kernel has left K in the memory-side cache and units are dealt to the XCDs.  256 units of 1500 tokens, 320 kept by the semantic half: 154 us with
+// reaches; loads without the hint: 75).  256 units of 1500 tokens, 320 kept by the semantic half: 154 us with
 // single fragments and ranks by counting, 19.8 now.
 template <int THREADS, int BATCH, typename Map>
 static __device__ __forceinline__ void copy_fragments(int n_frag, int tid, Map map) {
@@ -317,9 +317,10 @@ static hipError_t launch_dense_source(const ssd_cache *cache, int lb, int le, in
     // with 73 registers).  More units: room for no more candidates than there may be (2048 units of 1024 tokens 51.8 us with 8 per
     // thread, 58.3 with 16).
     const dim3 grid(units);
-    // Many units of few rows: with neighbours on one XCD each XCD meets an eighth of the source's pages (scores and compression together,
-    // 4096 units of 64 tokens 59.2 -> 56.5 us, of 120 129.6 -> 128.2, 2880 of 64 44.7 -> 43.9).  Longer units have pages to
-    // themselves (2048 of 1024 tokens 742 and 759), and fewer gain nothing (2048 of 96 49.3 both, 768 of 200 47.3 and 48.0).
+    // Many units of few rows: with neighbours on one XCD each XCD meets an eighth of the source's pages (us per launch, new prompts and ones
+    // just written: 4096 units of 64 tokens 37.4 -> 36.7 and 40.1 -> 37.3, 2560 of 64 26.8 -> 24.8 and 28.3 -> 26.1, 4096 of 120 40.2 -> 39.1
+    // and 42.7 -> 40.1).  Longer units have pages to themselves (scores and compression of 2048 of 1024 tokens 742 and 759), and
+    // fewer gain nothing (2048 of 96 49.3 both, 768 of 200 47.3 and 48.0).
     a.dealt = units >= 2560 && (size_t)n_src * a.g.row_bytes <= 32768 ? (int)(units & ~511u) : 0;
     if (n_cand <= 256 && (n_src <= 256 || n_cand > cache->Ml[lb])) hipLaunchKernelGGL((compress_dense_kernel<256, 1, LAYERS, HEADS>), grid, dim3(256), lds, s, a);
     else if (units <= 512) hipLaunchKernelGGL((compress_dense_kernel<1024, 4, LAYERS, HEADS>), grid, dim3(1024), lds, s, a);

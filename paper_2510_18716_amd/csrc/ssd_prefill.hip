@@ -5,14 +5,12 @@
 //     score[j] = sum_{i >= j} a_i(j)
 // which is what ssd_compress_kv's dense-source mode takes as score_src.
 //
-// This is the one step of the path that is a dense contraction (an n x n x d product per unit), so
-// it runs on the matrix cores: 32 x 32 output tiles of Q K^T with v_mfma_f32_32x32x16_bf16 (bf16
-// inputs, 8 k-values per lane and step) or v_mfma_f32_32x32x2_f32 (fp32 inputs).  Both operands keep their
-// row-major [n, d] layout on the way, from memory or through LDS: lane l supplies row (l mod 32) and the k-slice
-// selected by (l div 32), the same slice for Q and K, so nothing is transposed.
-// A tile's 32 x 32 results sit 16 per lane: column = l mod 32, row = 8*(v/4) + 4*(l/32) + v%4.
+// This is the one step of the path that is a dense contraction (an n x n x d product per unit), so it runs on the matrix cores,
+// in tiles of 32 x 32.  Both operands keep their row-major [n, d] layout on the way, from memory or through LDS: a lane supplies
+// one row and the same k-slice of Q and of K, so nothing is transposed.  Short prompts take v_mfma_f32_32x32x16_bf16 (8 k-values
+// per lane and step) or v_mfma_f32_32x32x2_f32, whose results sit 16 per lane, column = l mod 32, row = 8*(v/4) + 4*(l/32) + v%4; long
+// ones 16 x 16 products (mma_fragment).
 //
-// One workgroup per unit at a time.
 // Prompts of up to 128 tokens (one block per wave; the case the decode path's prompts fall in): the workgroup
 // fetches the unit's Q and K once, fully coalesced, and hands the matrix cores their fragments through LDS; the
 // tiles are taken as K Q^T so that a query's softmax statistics stay inside a lane pair and only the column
@@ -21,7 +19,8 @@
 // and what used to hold it back was the softmax bookkeeping on the vector ALUs (about 1100 instructions per
 // wave with the queries along the registers, about 400 now), not the matrix cores or the memory.
 // Longer prompts take two sweeps over the tiles on or below the diagonal -- the rows' sums, then the column sums -- in
-// which one operand stays in registers and the other streams through LDS (prefill_scores_long_kernel).  Nothing is added across waves but in a fixed order (bit-reproducible, no atomics).
+// which one operand stays in registers and the other streams through LDS (prefill_scores_long_kernel).
+// Nothing is added across waves but in a fixed order (bit-reproducible, no atomics).
 #include <cmath>
 #include <type_traits>
 
@@ -305,11 +304,11 @@ __global__ __launch_bounds__(64 * KT) void prefill_scores_short_kernel(PrefillAr
 // itself, with random data, takes 200 ns per product: what a large bf16 matrix product takes on this card, which clocks lower
 // under such loads (160 ns with zeros).  256 units of 1500 tokens (bf16, d = 128): 839 us with all operands read from memory in
 // fragment layout, 195 with 32 x 32 products and column sums that crossed lanes per tile (whose LDS reads and barriers the
-// waves spent half their time on), 163 now; of these 113 are the loop, the rest groups' beginnings (a held tile's loads touch a row
+// waves spent half their time on), 162 to 175 now, by the card's clock; of these 113 are the loop, the rest groups' beginnings (a held tile's loads touch a row
 // per lane) and diagonals (waves that have less to do wait).  Error against 64 bits 4.3e-8 -> 3.6e-8 (n = 256: 4.7e-8 both).
 // Few units: up to 128 leave half of the compute units idle, so two or three workgroups share a unit's keys; each goes through sweep 1
 // for the queries that see any of its keys, so the gain is less than their number (32 units of 1500 tokens: 168 -> 141 us in one
-// piece, 120 in two, 105 in three; four 105).
+// piece, 120 in two, 105 to 112 in three; four as much).
 // More than 256 units: four waves per workgroup, two workgroups on a compute unit fill each other's waits and no round is left half empty
 // (d = 128, bf16: 300 units of 1500 tokens 354 us before, 307 with eight waves, 293 with four; 512 of 640 103, 87, 80).  Not where
 // LDS has room for one (rows of 256 bytes and more, from 2017 tokens on: its statistics grow with the prompt), which would leave a SIMD
@@ -319,7 +318,7 @@ __global__ __launch_bounds__(64 * KT) void prefill_scores_short_kernel(PrefillAr
 // at once, or, in 128 registers, two of eight, 512 units, which are better where they need no more rounds and the prompt fills
 // them: 300 units of 400 tokens 34.4 -> 31.2 us (30.6 before), of 1000 118 -> 107 (111), 1024 of 400 65.5 -> 61.1 (59), but 600 of 640
 // tokens 78.4 and 89.1, 512 of 129 12.9 and 13.8.
-// NS = 3 where it takes a group less than NS = 2 (256 units of 640 tokens 51.0 and 45.2 us, of 1000 90.8 and 92.2).
+// NS = 3 where it takes a group less than NS = 2 (256 units of 640 tokens 51.0 with two and 45.2 us with three, of 1000, where it takes as many, 90.8 and 92.2).
 template <int ROW> static constexpr int long_stage_tiles() { return 1024 / ROW < 4 ? 1024 / ROW : 4; }
 
 static __device__ __forceinline__ void arrived(uint4 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
@@ -733,7 +732,7 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
     auto three = [&](int w) { return (n_blocks + 3 * w - 1) / (3 * w) < (n_blocks + 2 * w - 1) / (2 * w); };
     a.cut[0] = 0;
     a.cut[1] = n_blocks;
-    if (parts > 1 && n_blocks > 4) cut_long(n_blocks, parts, a.cut);       // (the search takes the host 1 to 3 us)
+    if (parts > 1 && n_blocks > 4) cut_long(n_blocks, parts, a.cut);       // (the search takes the host up to 1.6 us)
     hipError_t attr = hipSuccess;
     // more than 64 KB of dynamic LDS has to be asked for (the longest short prompts in fp32: 70 KB of the CU's 160 KB)
 #define SSD_PREFILL_SHORT_AS(T_, D_, KT_, KEEP_)                                                                                \

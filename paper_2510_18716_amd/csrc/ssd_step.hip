@@ -255,12 +255,13 @@ __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {         
         local = sem_unit ? sem_below : h - sem_below;
     } else {
         sem_unit = ((blockIdx.z & 1) == 0) == (a.sem_first != 0);
-        // Workgroups go round the eight XCDs.  With a multiple of eight of them per sequence each XCD would touch every
-        // sequence's units, and every page of the layer; dealt two whole sequences (1 MB of the 1B shape's units) at a
-        // time, an eighth.  One sequence at a time gains half as much, four as much as two; all of an XCD's sequences in one piece
-        // costs up to 2 %.  us per launch (bf16, d = 128): 512 units of 66 rows 6.45 -> 6.20, 2048 of 18 7.15 -> 6.80, 2048 of 129 to 385
-        // 34.7 -> 33.8; 4096 of 66 25.76 and 25.70.  Beside another part's launch, whose units the XCDs have to do with as well, it
-        // changes nothing or loses (7B shape on two streams 727 -> 736 us per step).
+        // Workgroups go round the eight XCDs, so that every XCD meets every sequence's units and every page of the layer; dealt two
+        // whole sequences at a time (0.5 MB of one type's units in the 1B shape) it meets an eighth of them.  Three bits of the head's
+        // and the sequence's index change places, which takes a multiple of eight workgroups per sequence and type; other numbers are
+        // left as they come, and pay 0.02 to 0.05 us for the question.  One sequence at a time gains half as much, four as much
+        // as two; all of an XCD's sequences in one piece costs up to 2 %.  us per launch (bf16, d = 128): 512 units of 66 rows 6.41 ->
+        // 6.23, 2048 of 18 7.01 -> 6.73, 2048 of 129 to 385 34.8 -> 33.9; 4096 of 66 24.97 and 25.00.  Beside another part's launch, whose
+        // units the XCDs have to do with as well, it changes nothing or loses (7B shape on two streams 727 -> 736 us per step).
         int x = blockIdx.x, y = blockIdx.y;
         if (y < a.by_xcd) {                               // exchange x mod 8 with bits 1..3 of y
             const int xcd = x & 7;
