@@ -304,7 +304,7 @@ __global__ __launch_bounds__(64 * KT) void prefill_scores_short_kernel(PrefillAr
 // itself, with random data, takes 200 ns per product: what a large bf16 matrix product takes on this card, which clocks lower
 // under such loads (160 ns with zeros).  256 units of 1500 tokens (bf16, d = 128): 839 us with all operands read from memory in
 // fragment layout, 195 with 32 x 32 products and column sums that crossed lanes per tile (whose LDS reads and barriers the
-// waves spent half their time on), 162 to 175 now, by the card's clock; of these 113 are the loop, the rest groups' beginnings (a held tile's loads touch a row
+// waves spent half their time on), 165 to 182 now, by the card's clock; of these 113 are the loop, the rest groups' beginnings (a held tile's loads touch a row
 // per lane) and diagonals (waves that have less to do wait).  Error against 64 bits 4.3e-8 -> 3.6e-8 (n = 256: 4.7e-8 both).
 // Few units: up to 128 leave half of the compute units idle, so two or three workgroups share a unit's keys; each goes through sweep 1
 // for the queries that see any of its keys, so the gain is less than their number (32 units of 1500 tokens: 168 -> 141 us in one
@@ -716,12 +716,14 @@ extern "C" int ssd_prefill_scores(const void *Q, const void *K, int n_units, int
     // kernel that waits for memory anyway is slower by that and the compression gains less than it loses, so K keeps the hint where
     // rows of 256 bytes or less fill seven eighths of their tiles.  Scores and compression of new, just written and repeated prompts, us
     // per layer with and without the hint (4096 units, bf16, d = 128; "just written" with the writing): 64 tokens 68, 143, 66 and 72, 137,
-    // 63; of 48 61, 118, 61 and 61, 112, 56; of 100 98, 211, 94 and 97, 206, 91; fp32 of 64 160, 307, 157 and 150, 291, 143.  K of up to
-    // 537 MB in fp32 gains as well (520, 1196, 508 and 514, 1156, 508 for 16384 units of 64 tokens), bf16 of full tiles from 168 MB on
-    // does not even where it was just written (16384 of 64: 529 and 535).  With less than 40 MB, which about fits the L2s, the hint is
-    // better (512 units of 64 tokens 13.95 and 14.33).
+    // 63; of 48 61, 118, 61 and 61, 112, 56; of 100 98, 211, 94 and 97, 206, 91; fp32 of 64 160, 307, 157 and 150, 291, 143.  Up to 512 MB
+    // it gains, or loses nothing (fp32, 16384 units of 64 tokens 583, 1192, 579 and 555, 1170, 547; bf16 of 100 647, 1582, 640 and 643,
+    // 1552, 631 for two layers); beyond, where little of K can stay, it gains nothing (fp32, 32768 of 64 1133, 2407, 1120 and 1098, 2386,
+    // 1091; 65536 of 64 2197, 4927, 2189 and 2188, 4922, 2185; bf16, 65536 of 40 700, 1466, 685 and 707, 1477, 675, the scores alone 250 and 285).
+    // With less than 40 MB, which about fits the L2s, the hint is better (512 units of 64 tokens 13.95 and 14.33).
     const bool full_tiles = n_src * 8 > (n_src + 31) / 32 * 32 * 7;
-    const bool keep_k = (size_t)n_units * (size_t)n_src * (size_t)a.row_bytes >= ((size_t)40 << 20) && !(full_tiles && a.row_bytes <= 256);
+    const size_t k_bytes = (size_t)n_units * (size_t)n_src * (size_t)a.row_bytes;
+    const bool keep_k = k_bytes >= ((size_t)40 << 20) && k_bytes <= ((size_t)512 << 20) && !(full_tiles && a.row_bytes <= 256);
     const int n_blocks = (n_src + 31) / 32;
     const int waves = n_blocks < 4 ? n_blocks : 4;
     const size_t lds_short = short_lds_bytes(waves, n_src, a.row_bytes);
