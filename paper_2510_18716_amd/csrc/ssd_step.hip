@@ -212,7 +212,7 @@ static __device__ __forceinline__ uint4 rope_fragment(const uint4 &raw, const fl
 // slots empty.  The partial sums of the waves are combined in another order than one wave adds them: outputs
 // and scores of the two forms agree to rounding, not to the bit.
 // Args: the argument block the launch carries (StepArgs: several layers).
-// FAR: a compression with one buffered candidate and more than 128 in all (a launch of one layer).
+// FAR: a compression with one buffered candidate and more than 128 in all (launches of four and five wave-loads per chunk).
 template <typename Args, typename T, int D, int CH, int WPB, bool FUSED, bool HEADS = false, bool ROPE = false, int SHARE = 1, bool FAR = false>
 __global__ __launch_bounds__(WPB * SHARE * 64) void step_kernel(Args) {          // read through fetch_args
     constexpr bool MANY = std::is_same<Args, StepArgs>::value;
@@ -598,6 +598,11 @@ static void launch_variant(const StepArgs &full, const HeadOrder *ho, dim3 block
             else if (far) hipLaunchKernelGGL((step_kernel<StepArgsOne, T, D, CH, WPB, true, false, false, SHARE, true>), blocks, threads, lds, s, x);
             else if (fused) hipLaunchKernelGGL((step_kernel<StepArgsOne, T, D, CH, WPB, true, false, false, SHARE>), blocks, threads, lds, s, x);
             else hipLaunchKernelGGL((step_kernel<StepArgsOne, T, D, CH, WPB, false, false, false, SHARE>), blocks, threads, lds, s, x);
+            return;
+        }
+        if (far) {
+            if (rope) hipLaunchKernelGGL((step_kernel<StepArgs, T, D, CH, WPB, true, false, true, SHARE, true>), blocks, threads, lds, s, full);
+            else hipLaunchKernelGGL((step_kernel<StepArgs, T, D, CH, WPB, true, false, false, SHARE, true>), blocks, threads, lds, s, full);
             return;
         }
         if (rope) {

@@ -553,6 +553,19 @@ def test_one_eviction_among_any_number_of_candidates(dtype, d, M, R, heads):
     _full_compare(wl, fused=True, lpc=1, export_every=1)
 
 
+@pytest.mark.parametrize("shape,dtype,d,R,rope,lpc,heads", [((4, 1, 0), "f32", 64, 1, 0, 1, False), ((4, 2, 0), "bf16", 128, 1, 0, None, False), ((4, 4, 0), "f32", 128, 0, 1, None, False),
+                                                            ((4, 4, 0), "bf16", 128, 1, 2, 1, False), ((4, 12, 0), "bf16", 64, 1, 0, None, False), ((4, 14, 0), "f32", 64, 1, 1, None, False),
+                                                            ((5, 14, 0), "bf16", 128, 1, 0, 1, False), ((2, 4, 0), "f32", 64, 1, 0, None, False), ((4, 4, 0), "f32", 64, 1, 0, 1, True),
+                                                            ((4, 12, 0), "f32", 64, 1, 1, 1, True)])
+def test_one_eviction_among_many_candidates_in_every_launch_shape(shape, dtype, d, R, rope, lpc, heads):
+    """More than 128 candidates: one wave per unit and units shared, the rotary step, budgets per head (some heads with fewer), one layer per
+    call and all; two wave-loads per chunk rank through LDS."""
+    own = [[5, 140, 70, 128], [5, 127, 140, 129]] if heads else None
+    wl = workload.Workload("one-eviction-shape", L=2, prompts=1, H=4, d=d, dtype=dtype, n0=134, grid_h=4, grid_w=4, W=5 if not heads else 140, M=140, S=1,
+                           R=R, C=R + 1, cadence=1, seed=91, plain=True, spatial_frac=0.25, head_budget=own)
+    _full_compare(wl, fused=True, lpc=lpc, export_every=1, rope=rope, shape=shape)
+
+
 @pytest.mark.parametrize("prompts,H,frac,rows,lpc", [(8, 16, 0.5, 9, 1), (9, 16, 0.5, 40, 1), (19, 32, 0.25, 33, 1), (19, 16, 0.5, 20, None), (7, 16, 0.5, 9, 1),
                                                      (43, 64, 0.5, 9, 1), (66, 32, 0.75, 12, None)])
 def test_units_dealt_to_the_xcds(prompts, H, frac, rows, lpc):
